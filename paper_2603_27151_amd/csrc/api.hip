@@ -52,8 +52,6 @@ struct soup_ctx {
     DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, frags, sorted;
     DevBuf region_counts, region_boff, flags;
     DevBuf log_frag, log_aux, log_counts, log_boff;   // the forward's fragment log
-    DevBuf frag_gates, sorted_gates;                  // ReLU gates of the kept and sorted fragments
-    bool frags_gated = false;        // the current fragment list carries the forward's gates
     DevBuf ssim;                                      // SSIM statistics of the training loss
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
     DevBuf gtex;                                      // its texture gradient when levels are asked for and the sorted path cannot fold them in
@@ -170,15 +168,6 @@ struct Timed {
 }  // namespace
 
 namespace soup {
-
-int gate_words(MlpKind k) {
-    switch (k) {
-        case MlpKind::k8_16_1: return 1;
-        case MlpKind::k16_32_2: return 2;
-        case MlpKind::k32_64_2: return 4;
-        default: return 0;
-    }
-}
 
 MlpKind mlp_kind(int n_layers, const int32_t* dims) {
     if (n_layers == 2 && dims[0] == 8 && dims[1] == 16 && dims[2] == 4) return MlpKind::k8_16_1;
@@ -590,7 +579,7 @@ void soup_ctx_destroy(soup_ctx* c) {
                       &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
                       &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
                       &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                      &c->chunk_base, &c->frag_gates, &c->sorted_gates, &c->gvert, &c->gtex};
+                      &c->chunk_base, &c->gvert, &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
@@ -676,7 +665,7 @@ soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
                             &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
                             &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
                             &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                            &c->chunk_base, &c->frag_gates, &c->sorted_gates, &c->gvert, &c->gtex};
+                            &c->chunk_base, &c->gvert, &c->gtex};
     int64_t n = 0;
     for (const DevBuf* b : bufs) n += static_cast<int64_t>(b->bytes);
     *bytes = n;
@@ -709,10 +698,7 @@ int decode_blocks(soup_ctx* c) { return std::max(1, std::min(c->num_cus * 4, kMa
 // *n_frag and of decode batches in *n_batch.
 soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64_t* vis, const float* grad_color,
                    const float* grad_logp, const float2* edge_w, bool all_front, int32_t* tri_count, int T,
-                   hipStream_t s, int64_t* n_frag, int64_t* n_batch, bool from_log = false, bool want_gates = false) {
-    // the forward's ReLU gates travel with the fragments when they come from its log
-    want_gates = want_gates && from_log;
-    c->frags_gated = want_gates;
+                   hipStream_t s, int64_t* n_frag, int64_t* n_batch, bool from_log = false) {
     if (p.n_pix >= (int64_t(1) << 32)) return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
     unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
     const int nb = from_log ? decode_blocks(c) : replay_blocks(c, p);
@@ -726,14 +712,11 @@ soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64
     if ((st = ensure(c, c->region_counts, static_cast<size_t>(kMaxRegions) * 4)) ||
         (st = ensure(c, c->region_boff, static_cast<size_t>(kMaxRegions + 1) * 4)))
         return st;
-    const int gw = gate_words(p.kind);
     auto launch = [&](uint64_t reg) {
         if (from_log) {
             CollectArgs ca{};
             ca.log_frag = static_cast<uint4*>(c->log_frag.p);
             ca.log_aux = static_cast<uint2*>(c->log_aux.p);
-            ca.gate_words = gw;   // the log's record layout
-            if (want_gates) ca.frag_gates = static_cast<uint32_t*>(c->frag_gates.p);
             ca.log_region = static_cast<uint32_t>(c->log_region);
             ca.log_counts = static_cast<uint32_t*>(c->log_counts.p);
             ca.log_boff = static_cast<uint32_t*>(c->log_boff.p);
@@ -771,9 +754,6 @@ soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64
         if (c->frag_regions != nr || c->frag_region == 0)
             return fail(c, SOUP_ERR_CAPACITY, "static mode: no fragment list sized for this call; run it once "
                         "outside static mode");
-        if (want_gates && c->frag_gates.bytes < static_cast<size_t>(c->frag_region) * nr * gate_stride(gw) * 4)
-            return fail(c, SOUP_ERR_CAPACITY, "static mode: no gate list sized for this call; run it once "
-                        "outside static mode");
         launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
         if (tri_count) launch_fill_i32(tri_count, T, 0, s);
         launch(c->frag_region);
@@ -786,8 +766,6 @@ soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64
     for (int attempt = 0; attempt < 2; ++attempt) {
         if (region >= (uint64_t(1) << 31)) return fail(c, SOUP_ERR_CAPACITY, "fragment region too large");
         if ((st = ensure(c, c->frags, static_cast<size_t>(region) * nr * sizeof(FragRec)))) return st;
-        if (want_gates && (st = ensure(c, c->frag_gates, static_cast<size_t>(region) * nr * gate_stride(gw) * 4)))
-            return st;
         {
             Timed t(c, SOUP_T_FILL, s);
             launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
@@ -838,7 +816,7 @@ static soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, Ras
                                      : (static_cast<uint64_t>(p.n_pix) * 2) / log_nr + 1024;
             if (log_region >= (uint64_t(1) << 31)) return fail(c, SOUP_ERR_CAPACITY, "fragment log region too large");
             if ((st = ensure(c, c->log_frag, static_cast<size_t>(log_region) * log_nr * sizeof(uint4))) ||
-                (st = ensure(c, c->log_aux, static_cast<size_t>(log_region) * log_nr * aux_words(gate_words(p.kind)) * 4)) ||
+                (st = ensure(c, c->log_aux, static_cast<size_t>(log_region) * log_nr * sizeof(uint2))) ||
                 (st = ensure(c, c->log_counts, static_cast<size_t>(kMaxRegions) * 4)) ||
                 (st = ensure(c, c->log_boff, static_cast<size_t>(kMaxRegions + 1) * 4)))
                 return st;
@@ -988,21 +966,11 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     }
     int64_t n_frag = 0, n_batch = 0;
     if ((st = replay(c, p, a, vis, grad_color, gl, ew, false, static_cast<int32_t*>(c->tri_count.p), T, s, &n_frag,
-                     &n_batch, from_log, true)))
+                     &n_batch, from_log)))
         return st;
     // the list sorted by triangle has at most as many entries as the regions hold
     const int64_t frag_cap = static_cast<int64_t>(c->frag_regions) * static_cast<int64_t>(c->frag_region);
-    const int gw = gate_words(p.kind);
-    if (!c->frags_gated) {
-        // replayed fragments: their ReLU gates from a decode in the forward's arithmetic
-        if ((st = ensure(c, c->frag_gates, static_cast<size_t>(frag_cap) * gate_stride(gw) * 4))) return st;
-        Timed t(c, SOUP_T_REPLAY, s);
-        launch_fragment_gates(decode_args(c, p, a), p.kind, static_cast<uint32_t*>(c->frag_gates.p), s);
-        c->frags_gated = true;
-    }
     if ((st = ensure(c, c->sorted, static_cast<size_t>(frag_cap) * sizeof(FragRec)))) return st;
-    if (c->frags_gated && (st = ensure(c, c->sorted_gates, static_cast<size_t>(frag_cap) * gate_stride(gw) * 4)))
-        return st;
     {
         Timed t(c, SOUP_T_GRAD, s);
         launch_scan(static_cast<int32_t*>(c->tri_count.p), T, static_cast<int64_t*>(c->tri_bsum.p),
@@ -1017,11 +985,6 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
         pa.tri_off = static_cast<int64_t*>(c->tri_off.p);
         pa.tri_fill = static_cast<unsigned long long*>(c->tri_fill.p);
         pa.sorted = static_cast<FragRec*>(c->sorted.p);
-        if (c->frags_gated) {
-            pa.frag_gates = static_cast<uint32_t*>(c->frag_gates.p);
-            pa.sorted_gates = static_cast<uint32_t*>(c->sorted_gates.p);
-            pa.gate_words = gw;
-        }
         pa.n_blocks = decode_blocks(c);
         launch_place(pa, s);
     }
@@ -1035,7 +998,6 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     {
         DecodeArgs d = decode_args(c, p, a);
         d.sorted = static_cast<FragRec*>(c->sorted.p);
-        d.sorted_gates = c->frags_gated ? static_cast<uint32_t*>(c->sorted_gates.p) : nullptr;
         d.tri_off = static_cast<int64_t*>(c->tri_off.p);
         d.grad_color = grad_color;
         d.edge_w = ew;

@@ -9,8 +9,4 @@ void launch_decode_bwd_k16_32_2(const DecodeArgs& a, bool logp, hipStream_t s) {
 
 size_t decode_bwd_lds_k16_32_2(int G, bool logp) { return decode_bwd_lds_s<MlpShape<16, 32, 2>>(G, logp); }
 
-void launch_fragment_gates_k16_32_2(const DecodeArgs& a, uint32_t* gates_out, hipStream_t s) {
-    launch_fragment_gates_s<MlpShape<16, 32, 2>>(a, gates_out, s);
-}
-
 }  // namespace soup

@@ -4,7 +4,8 @@
 //
 // The backward walks the fragment list sorted by triangle: every wave takes a
 // contiguous range of 64-fragment batches. For each batch:
-//   - recompute the bilinear feature and the MLP (float32, as the forward);
+//   - recompute the bilinear feature and the MLP (the forward's float32
+//     sequence, so its hidden layers and ReLU decisions are the forward's);
 //   - logit gradients: winner -> colour path g_C sigma'(o_rgb) and score
 //     g_L (1 - alpha); fragment in front -> score -g_L alpha (Eq. (9) through
 //     the sigmoid);
@@ -64,10 +65,12 @@ struct StageCfg {
 // v_mfma_f32_16x16x4f32 (A[m][k] = d[f_k][m], B[k][n] = a[f_k][n]); dW is
 // tiled in 16x16 blocks held in registers (4 per lane per block), padded
 // with zeros where DIN or DOUT is below 16. The bias gradient sum_f d_f is
-// kept per lane in the unit-major layout of d (units 16 bo + 4 grp + i of the
+// kept per lane in the unit-major layout of d (units 16 bo + 4 i + grp of the
 // lane's fragments; for the output layer, OUTL, output grp in element 0) and
-// summed over the lanes of a lane group at the end.
-template <int DIN, int DOUT, bool OUTL = false>
+// summed over the lanes of a lane group at the end. Staged rows of hidden units
+// are in position order (UIN: the inputs are hidden units, else channels); the
+// outputs are hidden units except in the output layer.
+template <int DIN, int DOUT, bool UIN, bool OUTL = false>
 struct LayerAcc {
     static constexpr int BI = (DIN + 15) / 16;
     static constexpr int BO = (DOUT + 15) / 16;
@@ -126,7 +129,8 @@ struct LayerAcc {
             for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int m = 16 * bo + 4 * (lane >> 4) + i, n = 16 * bi + (lane & 15);
+                    const int m = 16 * bo + (OUTL ? 4 * (lane >> 4) + i : 4 * i + (lane >> 4));
+                    const int n = 16 * bi + (UIN ? unit_of(lane & 15) : lane & 15);
                     if (m < DOUT && n < DIN) row[w_off + m * DIN + n] = w[bo * BI + bi][i];
                 }
         // bias: sum over the 16 lanes (fragments) of each lane group
@@ -143,7 +147,7 @@ struct LayerAcc {
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int m = 16 * bo + 4 * (lane >> 4) + i;
+                        const int m = 16 * bo + 4 * i + (lane >> 4);
                         if (m < DOUT) row[b_off + m] = v[i];
                     }
                 }
@@ -154,7 +158,7 @@ struct LayerAcc {
 
 // The output layer's weight gradient dW[4][DIN] += sum_f d_f a_f^T on
 // v_mfma_f32_4x4x1f32: block b (lanes 4b .. 4b + 3) accumulates the 4 x 4
-// tile of units 4 (b % 8) .. + 3 over the fragments of half b / 8 of the 16
+// tile of positions 4 (b % 8) .. + 3 over the fragments of half b / 8 of the 16
 // staged rows, one fragment per product (A = the fragment's four output
 // deltas, B = its four units); the two halves are added at the end. The
 // bias gradient as in LayerAcc (output grp in element 0 of lane group grp).
@@ -186,9 +190,9 @@ struct OutAcc {
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] = pair32f(w[i], w[i]);
         if (lane < 32) {
-            const int t = lane >> 2, j = lane & 3;
+            const int pos = lane;   // tile lane / 4, column lane & 3
 #pragma unroll
-            for (int i = 0; i < 4; ++i) row[w_off + i * DIN + 4 * t + j] = s[i];
+            for (int i = 0; i < 4; ++i) row[w_off + i * DIN + 16 * (pos >> 4) + unit_of(pos & 15)] = s[i];
         }
         f4v v = bs[0];
 #pragma unroll
@@ -199,7 +203,7 @@ struct OutAcc {
 
 template <class S, bool OUT4 = (S::H == 32)>
 struct OutAccOf {
-    using type = LayerAcc<S::H, 4, true>;
+    using type = LayerAcc<S::H, 4, true, true>;
 };
 template <class S>
 struct OutAccOf<S, true> {
@@ -208,8 +212,8 @@ struct OutAccOf<S, true> {
 
 template <class S>
 struct MlpGrad {
-    LayerAcc<S::C, S::H> l0;
-    LayerAcc<S::H, S::H> mid[S::NH > 1 ? S::NH - 1 : 1];
+    LayerAcc<S::C, S::H, false> l0;
+    LayerAcc<S::H, S::H, true> mid[S::NH > 1 ? S::NH - 1 : 1];
     typename OutAccOf<S>::type out;
 };
 
@@ -272,13 +276,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     uint2 nx = make_uint2(0u, 0u);           // (score weight, view)
     float ng0 = 0.f, ng1 = 0.f, ng2 = 0.f, nex = 0.f, ney = 0.f;
     bool nvalid = false;
-    constexpr int GW = GateWords<S>::kWords;
-    // the forward's ReLU gates of every sorted fragment (from its log, or from
-    // fragment_gates_kernel for a replayed list): the host always provides them
-    const bool use_gates = !LOGP;
-    uint32_t ngate[GW];
-#pragma unroll
-    for (int k = 0; k < GW; ++k) ngate[k] = 0u;
     auto prefetch = [&](uint64_t bi) __attribute__((always_inline)) {
         const int64_t fi = static_cast<int64_t>(bi) * 64 + lane;
         nvalid = bi < b_end && fi < E;
@@ -286,14 +283,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             const FragRec fr = a.sorted[fi];
             na = make_uint4(fr.p0.x, fr.p0.y, fr.p1.x, fr.p1.y);
             nx = fr.x;
-            if (use_gates) {
-#pragma unroll
-                for (int k = 0; k < GW; k += 2) {   // 8-byte units of the padded gate record
-                    const uint2 g = reinterpret_cast<const uint2*>(a.sorted_gates)[fi * (gate_stride(GW) / 2) + k / 2];
-                    ngate[k] = g.x;
-                    if (k + 1 < GW) ngate[k + 1] = g.y;
-                }
-            }
         }
     };
     auto pixfetch = [&]() __attribute__((always_inline)) {
@@ -337,9 +326,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     for (uint64_t bi = b_begin; bi < b_end; bi += b_step) {
         bool on;
         uint4 fa = make_uint4(0u, 0u, 0u, 0u), fb4 = make_uint4(0u, 0u, 0u, 0u), fc4 = make_uint4(0u, 0u, 0u, 0u);
-        uint32_t gt[GW];   // this lane's fragment: the forward's ReLU gates
-#pragma unroll
-        for (int k = 0; k < GW; ++k) gt[k] = ngate[k];
         if (LOGP) {
             int lo = 0, hi = a.n_regions - 1;   // region: last w with boff[w] <= bi
             while (lo < hi) {
@@ -438,7 +424,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             __builtin_amdgcn_s_setprio(2);
             for (int nb = 0; nb < 4; ++nb) {   // fragment 16 nb + col (lane 16 nb + col holds its record)
                 // inputs, unit-major: channels 16 cb + 4 grp .. + 3 (an empty lane's
-                // weights are zero; channels past C meet zero weights in layer 0)
+                // weights are zero; channels past C enter no step of layer 0)
                 f4v xin[CB];
                 // d feature / d fx and d feature / d fy at the fragment's texture
                 // position (bilinear), the directions in which a winner's vertices
@@ -460,31 +446,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                     }
                 }
                 if (nb < 3) gather(nb + 1);
-                // the block fragment's gates of this lane's units 16 ob + 4 grp + i
-                uint32_t gate0[HB], gate1[HB];
+                // channels in the order of the layer's steps
 #pragma unroll
-                for (int ob = 0; ob < HB; ++ob) {
-                    gate0[ob] = 0u;
-                    gate1[ob] = 0u;
-                }
-                if (use_gates) {
-#pragma unroll
-                    for (int ob = 0; ob < HB; ++ob) {
-                        constexpr int kH = S::H;
-                        const int b0 = 16 * ob, b1 = kH + 16 * ob;   // first unit of the block, layers 0 and 1
-                        const uint32_t w0 = row_bcast(gt[b0 >> 5], nb);
-                        gate0[ob] = (w0 >> ((b0 & 31) + 4 * grp)) & 0xFu;
-                        if constexpr (S::NH == 2) {
-                            const uint32_t w1 = row_bcast(gt[b1 >> 5], nb);
-                            gate1[ob] = (w1 >> ((b1 & 31) + 4 * grp)) & 0xFu;
-                        }
-                    }
-                }
+                for (int cb = 0; cb < CB; ++cb) xin[cb] = transpose_rows(xin[cb]);
                 // forward
                 f4v h0[HB];
-                mfma_layer_gated<HB, CB>(Wt.l0, Wt.b0, xin, h0, lane, use_gates, gate0);
+                mfma_layer<HB, CB, S::C>(Wt.l0, Wt.b0, xin, h0, lane);
                 f4v h1[S::NH == 2 ? HB : 1];
-                if constexpr (S::NH == 2) mfma_layer_gated<HB, HB>(Wt.l1, Wt.b1, h0, h1, lane, use_gates, gate1);
+                if constexpr (S::NH == 2) mfma_layer<HB, HB, S::H>(Wt.l1, Wt.b1, h0, h1, lane);
                 const f4v (&hl)[HB] = *reinterpret_cast<const f4v (*)[HB]>(S::NH == 2 ? &h1[0] : &h0[0]);
                 // output layer and the logit gradients (Eq. (9) through the sigmoid for the score term)
                 float dO;   // lane group j: output j of the fragment
@@ -492,7 +461,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                 const bool win_n = (row_bcast(fkey, nb) >> 31) != 0;
                 const float gl_n = row_bcast(__uint_as_float(fb4.x), nb);
                 {
-                    // lane group g: outputs 0..3 summed over its own units 16 ib + 4 g + s
+                    // lane group g: outputs 0..3 summed over its own units 16 ib + 4 s + g
                     f4v pr = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int ib = 0; ib < HB; ++ib) {
@@ -563,7 +532,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                     }
                 }
                 // first-layer weight gradient
-                stage_rows<CB>(st, S::C, xin, lane);
+                stage_channels<CB>(st, S::C, xin, lane);
                 stage_rows<HB>(st + kStageRows * (S::C + kRowPad), S::H, dh0, lane);
                 wave_fence();
                 acc.l0.accumulate(st, st + kStageRows * (S::C + kRowPad), lane);
@@ -848,51 +817,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         if constexpr (S::NH == 2) acc.mid[0].store(row, S::w_off(1), S::b_off(1), lane);
         acc.out.store(row, S::w_off(S::NH), S::b_off(S::NH), lane);
     }
-}
-
-// The forward's ReLU gates of every fragment of a replayed list (a backward
-// without the forward's log): each lane decodes its fragment with the
-// forward's float32 arithmetic (the contract's texture fetch and MLP, from the
-// same barycentrics) and keeps the gates in gates_out, at the fragment's slot
-// of the region list. Waves take batches as the logp decode does.
-template <class S>
-__global__ __launch_bounds__(256) void fragment_gates_kernel(DecodeArgs a, uint32_t* __restrict__ gates_out) {
-    constexpr int NW = 4, GW = GateWords<S>::kWords;
-    __shared__ uint32_t s_boff[kMaxRegions + 1];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int i = tid; i <= a.n_regions; i += blockDim.x) s_boff[i] = a.boff[i];
-    __syncthreads();
-    gfloat* __restrict__ feats = as_global(uniform_ptr(a.feats));
-    const uint32_t n_batch = s_boff[a.n_regions];
-    const uint32_t n_waves = gridDim.x * NW;
-    for (uint32_t bi = blockIdx.x * NW + w; bi < n_batch; bi += n_waves) {
-        int lo = 0, hi = a.n_regions - 1;   // region: last w with boff[w] <= bi
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_boff[mid] <= bi) lo = mid;
-            else hi = mid - 1;
-        }
-        const uint32_t cr = a.counts[lo];
-        const uint32_t in_region = (bi - s_boff[lo]) * 64u + static_cast<uint32_t>(lane);
-        if (in_region >= (cr < a.region ? cr : a.region)) continue;
-        const uint64_t at = static_cast<uint64_t>(lo) * a.region + in_region;
-        const FragRec fr = a.frags[at];
-        const Cell c = cell_of(__uint_as_float(fr.p1.x), __uint_as_float(fr.p1.y), a.G);
-        float x[S::C];
-        fetch_feature<S::C>(feats, fr.p0.y & 0x7FFFFFFFu, a.G, c, x);
-        float o[4];
-        uint32_t g[GW];
-        mlp_logits_gates<S>(as_const(opaque_ptr(a.mlp)), x, o, g);
-#pragma unroll
-        for (int k = 0; k < GW; k += 2)   // the padded gate record, 8 bytes at a time
-            reinterpret_cast<uint2*>(gates_out)[at * (gate_stride(GW) / 2) + k / 2] =
-                make_uint2(g[k], k + 1 < GW ? g[k + 1] : 0u);
-    }
-}
-
-template <class S>
-static void launch_fragment_gates_s(const DecodeArgs& a, uint32_t* gates_out, hipStream_t s) {
-    hipLaunchKernelGGL(fragment_gates_kernel<S>, dim3(a.n_blocks), dim3(256), 0, s, a, gates_out);
 }
 
 // Bytes of LDS one workgroup of the decode needs (static + dynamic), or 0 when

@@ -4,30 +4,37 @@
 //
 // Operand layout of the instruction (lane l, col = l & 15, grp = l >> 4): the
 // lane supplies A[col][grp] and B[grp][col] (K = 4 runs over the four lane
-// groups) and holds D[4 grp + i][col], i = 0..3.
+// groups) and holds D[4 grp + i][col], i = 0..3. Each product is the float32
+// chain fma(A[.][3], B[3][.], ... fma(A[.][0], B[0][.], C)): one rounding per
+// step, k ascending, denormals kept (checked bit for bit against fmaf on
+// gfx950, infinities and NaN included).
 //
-// Activations are kept unit-major: an f4v act[ub][nb] holds units
-// 16 ub + 4 grp + i of fragment 16 nb + col. A layer out = W in runs as
-// D = W act with the contraction over input units split in steps of four,
-// step s of input block ib taking unit 16 ib + 4 grp + s in lane group grp;
-// the B operand of step s is then register s of the previous layer's D, so
-// layers chain without moving data between lanes, and the A operand is the
-// weight W[16 ob + col][16 ib + 4 grp + s] (pre-arranged in LDS, four steps
-// per 16-byte read). The output layer (four outputs) runs on
+// Activations are kept unit-major: element i of an f4v act[ub][nb] holds unit
+// 16 ub + 4 i + grp of fragment 16 nb + col (rows of the A operand are ordered
+// so: row 4 grp + i is that unit). A layer out = W in runs as D = W act, step s
+// of input block ib taking unit 16 ib + 4 s + grp in lane group grp: the B
+// operand of step s is then register s of the previous layer's D, so layers
+// chain without moving data between lanes, and the contraction runs over the
+// units in ascending order, which is the forward's own float32 sequence. The
+// recompute's hidden layers are therefore bit for bit the forward's, and so
+// are its ReLU decisions: nothing of them is stored between the two (logged
+// gate bits cost the log, its filter and the sort 8 bytes of 32 per fragment).
+// The A operands are pre-arranged in LDS, four steps per 16-byte read. The
+// input features arrive as four consecutive channels per lane group and are
+// transposed into this order by four row swaps. The output layer (four
+// outputs) runs on
 // v_mfma_f32_4x4x1f32, sixteen independent 4x4 blocks of four lanes each
 // (lane 4b + j supplies A[j][0] and B[0][j] of block b and holds D[i][j] in
 // register i): block b's lanes share one lane group, so its B operand is the
-// hidden units 16 ib + 4 grp + s of four fragments and its A operand the four
+// hidden units 16 ib + 4 s + grp of four fragments and its A operand the four
 // outputs' weights of those units; the four lane groups' partial sums are
 // then summed across rows with row swaps so that lane group j ends with
 // output j of every fragment, which is exactly the B operand of the first
 // backward product (K = the 4 outputs).
 // Weight gradients contract over fragments, the other index; activations and
-// deltas are staged through LDS as rows, 16 fragments at a time.
-//
-// The backward needs no bit-exact forward (only the forward's mask decision
-// is fixed by the contract), so the recompute may sum in the matrix cores'
-// order.
+// deltas are staged through LDS as rows, 16 fragments at a time, each row in
+// position order (position 16 b + 4 grp + i = element i of lane group grp);
+// the store of the sums puts them back in unit order.
 #include "raster_common.hpp"
 
 namespace soup {
@@ -63,6 +70,20 @@ __device__ __forceinline__ U2 swap16(uint32_t a, uint32_t b) {
 __device__ __forceinline__ U2 swap32(uint32_t a, uint32_t b) {
     const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
     return {static_cast<uint32_t>(r[0]), static_cast<uint32_t>(r[1])};
+}
+
+// Unit of position p (0..15) of a 16-unit block: element i = p & 3 of lane
+// group grp = p >> 2 holds unit 4 i + grp.
+__host__ __device__ constexpr int unit_of(int p) { return 4 * (p & 3) + (p >> 2); }
+
+// Channels 4 grp + i in element i of lane group grp -> channels 4 i + grp: a
+// 4x4 transpose between elements and rows, two row swaps per stage.
+__device__ __forceinline__ f4v transpose_rows(const f4v& v) {
+    const U2 p = swap16(__float_as_uint(v[0]), __float_as_uint(v[1]));   // (v0.r0, v1.r0, v0.r2, v1.r2), odd rows
+    const U2 q = swap16(__float_as_uint(v[2]), __float_as_uint(v[3]));
+    const U2 e = swap32(p.a, q.a);   // (v0.r0, v1.r0, v2.r0, v3.r0), (v0.r2, ...)
+    const U2 o = swap32(p.b, q.b);   // (v0.r1, ...), (v0.r3, ...)
+    return f4v{__uint_as_float(e.a), __uint_as_float(o.a), __uint_as_float(e.b), __uint_as_float(o.b)};
 }
 
 // Row n of x in every row: lane (row g, column c) receives lane 16 n + c.
@@ -153,14 +174,15 @@ struct MfmaWeights {
     static constexpr int CB = (S::C + 15) / 16;   // channel blocks
     static constexpr int HB = S::H / 16;          // hidden-unit blocks
     static constexpr int MB = S::NH == 2 ? HB : 1;
-    f4v l0[HB][CB][64];      // W0[16 ob + col][16 ib + 4 grp + s]
-    f4v l1[MB][MB][64];      // W1[16 ob + col][16 ib + 4 grp + s]
-    f4v lo[HB][64];          // W_out[lane & 3][16 ib + 4 grp + s]: A operand of the 4x4x1 output products
-    float loT[HB][64];       // W_out[grp][16 ob + col]
-    f4v l1T[MB][MB][64];     // W1[16 ib + 4 grp + s][16 ob + col]
-    f4v l0T[CB][HB][64];     // W0[16 ib + 4 grp + s][16 cb + col]
-    f4v b0[HB][64];          // b0[16 ob + 4 grp + i]
-    f4v b1[MB][64];          // b1[16 ob + 4 grp + i]
+    // u(col) = unit_of(col): the unit of row col
+    f4v l0[HB][CB][64];      // W0[16 ob + u(col)][16 ib + 4 s + grp]
+    f4v l1[MB][MB][64];      // W1[16 ob + u(col)][16 ib + 4 s + grp]
+    f4v lo[HB][64];          // W_out[lane & 3][16 ib + 4 s + grp]: A operand of the 4x4x1 output products
+    float loT[HB][64];       // W_out[grp][16 ob + u(col)]
+    f4v l1T[MB][MB][64];     // W1[16 ib + 4 s + grp][16 ob + u(col)]
+    f4v l0T[CB][HB][64];     // W0[16 ib + 4 s + grp][16 cb + col] (channels in natural order)
+    f4v b0[HB][64];          // b0[16 ob + 4 i + grp]
+    f4v b1[MB][64];          // b1[16 ob + 4 i + grp]
     float bo[64];            // b_out[grp]
 
     // Cooperative fill by the whole workgroup from the flat parameter array.
@@ -174,14 +196,14 @@ struct MfmaWeights {
             f4v v, t;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int k = 16 * ib + 4 * grp + s;
-                v[s] = k < S::C ? W0[(16 * ob + col) * S::C + k] : 0.0f;
+                const int k = 16 * ib + 4 * s + grp;
+                v[s] = k < S::C ? W0[(16 * ob + unit_of(col)) * S::C + k] : 0.0f;
             }
             l0[ob][ib][l] = v;
             // transposed: output block = channel block ib (as cb), input block = ob (as unit block)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int u = 16 * ob + 4 * grp + s, ch = 16 * ib + col;
+                const int u = 16 * ob + 4 * s + grp, ch = 16 * ib + col;
                 t[s] = ch < S::C ? W0[u * S::C + ch] : 0.0f;
             }
             l0T[ib][ob][l] = t;
@@ -191,13 +213,13 @@ struct MfmaWeights {
             f4v v, bb;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int k = 16 * b + 4 * grp + s;
+                const int k = 16 * b + 4 * s + grp;
                 v[s] = WO[(l & 3) * S::H + k];
-                bb[s] = B0[16 * b + 4 * grp + s];
+                bb[s] = B0[k];
             }
             lo[b][l] = v;
             b0[b][l] = bb;
-            loT[b][l] = WO[grp * S::H + 16 * b + col];
+            loT[b][l] = WO[grp * S::H + 16 * b + unit_of(col)];
         }
         if constexpr (S::NH == 2) {
             const float* W1 = p + S::w_off(1);
@@ -207,8 +229,8 @@ struct MfmaWeights {
                 f4v v, t;
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    v[s] = W1[(16 * ob + col) * S::H + 16 * ib + 4 * grp + s];
-                    t[s] = W1[(16 * ib + 4 * grp + s) * S::H + 16 * ob + col];
+                    v[s] = W1[(16 * ob + unit_of(col)) * S::H + 16 * ib + 4 * s + grp];
+                    t[s] = W1[(16 * ib + 4 * s + grp) * S::H + 16 * ob + unit_of(col)];
                 }
                 l1[ob][ib][l] = v;
                 l1T[ob][ib][l] = t;
@@ -217,7 +239,7 @@ struct MfmaWeights {
                 const int l = e & 63, b = e >> 6, grp = l >> 4;
                 f4v bb;
 #pragma unroll
-                for (int s = 0; s < 4; ++s) bb[s] = B1[16 * b + 4 * grp + s];
+                for (int s = 0; s < 4; ++s) bb[s] = B1[16 * b + 4 * s + grp];
                 b1[b][l] = bb;
             }
         }
@@ -225,9 +247,12 @@ struct MfmaWeights {
     }
 };
 
-// One 16-fragment block: out[ob] = act(bias + W in), IB input blocks, OB
-// output blocks.
-template <int OB, int IB, bool RELU>
+// max(x, 0), +0 for NaN, as the forward's ReLU (one instruction).
+__device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, __builtin_huge_valf()); }
+
+// One 16-fragment block: out[ob] = relu(bias + W in), IB input blocks holding
+// KIN inputs, OB output blocks.
+template <int OB, int IB, int KIN>
 __device__ __forceinline__ void mfma_layer(const f4v (*w)[IB][64], const f4v (*bias)[64], const f4v (&in)[IB],
                                            f4v (&out)[OB], int lane) {
 #pragma unroll
@@ -237,45 +262,11 @@ __device__ __forceinline__ void mfma_layer(const f4v (*w)[IB][64], const f4v (*b
         for (int ib = 0; ib < IB; ++ib) {
             const f4v wv = w[ob][ib][lane];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc = mfma4(wv[s], in[ib][s], acc);
-        }
-        if (RELU) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)   // max(x, 0) on the bit pattern: one integer max, no canonicalisation
-                acc[i] = __int_as_float(max(__float_as_int(acc[i]), 0));
-        }
-        out[ob] = acc;
-    }
-}
-
-// mfma_layer with the ReLU gate of unit 16 ob + 4 grp + i taken from bit i of
-// gate[ob] when use_gates (the forward's decision, logged by its bit-exact
-// decode), else from the sign of the recomputed value. The recompute sums in
-// the matrix cores' order, so a pre-activation within rounding of zero may
-// land on the other side of the kink than in the forward; the logged gate
-// keeps the forward's side. An open gate keeps at least FLT_MIN, so that the
-// "> 0" tests of the backward see it.
-template <int OB, int IB>
-__device__ __forceinline__ void mfma_layer_gated(const f4v (*w)[IB][64], const f4v (*bias)[64], const f4v (&in)[IB],
-                                                 f4v (&out)[OB], int lane, bool use_gates, const uint32_t (&gate)[OB]) {
-#pragma unroll
-    for (int ob = 0; ob < OB; ++ob) {
-        f4v acc = bias[ob][lane];
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib) {
-            const f4v wv = w[ob][ib][lane];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc = mfma4(wv[s], in[ib][s], acc);
+            for (int s = 0; s < 4; ++s)
+                if (16 * ib + 4 * s < KIN) acc = mfma4(wv[s], in[ib][s], acc);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (use_gates) {   // bit i of the gate as an all-ones or all-zeros mask
-                const int m = static_cast<int>(gate[ob] << (31 - i)) >> 31;
-                acc[i] = __int_as_float(__float_as_int(__builtin_fmaxf(acc[i], 0x1p-126f)) & m);
-            } else {
-                acc[i] = acc[i] > 0.0f ? acc[i] : 0.0f;
-            }
-        }
+        for (int i = 0; i < 4; ++i) acc[i] = relu(acc[i]);
         out[ob] = acc;
     }
 }
@@ -332,7 +323,7 @@ __device__ __forceinline__ void mfma_back2(const f4v (*wT)[IB][64], const f4v (&
 }
 
 // The 16 rows of one fragment block into an LDS stage laid out [row][D + kRowPad]
-// (D = n_units): lane (grp, col) writes its four units of row col.
+// (D = n_units): lane (grp, col) writes its four units of row col, in position order.
 template <int NBLK>
 __device__ __forceinline__ void stage_rows(float* __restrict__ st, int D, const f4v (&v)[NBLK], int lane) {
     const int col = lane & 15, grp = lane >> 4;
@@ -341,6 +332,18 @@ __device__ __forceinline__ void stage_rows(float* __restrict__ st, int D, const 
         const int u = 16 * b + 4 * grp;
         if (u < D) *reinterpret_cast<float4*>(st + col * (D + kRowPad) + u) = make_float4(v[b][0], v[b][1], v[b][2], v[b][3]);
     }
+}
+
+// The same for the input features (element s = channel 16 b + 4 s + grp), in
+// channel order.
+template <int NBLK>
+__device__ __forceinline__ void stage_channels(float* __restrict__ st, int D, const f4v (&v)[NBLK], int lane) {
+    const int col = lane & 15, grp = lane >> 4;
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (16 * b + 4 * s < D) st[col * (D + kRowPad) + 16 * b + 4 * s + grp] = v[b][s];
 }
 
 }  // namespace soup

@@ -55,21 +55,12 @@ struct RasterArgs {
     int n_blocks;                  // persistent grid of the forward (single-wave workgroups)
     int region;                    // side of a forward wave's region: 16 (tiles of 16, 32) or 8
     // optional log of the forward's decoded fragments, one region per wave (= workgroup):
-    // log_frag = (pixel, triangle, b1, b2); log_aux = aux_words(gate_words) words per
-    // fragment: depth bits, view, then the decode's ReLU gates (zero-padded to an even count)
+    // log_frag = (pixel, triangle, b1, b2), log_aux = (depth bits, view)
     uint4* log_frag;
     uint2* log_aux;
     uint32_t log_region;
     uint32_t* log_counts;
 };
-
-// Words of ReLU gate bits a decode of this MLP shape logs (one bit per hidden unit).
-int gate_words(MlpKind k);
-// Words of one log_aux record: depth bits, view and the gates, rounded up to an even count.
-__host__ __device__ constexpr int aux_words(int gate_words) { return (2 + gate_words + 1) & ~1; }
-// Words per fragment in the gate arrays beside the fragment lists: the gates padded to an
-// even count, so that every copy moves 8-byte units.
-__host__ __device__ constexpr int gate_stride(int gate_words) { return (gate_words + 1) & ~1; }
 
 void launch_raster_fwd(const RasterArgs& a, int tile, MlpKind k, hipStream_t s);
 // Resident single-wave workgroups per CU of the forward kernel for a tile side, MLP shape and
@@ -117,10 +108,7 @@ void launch_replay(const ReplayArgs& a, int tile, hipStream_t s);
 // by the forward, since the forward's best key never drops below the winner's.
 struct CollectArgs {
     const uint4* log_frag;
-    const uint2* log_aux;          // aux_words(gate_words) words per logged fragment
-    uint32_t* frag_gates;          // the log's ReLU gates of every kept fragment (same slots as frags, gate_stride
-                                   // words each), or null
-    int gate_words;
+    const uint2* log_aux;          // (depth bits, view) per logged fragment
     uint32_t log_region;
     const uint32_t* log_counts;    // [log_regions]
     const uint32_t* log_boff;      // [log_regions + 1] batch offsets of the log
@@ -159,9 +147,6 @@ struct PlaceArgs {
     const int64_t* tri_off;        // [T + 1] exclusive scan of the per-triangle counts
     unsigned long long* tri_fill;  // [T] zeroed: winners placed (low 32 bits), others (high 32 bits)
     FragRec* sorted;               // [tri_off[T]]
-    const uint32_t* frag_gates;    // ReLU gates of frags (gate_words each), or null
-    uint32_t* sorted_gates;        // ... placed as sorted
-    int gate_words;
     int n_blocks;
 };
 
@@ -183,7 +168,6 @@ struct DecodeArgs {
     int n_regions;
     // backward: the list sorted by triangle
     const FragRec* sorted;         // [tri_off[T]]
-    const uint32_t* sorted_gates;  // the forward's ReLU gates of each sorted fragment, or null (recomputed)
     const int64_t* tri_off;        // [T + 1]
     const float* verts;            // [T, 3, 3]: the winners' clip coordinates are recomputed
     const float* grad_color;       // [P, 3]: the winners' colour gradients
@@ -198,9 +182,6 @@ struct DecodeArgs {
 };
 
 void launch_decode_bwd(const DecodeArgs& a, MlpKind k, bool logp_pass, hipStream_t s);
-// The forward's ReLU gates of a replayed fragment list (a.frags, a.region, a.counts,
-// a.boff, a.n_regions), gate_words(k) words per slot into gates_out.
-void launch_fragment_gates(const DecodeArgs& a, MlpKind k, uint32_t* gates_out, hipStream_t s);
 // LDS bytes one workgroup of the decode needs for a grid side G (0: unknown).
 size_t decode_bwd_lds(MlpKind k, int G, bool logp_pass);
 // ew[p] = (x, y) edge weights of the pairs pixel p occludes (Section 3.2),

@@ -199,10 +199,6 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
         int pl = 0;
         bool pass = false;
         float o[4] = {0.f, 0.f, 0.f, 0.f};
-        constexpr int GW = GateWords<S>::kWords;
-        uint32_t gates[GW > 0 ? GW : 1];
-#pragma unroll
-        for (int w = 0; w < GW; ++w) gates[w] = 0u;
         if (act) {
             key = L.qkey[lane];
             pl = static_cast<int>(L.qpl[lane]);
@@ -226,9 +222,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                 fetch_feature<S::C>(feats, tri, G, c, x);
                 // an opaque copy of the weight pointer per batch: the compiler may
                 // not hoist the weights' scalar loads out of the traversal loops
-                // (the ReLU gates are kept for the log; forming them costs two
-                // instructions per hidden unit)
-                mlp_logits_gates<S>(as_const(opaque_ptr(mlp_p)), x, o, gates);
+                mlp_logits<S>(as_const(opaque_ptr(mlp_p)), x, o);
                 if (a.o.mode == 0) {
                     const float alpha = sigmoid_c(o[3]);
                     const uint32_t pidx = static_cast<uint32_t>(gy * W + gx);
@@ -244,11 +238,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                     const int64_t pg = pix_base + static_cast<int64_t>(gy) * W + gx;
                     a.log_frag[log_base + at] =
                         make_uint4(static_cast<uint32_t>(pg), tri, __float_as_uint(b1), __float_as_uint(b2));
-                    constexpr int AW2 = aux_words(GW) / 2;
-                    uint2* ax = a.log_aux + (log_base + at) * AW2;
-                    ax[0] = make_uint2(static_cast<uint32_t>(key >> 32), static_cast<uint32_t>(v));
-#pragma unroll
-                    for (int w = 0; w < GW; w += 2) ax[1 + w / 2] = make_uint2(gates[w], w + 1 < GW ? gates[w + 1] : 0u);
+                    a.log_aux[log_base + at] = make_uint2(static_cast<uint32_t>(key >> 32), static_cast<uint32_t>(v));
                 }
             }
         }

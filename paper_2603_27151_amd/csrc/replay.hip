@@ -320,13 +320,6 @@ __global__ __launch_bounds__(256) void place_kernel(PlaceArgs a) {
             const int64_t dst = win ? a.tri_off[tri] + static_cast<int64_t>(hb & 0xFFFFFFFFull) + w_before
                                     : a.tri_off[tri + 1] - 1 - static_cast<int64_t>(hb >> 32) - ((lane - hl) - w_before);
             a.sorted[dst] = fr;
-            if (a.frag_gates) {   // 8-byte units of the padded gate record
-                const uint64_t src = static_cast<uint64_t>(lo) * a.region + in_region;
-                const int g2 = gate_stride(a.gate_words) / 2;
-                const uint2* gs = reinterpret_cast<const uint2*>(a.frag_gates) + src * g2;
-                uint2* gd = reinterpret_cast<uint2*>(a.sorted_gates) + static_cast<uint64_t>(dst) * g2;
-                for (int w = 0; w < g2; ++w) gd[w] = gs[w];
-            }
         }
     }
 }
@@ -367,8 +360,7 @@ __global__ __launch_bounds__(256) void collect_kernel(CollectArgs a) {
         if (on) {
             const uint64_t at = static_cast<uint64_t>(lo) * a.log_region + in_region;
             const uint4 e = a.log_frag[at];
-            const int aw2 = aux_words(a.gate_words) / 2;
-            const uint2 x = a.log_aux[at * aw2];
+            const uint2 x = a.log_aux[at];
             const uint64_t key = (static_cast<uint64_t>(x.x) << 32) | e.y;
             const uint64_t kstar = a.vis[e.x];
             win = key == kstar;
@@ -384,16 +376,7 @@ __global__ __launch_bounds__(256) void collect_kernel(CollectArgs a) {
         }
         const uint64_t km = __ballot(keep);
         const uint32_t pos = cursor + static_cast<uint32_t>(__popcll(km & lanemask_lt()));
-        if (keep && pos < a.region) {
-            a.frags[out_base + pos] = fr;
-            if (a.frag_gates) {   // the aux record's gates (words 2.., zero-padded to even) as 8-byte units
-                const uint64_t at = static_cast<uint64_t>(lo) * a.log_region + in_region;
-                const int g2 = gate_stride(a.gate_words) / 2;
-                const uint2* g = a.log_aux + at * (aux_words(a.gate_words) / 2) + 1;
-                uint2* gd = reinterpret_cast<uint2*>(a.frag_gates) + (out_base + pos) * g2;
-                for (int w = 0; w < g2; ++w) gd[w] = g[w];
-            }
-        }
+        if (keep && pos < a.region) a.frags[out_base + pos] = fr;
         // fragments per triangle, counting only those stored (one atomic per
         // run of equal triangles among consecutive lanes)
         if (a.tri_count) {
