@@ -48,6 +48,7 @@ struct soup_ctx {
     std::string err;
     soup_stats stats{};
     DevBuf views, scenes, recs, tile_count, tile_fill, tile_start, bsum, entries, edge_w, partial, counters;
+    DevBuf fwd_weights;  // every scene's MLP weights as the forward's matrix operands
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
     DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, frags, sorted;
     DevBuf region_counts, region_boff, flags;
@@ -579,7 +580,7 @@ void soup_ctx_destroy(soup_ctx* c) {
                       &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
                       &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
                       &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                      &c->chunk_base, &c->gvert, &c->gtex};
+                      &c->chunk_base, &c->fwd_weights, &c->gvert, &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
@@ -665,7 +666,7 @@ soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
                             &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
                             &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
                             &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                            &c->chunk_base, &c->gvert, &c->gtex};
+                            &c->chunk_base, &c->fwd_weights, &c->gvert, &c->gtex};
     int64_t n = 0;
     for (const DevBuf* b : bufs) n += static_cast<int64_t>(b->bytes);
     *bytes = n;
@@ -792,6 +793,15 @@ soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64
     return SOUP_OK;
 }
 
+// The forward's work counter and weight operands.
+static soup_status fwd_begin(soup_ctx* c, const Plan& p, RasterArgs& a, hipStream_t s) {
+    soup_status st;
+    if ((st = ensure(c, c->fwd_weights, fwd_weights_bytes(p.kind) * p.scenes.size()))) return st;
+    a.weights = static_cast<float*>(c->fwd_weights.p);
+    launch_fwd_begin(a.scenes, static_cast<int>(p.scenes.size()), p.kind, a.work, static_cast<float*>(c->fwd_weights.p), s);
+    return SOUP_OK;
+}
+
 // The forward raster, with the log of its decoded fragments when `keep`: the
 // log is sized from the last call's largest region count (twice, so that a
 // static-mode call fits), its counts are scanned, and an eager call reads
@@ -826,7 +836,7 @@ static soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, Ras
         a.log_region = static_cast<uint32_t>(log_region);
         a.log_counts = static_cast<uint32_t*>(c->log_counts.p);
     }
-    launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
+    if ((st = fwd_begin(c, p, a, s))) return st;
     {
         Timed t(c, SOUP_T_FWD, s);
         launch_raster_fwd(a, c->tile, p.kind, s);
@@ -1061,7 +1071,7 @@ soup_status soup_render(soup_ctx* c, const soup_scene* scenes, int32_t R, const 
     RasterArgs a = raster_args(c, p, o);
     a.vis = nullptr;
     a.color = nullptr;
-    launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
+    if ((st = fwd_begin(c, p, a, s))) return st;
     {
         Timed t(c, SOUP_T_FWD, s);
         launch_raster_fwd(a, c->tile, p.kind, s);

@@ -52,6 +52,7 @@ struct RasterArgs {
     float* color;
     unsigned long long* counter;   // counters or null: [0] decodes, [8] pixels that some fragment covers
     unsigned int* work;            // persistent-kernel tile counter (zeroed by the launcher's caller)
+    const float* weights;          // forward: every scene's weights as matrix operands (launch_fwd_begin), or null
     int n_blocks;                  // persistent grid of the forward (single-wave workgroups)
     int region;                    // side of a forward wave's region: 16 (tiles of 16, 32) or 8
     // optional log of the forward's decoded fragments, one region per wave (= workgroup):
@@ -62,6 +63,11 @@ struct RasterArgs {
     uint32_t* log_counts;
 };
 
+// What a forward needs right before its raster: *work zeroed and, for the MLP shapes decoded on
+// the matrix cores, the weights of each scene in their operand order (fwd_weights_bytes per scene).
+size_t fwd_weights_bytes(MlpKind k);
+void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned int* work, float* weights,
+                      hipStream_t s);
 void launch_raster_fwd(const RasterArgs& a, int tile, MlpKind k, hipStream_t s);
 // Resident single-wave workgroups per CU of the forward kernel for a tile side, MLP shape and
 // region side (16: 16x16 pixels of a tile of 16 or 32; 8: one 8x8 block).

@@ -1,7 +1,7 @@
 // Forward raster dispatch over the compiled MLP shapes and tile sizes (the
 // kernel is in raster_fwd_impl.hpp, instantiated once per shape and tile in
 // fwd_*.hip so that the units compile in parallel).
-#include "internal.hpp"
+#include "raster_fwd_impl.hpp"
 
 namespace soup {
 
@@ -55,6 +55,28 @@ void launch_raster_fwd(const RasterArgs& a, int tile, MlpKind k, hipStream_t s) 
             else launch_raster_fwd_paper_t16(a, s);
             break;
         default: break;
+    }
+}
+
+size_t fwd_weights_bytes(MlpKind k) {
+    switch (k) {
+        case MlpKind::k16_32_2: return FwdWeights<MlpShape<16, 32, 2>>::kGroups * 16;
+        case MlpKind::k32_64_2: return FwdWeights<MlpShape<32, 64, 2>>::kGroups * 16;
+        default: return 0;
+    }
+}
+
+void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned int* work, float* weights,
+                      hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(n_scenes), 8), block(256);
+    switch (k) {
+        case MlpKind::k16_32_2:
+            hipLaunchKernelGGL((fwd_weights_kernel<MlpShape<16, 32, 2>>), grid, block, 0, s, scenes, work, weights);
+            break;
+        case MlpKind::k32_64_2:
+            hipLaunchKernelGGL((fwd_weights_kernel<MlpShape<32, 64, 2>>), grid, block, 0, s, scenes, work, weights);
+            break;
+        default: launch_fill_i32(reinterpret_cast<int32_t*>(work), 1, 0, s); break;
     }
 }
 

@@ -34,11 +34,12 @@
 // pixel: front-to-back early-out without sorting fragments. The result does
 // not depend on the visiting order (the draws are fixed by Philox), only the
 // amount of work does.
+#include "fwd_mfma.hpp"
 #include "pform.hpp"
 
 namespace soup {
 
-// A slice pair's geometry, one 16-byte aligned record (five 16-byte reads).
+// A slice pair's geometry and depth bound, one 16-byte aligned record (five 16-byte reads).
 struct alignas(16) PairGeo {
     double e0[3];        // orientation-normalised edge functions at the block's first pixel centre
     int32_t ndx[3];      // ... whose steps per pixel are -256 ndy in x and 256 ndx in y
@@ -46,18 +47,21 @@ struct alignas(16) PairGeo {
     float z[3];          // vertex depths
     float iw[3];         // 1 / w at the vertices
     float ra;            // 1 / |2 x area|
-    float pad;
+    uint32_t zmin;       // the list entry's depth bound
 };
-// A slice pair's run of combinations: coverage mask, list entry, first combination, block.
-struct alignas(8) PairMeta {
+// A slice pair's run of combinations (one 16-byte read): coverage mask, triangle, first
+// combination (below 64 x 64) | block << 16.
+struct alignas(16) PairMeta {
     uint32_t mlo, mhi;
-    uint32_t ent_lo, ent_hi;
-    int32_t off, blk;
+    uint32_t tri;
+    uint32_t off_blk;
 };
 
-// LDS of one wave owning NB 8x8 blocks.
-template <int NB>
+// LDS of one wave owning NB 8x8 blocks: with four blocks and the weights of
+// 16->32->32->4 13,488 bytes, so that twelve waves fit a CU's 160 KB.
+template <int NB, class S>
 struct FwdWaveLds {
+    f4v wts[FwdWeights<S>::kLds];   // the groups of the scene's weights that are kept here
     // the current slice: (triangle, block) pairs that cover a pixel of their block
     PairGeo geo[64];
     PairMeta meta[64];
@@ -75,7 +79,7 @@ struct FwdWaveLds {
     // the region's pixels: current best key (their colours go straight to the output)
     uint64_t key[64 * NB];
     // per round of the fragment step: the slice pair whose run of combinations starts here
-    int32_t head[64];
+    int8_t head[64];
     // counting only: the region's pixels that some fragment covers, per block (bits 0..31, 32..63)
     uint32_t cov[2 * NB];
 };
@@ -124,7 +128,9 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     static_assert(RS == 8 || (RS == 16 && TS >= 16), "a region is one 8x8 block, or 16x16 pixels of a larger tile");
     constexpr int BR = RS / 8, NB = BR * BR;       // 8x8 blocks per region
     constexpr int RT = TS / RS, RPT = RT * RT;     // regions per tile
-    __shared__ FwdWaveLds<NB> L;
+    __shared__ FwdWaveLds<NB, S> L;
+    FwdRegs<S> wregs;
+    const f4v* wcur = nullptr;   // the weights held in wregs and L.wts
     const int lane = threadIdx.x;
     const int pu = lane & 7, pv = lane >> 3;       // the lane's pixel in a block
     const double fx = static_cast<double>(pu), fy = static_cast<double>(pv);
@@ -165,6 +171,15 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     const SceneDesc sc = a.scenes[vd.scene];
     gfloat* __restrict__ feats = as_global(uniform_ptr(sc.feats));
     const float* mlp_p = uniform_ptr(sc.mlp);
+    const f4v* wops = nullptr;   // the scene's weights as matrix operands
+    if constexpr (FwdWeights<S>::kMfma)
+        wops = uniform_ptr(reinterpret_cast<const f4v*>(a.weights) + static_cast<size_t>(vd.scene) * FwdWeights<S>::kGroups);
+    if constexpr (FwdWeights<S>::kRegs) {
+        if (wops != wcur) {   // the first region of a scene
+            wregs.load(wops, L.wts, lane);
+            wcur = wops;
+        }
+    }
     const TriRec* __restrict__ recs = uniform_ptr(a.recs + vd.rec_base);
     // the view's fields that the batches and the epilogue use, read once: read
     // through vd after a store, they would be loaded again (the store may alias)
@@ -199,11 +214,27 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
         int pl = 0;
         bool pass = false;
         float o[4] = {0.f, 0.f, 0.f, 0.f};
+        float b1 = 0.0f, b2 = 0.0f;
+        if constexpr (FwdWeights<S>::kMfma) {
+            // every lane takes part in the products: a lane without a candidate has zero input
+            float x[S::C];
+#pragma unroll
+            for (int k = 0; k < S::C; ++k) x[k] = 0.0f;
+            if (act) {
+                key = L.qkey[lane];
+                persp_from_t(L.qt[0][lane], L.qt[1][lane], L.qt[2][lane], b1, b2);
+                fetch_feature<S::C>(feats, static_cast<uint32_t>(key), G, cell_of(b1, b2, G), x);
+            }
+            // an opaque copy of the weight pointer per batch: the compiler may
+            // not hoist the weights' loads out of the traversal loops
+            const f4v* wg = opaque_ptr(wops);
+            mfma_logits<S>(wregs, wg, FwdWeights<S>::kRegs ? L.wts : wg + FwdWeights<S>::kWo, x, o, lane);
+        }
         if (act) {
             key = L.qkey[lane];
             pl = static_cast<int>(L.qpl[lane]);
-            float b1, b2;
-            persp_from_t(L.qt[0][lane], L.qt[1][lane], L.qt[2][lane], b1, b2);
+            if constexpr (!FwdWeights<S>::kMfma)
+                persp_from_t(L.qt[0][lane], L.qt[1][lane], L.qt[2][lane], b1, b2);
             const uint32_t tri = static_cast<uint32_t>(key);
             const int blk = pl >> 6, p = pl & 63;
             const int gx = rx + (blk % BR) * 8 + (p & 7), gy = ry + (blk / BR) * 8 + (p >> 3);
@@ -217,12 +248,12 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                     pass = alpha > 0.5f;
                 }
             } else {
-                const Cell c = cell_of(b1, b2, G);
-                float x[S::C];
-                fetch_feature<S::C>(feats, tri, G, c, x);
-                // an opaque copy of the weight pointer per batch: the compiler may
-                // not hoist the weights' scalar loads out of the traversal loops
-                mlp_logits<S>(as_const(opaque_ptr(mlp_p)), x, o);
+                if constexpr (!FwdWeights<S>::kMfma) {
+                    const Cell c = cell_of(b1, b2, G);
+                    float x[S::C];
+                    fetch_feature<S::C>(feats, tri, G, c, x);
+                    mlp_logits<S>(as_const(opaque_ptr(mlp_p)), x, o);
+                }
                 if (a.o.mode == 0) {
                     const float alpha = sigmoid_c(o[3]);
                     const uint32_t pidx = static_cast<uint32_t>(gy * W + gx);
@@ -269,7 +300,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     const int64_t beg = a.tile_start[tile], end = a.tile_start[tile + 1];
     int64_t c0 = beg;         // next list entry to scan
     bool listed = false;      // the scan has reached the end of the list or its early-out
-    constexpr int kRing = FwdWaveLds<NB>::kRing;
+    constexpr int kRing = FwdWaveLds<NB, S>::kRing;
     int ph = 0;               // first waiting pair in the ring (L.ptri, L.pblk)
     int pn = 0;               // pairs waiting for the coverage step
     int qn = 0;               // queued candidates
@@ -330,20 +361,20 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
             // the pair of a combination: the last pair whose run starts at or before it
             L.head[lane] = -1;
             wave_fence();
-            if (cnt > 0 && off >= base && off < base + 64) L.head[off - base] = lane;
+            if (cnt > 0 && off >= base && off < base + 64) L.head[off - base] = static_cast<int8_t>(lane);
             wave_fence();
             const uint64_t before = __ballot(cnt > 0 && off < base);
             const int carry = before ? 63 - __builtin_clzll(before) : -1;
-            const int h = wave_scan_dpp(L.head[lane], -1, [](int x, int y) { return x > y ? x : y; });
+            const int h = wave_scan_dpp(static_cast<int>(L.head[lane]), -1, [](int x, int y) { return x > y ? x : y; });
             const int c = base + lane;
             const bool valid = c < n_comb;
             const int j = valid ? (h > carry ? h : carry) : 0;
             // its pixel: the k-th covered pixel of the pair, k its rank in the pair's run
             const PairMeta mj = L.meta[j];
             const PairGeo gj = L.geo[j];
-            const int p = select_bit(mj.mlo, mj.mhi, valid ? c - mj.off : 0);
-            const int bj = mj.blk;
-            const uint64_t zk = (static_cast<uint64_t>(mj.ent_hi) << 32) | mj.ent_lo;
+            const int p = select_bit(mj.mlo, mj.mhi, valid ? c - static_cast<int>(mj.off_blk & 0xFFFFu) : 0);
+            const int bj = static_cast<int>(mj.off_blk >> 16);
+            const uint64_t zk = (static_cast<uint64_t>(gj.zmin) << 32) | mj.tri;
             const uint64_t kp = L.key[bj * 64 + p];   // the pixel's best key as of the last decode batch
             const double px = static_cast<double>(p & 7), py = static_cast<double>(p >> 3);
             Frag f;
@@ -359,7 +390,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
             float z = __builtin_fmaf(f.beta[2], gj.z[2], __builtin_fmaf(f.beta[1], gj.z[1], f.beta[0] * gj.z[0]));
             if (!(z > 0.0f)) z = 0.0f;
             if (z > 1.0f) z = 1.0f;
-            f.key = (static_cast<uint64_t>(__float_as_uint(z)) << 32) | static_cast<uint32_t>(zk);
+            f.key = (static_cast<uint64_t>(__float_as_uint(z)) << 32) | mj.tri;
             const bool cand = valid & (zk < kp) & (f.key < kp);
             const uint64_t m = __ballot(cand);
             if (cand) {
@@ -462,14 +493,15 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                     g.iw[1] = __uint_as_float(q2.z);
                     g.iw[2] = __uint_as_float(q2.w);
                     g.ra = __builtin_fabsf(rA);
-                    g.pad = 0.0f;
+                    g.zmin = static_cast<uint32_t>(cent >> 32);
                     L.geo[lane] = g;
                 }
             }
             cnt = __popc(mlo) + __popc(mhi);
             const int incl = wave_incl_scan_i32(cnt);
             off = incl - cnt;
-            L.meta[lane] = PairMeta{mlo, mhi, static_cast<uint32_t>(cent), static_cast<uint32_t>(cent >> 32), off, cblk};
+            L.meta[lane] = PairMeta{mlo, mhi, static_cast<uint32_t>(cent),
+                                    static_cast<uint32_t>(off) | (static_cast<uint32_t>(cblk) << 16)};
             n_comb = __builtin_amdgcn_readlane(incl, 63);
             rnd = 0;
             n_rnd = (n_comb + 63) >> 6;
@@ -584,5 +616,18 @@ static void launch_fwd_t(const RasterArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((raster_fwd_kernel<TS, 8, S>), dim3(static_cast<unsigned>(a.n_blocks)), dim3(64), 0, s, a);
 }
 
+
+// Before the raster: the work counter at zero and every scene's weights as
+// matrix operands (a column of workgroups per scene).
+template <class S>
+__global__ __launch_bounds__(256) void fwd_weights_kernel(const SceneDesc* __restrict__ scenes,
+                                                          unsigned int* __restrict__ work, float* __restrict__ out) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *work = 0u;
+    const SceneDesc& sc = scenes[blockIdx.x];
+    if (sc.T <= 0) return;   // an empty scene may have no parameters, and decodes nothing
+    float* o = out + static_cast<size_t>(blockIdx.x) * FwdWeights<S>::kGroups * 4;
+    for (int i = blockIdx.y * 256 + threadIdx.x; i < FwdWeights<S>::kGroups * 4; i += gridDim.y * 256)
+        o[i] = sc.mlp[FwdWeights<S>::source(i >> 2, i & 3)];
+}
 
 }  // namespace soup
