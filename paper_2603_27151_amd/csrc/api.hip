@@ -259,6 +259,9 @@ Opts to_opts(const soup_opts* o) {
     return r;
 }
 
+// The counters buffer: 128 bytes of counts, totals and flags, then the work counters.
+constexpr size_t kCountersBytes = 128;
+
 // Per-call plan: descriptors and sizes.
 struct Plan {
     std::vector<ViewDesc> views;
@@ -307,7 +310,7 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     const size_t vbytes = p.views.size() * sizeof(ViewDesc), sbytes = p.scenes.size() * sizeof(SceneDesc);
     const int chunk = bin_chunk_size(static_cast<int>(p.views.size()), p.maxT, c->num_cus);
     soup_status st;
-    // the forward counts its regions in 32 bits
+    // the forward counts its regions in 32 bits (with room for the waves' last draws)
     if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >= (int64_t(1) << 32))
         return fail(c, SOUP_ERR_CAPACITY, "too many pixels in one call (2^32 forward regions)");
     if ((st = ensure(c, c->views, vbytes)) || (st = ensure(c, c->scenes, sbytes)) ||
@@ -320,7 +323,7 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
                      chunk >= kBinChunk ? static_cast<size_t>(bin_chunks(p.maxT, chunk)) * p.n_tiles * 4 : 0)) ||
         (st = ensure(c, c->tile_start, static_cast<size_t>(p.n_tiles + 1) * 8)) ||
         (st = ensure(c, c->bsum, static_cast<size_t>((p.n_tiles + 1023) / 1024 + 1) * 8)) ||
-        (st = ensure(c, c->counters, 128)) || (st = ensure(c, c->flags, 256)) ||
+        (st = ensure(c, c->counters, kCountersBytes + kWorkCounters * kWorkStride * 4)) || (st = ensure(c, c->flags, 256)) ||
         (st = ensure_host(c, vbytes + sbytes + 64)))
         return st;
     if (!c->flags_ready) {   // first allocation (never in static mode): clear the sticky flags
@@ -411,7 +414,7 @@ RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o) {
     a.n_tiles = p.n_tiles;
     unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
     a.counter = c->counting ? cnt : nullptr;
-    a.work = reinterpret_cast<unsigned int*>(cnt + 2);
+    a.work = reinterpret_cast<unsigned int*>(cnt) + kCountersBytes / 4;
     // the forward's workgroups are single waves, one region of a tile at a time: 16x16 pixels, or a
     // single 8x8 block for 8-pixel tiles and for calls with fewer 16x16 regions than two per resident
     // wave (a small render); as many waves as are resident
@@ -425,6 +428,9 @@ RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o) {
     const int64_t items = p.n_tiles * fwd_regions_per_tile(c->tile, region);
     const int64_t resident = static_cast<int64_t>(c->num_cus) * raster_fwd_blocks_per_cu(c->tile, p.kind, region);
     a.n_blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident, kMaxRegions), items)));
+    // few single-block regions per wave are all dealt by stride, else only the first round
+    a.fixed = static_cast<uint32_t>(region == 8 && items <= int64_t(16) * a.n_blocks
+                                        ? (items + a.n_blocks - 1) / a.n_blocks * a.n_blocks : a.n_blocks);
     return a;
 }
 

@@ -38,6 +38,9 @@ enum class MlpKind { k8_16_1, k16_32_2, k32_64_2, kPaper, kNone };
 MlpKind mlp_kind(int n_layers, const int32_t* dims);
 int mlp_params(int n_layers, const int32_t* dims);
 
+// Work counters of the forward, each in a 256-byte line of its own.
+constexpr uint32_t kWorkCounters = 8, kWorkStride = 64;
+
 struct RasterArgs {
     const ViewDesc* views;
     int V;
@@ -51,7 +54,8 @@ struct RasterArgs {
     uint64_t* vis;                 // concatenated outputs (may be null when views carry their own)
     float* color;
     unsigned long long* counter;   // counters or null: [0] decodes, [8] pixels that some fragment covers
-    unsigned int* work;            // persistent-kernel tile counter (zeroed by the launcher's caller)
+    unsigned int* work;            // persistent-kernel work counters (zeroed by the launcher's caller)
+    uint32_t fixed;                // forward: regions below it are dealt by stride (a multiple of n_blocks)
     const float* weights;          // forward: every scene's weights as matrix operands (launch_fwd_begin), or null
     int n_blocks;                  // persistent grid of the forward (single-wave workgroups)
     int region;                    // side of a forward wave's region: 16 (tiles of 16, 32) or 8
@@ -63,7 +67,7 @@ struct RasterArgs {
     uint32_t* log_counts;
 };
 
-// What a forward needs right before its raster: *work zeroed and, for the MLP shapes decoded on
+// What a forward needs right before its raster: the work counters zeroed and, for the MLP shapes decoded on
 // the matrix cores, the weights of each scene in their operand order (fwd_weights_bytes per scene).
 size_t fwd_weights_bytes(MlpKind k);
 void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned int* work, float* weights,

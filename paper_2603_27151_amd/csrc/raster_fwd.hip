@@ -76,7 +76,7 @@ void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned
         case MlpKind::k32_64_2:
             hipLaunchKernelGGL((fwd_weights_kernel<MlpShape<32, 64, 2>>), grid, block, 0, s, scenes, work, weights);
             break;
-        default: launch_fill_i32(reinterpret_cast<int32_t*>(work), 1, 0, s); break;
+        default: launch_fill_i32(reinterpret_cast<int32_t*>(work), kWorkCounters * kWorkStride, 0, s); break;
     }
 }
 

@@ -4,8 +4,8 @@
 //
 // One wave is one workgroup and owns one region of a screen tile at a time
 // (16x16 pixels, four 8x8 blocks, or a single 8x8 block when a call has too
-// few 16x16 regions to fill the GPU), taken from a counter (persistent, the
-// next region fetched while the current one runs),
+// few 16x16 regions to fill the GPU), dealt by stride or from counters
+// (persistent, the next region fetched while the current one runs),
 // so no barrier ever waits for another wave (the wave's LDS accesses are
 // ordered by wavefront-scope fences, which wait on nothing). It walks the tile's triangle
 // list (sorted by a lower bound of their depth) in three steps, all in one
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     uint32_t log_cursor = 0;   // wave-uniform
     int vcur = 0;              // view of the previous region, and its tiles [vlo, vhi)
     int64_t vlo = 0, vhi = 0;
-    uint32_t next = 0;
-    if (lane == 0) next = atomicAdd(a.work, 1u);
+    uint32_t next = blockIdx.x;
     // The walk's scan, coverage and fragment steps wait on memory and LDS; at a
     // raised priority they issue ahead of the other waves' decode batches, long
     // runs of VALU work that then fill the gaps: priority 2 for the scan and the
@@ -150,10 +149,23 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     // (forward 2.26 -> 2.22 ms)
     __builtin_amdgcn_s_setprio(1);
 
-    for (;;) {   // persistent: regions from a counter
+    // Regions below a.fixed are dealt by stride (the first round always), the
+    // rest from kWorkCounters counters, counter c dealing every kWorkCounters-th
+    // region to the waves with blockIdx.x % kWorkCounters == c. Atomics on one
+    // address complete about 7 ns apart over the whole GPU, which with a single
+    // counter was most of a small call (640x360, 14,720 regions: 130 us, by
+    // stride 52) and showed in large ones (16 serving requests 1.11 -> 0.84 ms
+    // with eight counters; 4, 16 and 32 are 1 to 3% slower, 64 lose balance). A
+    // stride for all rounds is only safe where they are few: with sides that
+    // are powers of two it gives a wave the same image columns in every round
+    // (64 views: 1.78 ms from one counter, 1.72 from eight, 2.9 by stride).
+    const uint32_t wc = blockIdx.x % kWorkCounters;
+    for (;;) {
     const uint64_t item = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(next)));
     if (item >= n_items) break;
-    if (lane == 0) next = atomicAdd(a.work, 1u);   // the following region, fetched while this one runs
+    // (the sums stay below 2^32: checked on the host)
+    if (static_cast<uint32_t>(item) + gridDim.x < a.fixed) next = static_cast<uint32_t>(item) + gridDim.x;
+    else if (lane == 0) next = a.fixed + atomicAdd(a.work + kWorkStride * wc, 1u) * kWorkCounters + wc;   // fetched while this one runs
     const int64_t tile = static_cast<int64_t>(item / RPT);
     const int rq = static_cast<int>(item % RPT);
     if (tile < vlo || tile >= vhi) {
@@ -617,12 +629,12 @@ static void launch_fwd_t(const RasterArgs& a, hipStream_t s) {
 }
 
 
-// Before the raster: the work counter at zero and every scene's weights as
+// Before the raster: the work counters at zero and every scene's weights as
 // matrix operands (a column of workgroups per scene).
 template <class S>
 __global__ __launch_bounds__(256) void fwd_weights_kernel(const SceneDesc* __restrict__ scenes,
                                                           unsigned int* __restrict__ work, float* __restrict__ out) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *work = 0u;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWorkCounters) work[kWorkStride * threadIdx.x] = 0u;
     const SceneDesc& sc = scenes[blockIdx.x];
     if (sc.T <= 0) return;   // an empty scene may have no parameters, and decodes nothing
     float* o = out + static_cast<size_t>(blockIdx.x) * FwdWeights<S>::kGroups * 4;
