@@ -309,14 +309,15 @@ bool same_descriptors(const soup_ctx* c, const Plan& p) {
 soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     const size_t vbytes = p.views.size() * sizeof(ViewDesc), sbytes = p.scenes.size() * sizeof(SceneDesc);
     const int chunk = bin_chunk_size(static_cast<int>(p.views.size()), p.maxT, c->num_cus);
+    const int stride = bin_stride(chunk, p.n_tiles);
     soup_status st;
     // the forward counts its regions in 32 bits (with room for the waves' last draws)
     if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >= (int64_t(1) << 32))
         return fail(c, SOUP_ERR_CAPACITY, "too many pixels in one call (2^32 forward regions)");
     if ((st = ensure(c, c->views, vbytes)) || (st = ensure(c, c->scenes, sbytes)) ||
         (st = ensure(c, c->recs, static_cast<size_t>(p.n_recs) * sizeof(TriRec))) ||
-        (st = ensure(c, c->tile_count, static_cast<size_t>(p.n_tiles) * 4)) ||
-        (st = ensure(c, c->tile_fill, static_cast<size_t>(p.n_tiles) * 4)) ||
+        (st = ensure(c, c->tile_count, static_cast<size_t>(p.n_tiles) * stride * 4)) ||
+        (st = ensure(c, c->tile_fill, static_cast<size_t>(p.n_tiles) * stride * 4)) ||
         // per-chunk tile slots exist only for the LDS-histogram chunks (a small render's
         // one-triangle-per-thread chunks count with global atomics and need none)
         (st = ensure(c, c->chunk_base,
@@ -350,8 +351,8 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
     {
         Timed t(c, SOUP_T_FILL, s);
-        launch_fill_i32(reinterpret_cast<int32_t*>(cnt), 32, 0, s);
-        launch_fill_i32(static_cast<int32_t*>(c->tile_count.p), p.n_tiles, 0, s);
+        launch_zero3(reinterpret_cast<int32_t*>(cnt), 32, static_cast<int32_t*>(c->tile_count.p), p.n_tiles * stride,
+                     static_cast<int32_t*>(c->tile_fill.p), p.n_tiles * stride, s);
     }
     {
     Timed t_setup(c, SOUP_T_SETUP, s);
@@ -362,7 +363,7 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     }
     {
         Timed t(c, SOUP_T_SCAN, s);
-        launch_scan(static_cast<int32_t*>(c->tile_count.p), p.n_tiles, static_cast<int64_t*>(c->bsum.p),
+        launch_scan(static_cast<int32_t*>(c->tile_count.p), p.n_tiles, stride, static_cast<int64_t*>(c->bsum.p),
                     static_cast<int64_t*>(c->tile_start.p), s);
     }
     int64_t total = -1;
@@ -381,7 +382,6 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     }
     {
         Timed t(c, SOUP_T_SCATTER, s);
-        launch_fill_i32(static_cast<int32_t*>(c->tile_fill.p), p.n_tiles, 0, s);
         launch_scatter(static_cast<ViewDesc*>(c->views.p), static_cast<int>(p.views.size()), p.maxT, chunk, c->tile,
                        static_cast<TriRec*>(c->recs.p), static_cast<int64_t*>(c->tile_start.p), p.n_tiles,
                        static_cast<int32_t*>(c->chunk_base.p), static_cast<int32_t*>(c->tile_fill.p),
@@ -989,7 +989,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = ensure(c, c->sorted, static_cast<size_t>(frag_cap) * sizeof(FragRec)))) return st;
     {
         Timed t(c, SOUP_T_GRAD, s);
-        launch_scan(static_cast<int32_t*>(c->tri_count.p), T, static_cast<int64_t*>(c->tri_bsum.p),
+        launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
                     static_cast<int64_t*>(c->tri_off.p), s);
         launch_fill_i32(static_cast<int32_t*>(c->tri_fill.p), 2 * T, 0, s);
         PlaceArgs pa{};
@@ -1252,7 +1252,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         if ((st = ensure(c, c->sorted, static_cast<size_t>(frag_cap) * sizeof(FragRec)))) return st;
         {
             Timed t(c, SOUP_T_GRAD, s);
-            launch_scan(static_cast<int32_t*>(c->tri_count.p), T, static_cast<int64_t*>(c->tri_bsum.p),
+            launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
                         static_cast<int64_t*>(c->tri_off.p), s);
             launch_fill_i32(static_cast<int32_t*>(c->tri_fill.p), 2 * T, 0, s);
             PlaceArgs pa{};

@@ -6,13 +6,15 @@
 namespace soup {
 
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
+// Clears three ranges (any of them empty) in one launch.
+void launch_zero3(int32_t* p0, int64_t n0, int32_t* p1, int64_t n1, int32_t* p2, int64_t n2, hipStream_t s);
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);
 // Binning works on chunks of triangles per view. Large chunks (kBinChunk) of
 // a view with at most kHistBins tiles are counted in an LDS histogram, and
 // chunk_base ([chunks][tiles] int32) receives each chunk's first slot in every
 // tile list it touches; when large chunks would leave the GPU idle (few views,
-// few triangles) the chunks are one triangle per thread, counted with global
-// atomics.
+// few triangles) the chunks are small, their (tile, triangle) pairs spread over
+// a workgroup and counted with global atomics.
 constexpr int kBinChunk = 2048;
 constexpr int kHistBins = 8192;
 int bin_chunk_size(int V, int maxT, int num_cus);
@@ -20,7 +22,9 @@ inline int bin_chunks(int maxT, int chunk) { return maxT <= 0 ? 0 : (maxT + chun
 void launch_setup(const ViewDesc* views, int V, int maxT, int chunk, const SceneDesc* scenes, const Opts& o,
                   int tile, TriRec* recs, int32_t* tile_count, int32_t* chunk_base, int64_t n_tiles,
                   unsigned long long* visible, hipStream_t s);
-void launch_scan(const int32_t* in, int64_t n, int64_t* bsum, int64_t* out, hipStream_t s);
+// Distance of two tiles' counters in the count and fill arrays.
+int bin_stride(int chunk, int64_t n_tiles);
+void launch_scan(const int32_t* in, int64_t n, int stride, int64_t* bsum, int64_t* out, hipStream_t s);
 void launch_scatter(const ViewDesc* views, int V, int maxT, int chunk, int tile, const TriRec* recs,
                     const int64_t* tile_start, int64_t n_tiles, const int32_t* chunk_base, int32_t* tile_fill,
                     uint64_t* entries, hipStream_t s);
