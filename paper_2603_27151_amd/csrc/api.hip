@@ -32,11 +32,17 @@ struct soup_ctx {
     bool counting = false;
     bool fixed = false;              // static-capacity mode: no synchronisation, no allocation
     bool flags_ready = false;        // sticky overflow flags cleared after allocation
-    // the forward's fragment log: region size and count, hint for the next,
-    // and the draws it was made with (valid only with bins_valid)
+    // a fragment log: its buffers, region size and count, and the largest count of the
+    // last call (0: none yet), which sizes the next
+    struct FragLog {
+        DevBuf frag, bary, counts;
+        uint64_t region = 0, hint = 0;
+        int regions = 0;
+    };
+    FragLog flog, rlog;              // the forward's, and that of the walk with the winners known
+    DevBuf masks;                    // what is kept of a log
+    // the draws the forward's log was made with (valid only with bins_valid)
     bool log_valid = false;
-    uint64_t log_region = 0, log_hint = 0;
-    int log_regions = 0;
     uint64_t log_seed = 0;
     uint32_t log_step = 0;
     int log_mode = 0;
@@ -50,15 +56,10 @@ struct soup_ctx {
     DevBuf views, scenes, recs, tile_count, tile_fill, tile_start, bsum, entries, edge_w, partial, counters;
     DevBuf fwd_weights;  // every scene's MLP weights as the forward's matrix operands
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
-    DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, frags, sorted;
-    DevBuf region_counts, region_boff, flags;
-    DevBuf log_frag, log_aux, log_counts, log_boff;   // the forward's fragment log
+    DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, sorted, flags;
     DevBuf ssim;                                      // SSIM statistics of the training loss
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
     DevBuf gtex;                                      // its texture gradient when levels are asked for and the sorted path cannot fold them in
-    uint64_t region_hint = 0;        // largest replay-region count of the last call, to size the next
-    uint64_t frag_region = 0;        // region size and count of the current fragment list
-    int frag_regions = 0;
     void* host_stage = nullptr;      // pinned: descriptors up, totals down
     float* scratch = nullptr;        // this device's address of the allocation-free loss's static scratch
     size_t host_stage_bytes = 0;
@@ -212,8 +213,8 @@ soup_status check_scene(soup_ctx* c, const soup_scene* s, MlpKind* kind) {
 
 // The backward decode keeps one triangle's gradient grid per wave in LDS: refuse a
 // grid that would not fit one workgroup's LDS rather than launch it.
-soup_status check_decode_lds(soup_ctx* c, MlpKind kind, int G, bool logp) {
-    const size_t need = decode_bwd_lds(kind, G, logp);
+soup_status check_decode_lds(soup_ctx* c, MlpKind kind, int G) {
+    const size_t need = decode_bwd_lds(kind, G);
     if (need > c->lds_limit)
         return fail(c, SOUP_ERR_UNSUPPORTED, "the backward decode needs %zu bytes of LDS per workgroup for G = %d "
                     "(the device has %zu): use a smaller texture grid", need, G, c->lds_limit);
@@ -401,7 +402,7 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     return SOUP_OK;
 }
 
-RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o) {
+RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o, MlpKind kind) {
     RasterArgs a{};
     a.views = static_cast<ViewDesc*>(c->views.p);
     a.V = static_cast<int>(p.views.size());
@@ -421,12 +422,12 @@ RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o) {
     int region = 8;
     if (c->tile >= 16) {
         const int64_t r16 = p.n_tiles * fwd_regions_per_tile(c->tile, 16);
-        const int64_t res16 = static_cast<int64_t>(c->num_cus) * raster_fwd_blocks_per_cu(c->tile, p.kind, 16);
+        const int64_t res16 = static_cast<int64_t>(c->num_cus) * raster_fwd_blocks_per_cu(c->tile, kind, 16);
         region = r16 >= 2 * res16 ? 16 : 8;
     }
     a.region = region;
     const int64_t items = p.n_tiles * fwd_regions_per_tile(c->tile, region);
-    const int64_t resident = static_cast<int64_t>(c->num_cus) * raster_fwd_blocks_per_cu(c->tile, p.kind, region);
+    const int64_t resident = static_cast<int64_t>(c->num_cus) * raster_fwd_blocks_per_cu(c->tile, kind, region);
     a.n_blocks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident, kMaxRegions), items)));
     // few single-block regions per wave are all dealt by stride, else only the first round
     a.fixed = static_cast<uint32_t>(region == 8 && items <= int64_t(16) * a.n_blocks
@@ -581,12 +582,11 @@ void soup_ctx_destroy(soup_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    DevBuf* bufs[] = {&c->views,     &c->scenes,    &c->recs,          &c->tile_count,  &c->tile_fill,
-                      &c->tile_start, &c->bsum,      &c->entries,       &c->edge_w,      &c->partial,
-                      &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
-                      &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
-                      &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                      &c->chunk_base, &c->fwd_weights, &c->gvert, &c->gtex};
+    DevBuf* bufs[] = {&c->views,      &c->scenes,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
+                      &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
+                      &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
+                      &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
+                      &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
@@ -667,12 +667,11 @@ soup_status soup_ctx_set_counting(soup_ctx* c, int32_t on) {
 
 soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
     if (!c || !bytes) return SOUP_ERR_INVALID;
-    const DevBuf* bufs[] = {&c->views,     &c->scenes,    &c->recs,          &c->tile_count,  &c->tile_fill,
-                            &c->tile_start, &c->bsum,      &c->entries,       &c->edge_w,      &c->partial,
-                            &c->counters,   &c->tri_count, &c->tri_fill,      &c->tri_off,     &c->tri_bsum,
-                            &c->mlp_mid,    &c->frags,     &c->sorted,        &c->region_counts, &c->region_boff,
-                            &c->flags,      &c->log_frag,  &c->log_aux,       &c->log_counts,  &c->log_boff, &c->ssim,
-                            &c->chunk_base, &c->fwd_weights, &c->gvert, &c->gtex};
+    const DevBuf* bufs[] = {&c->views,      &c->scenes,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
+                            &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
+                            &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
+                            &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
+                            &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     int64_t n = 0;
     for (const DevBuf* b : bufs) n += static_cast<int64_t>(b->bytes);
     *bytes = n;
@@ -685,117 +684,132 @@ soup_status soup_last_stats(const soup_ctx* c, soup_stats* out) {
     return SOUP_OK;
 }
 
-// Persistent grid of the replay: 4 workgroups per CU, at most kMaxRegions waves.
-int replay_blocks(soup_ctx* c, const Plan& p) {
-    const int wpb = replay_waves_per_block(c->tile);
-    const int64_t want = std::min<int64_t>(static_cast<int64_t>(c->num_cus) * 4, kMaxRegions / wpb);
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, p.n_tiles)));
-}
-
 // Persistent grid of the decode kernel: 4 waves per workgroup, 4 workgroups per CU.
 int decode_blocks(soup_ctx* c) { return std::max(1, std::min(c->num_cus * 4, kMaxRegions / 4)); }
 
-// Backward, part 1: gather the fragments the backward needs into c->frags,
-// one region per wave, then scan the region counts into batch offsets. The
-// fragments come from the replay (coverage re-run from the tile lists) or,
-// when from_log, from the filter of the forward's log. Regions are sized
-// from the last call's largest count, doubled (else from 1.5
-// fragments per pixel); an overflow is detected from the counts and the
-// gather runs again, sized exactly. Returns the number of fragments in
-// *n_frag and of decode batches in *n_batch.
-soup_status replay(soup_ctx* c, const Plan& p, const RasterArgs& a, const uint64_t* vis, const float* grad_color,
-                   const float* grad_logp, const float2* edge_w, bool all_front, int32_t* tri_count, int T,
-                   hipStream_t s, int64_t* n_frag, int64_t* n_batch, bool from_log = false) {
-    if (p.n_pix >= (int64_t(1) << 32)) return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
-    unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
-    const int nb = from_log ? decode_blocks(c) : replay_blocks(c, p);
-    const int nr = nb * (from_log ? 4 : replay_waves_per_block(c->tile));
-    // per-wave counts vary between calls (tiles are handed out dynamically):
-    // twice the last call's largest, so that a static-mode call fits
-    uint64_t hint = c->region_hint;
-    if (hint && c->frag_regions && c->frag_regions != nr) hint = hint * c->frag_regions / nr + 64;
-    uint64_t region = hint ? 2 * hint + 1024 : (static_cast<uint64_t>(p.n_pix) * 3 / 2) / nr + 1024;
+// The view of a log that its readers take. A region's batches are shared by as many waves as
+// give each about eight (a wave per region where the regions are short).
+FragLogView log_view(const soup_ctx::FragLog& g) {
+    FragLogView v{};
+    v.frag = static_cast<uint4*>(g.frag.p);
+    v.bary = static_cast<uint2*>(g.bary.p);
+    v.counts = static_cast<uint32_t*>(g.counts.p);
+    v.region = static_cast<uint32_t>(g.region);
+    v.n_regions = g.regions;
+    v.split = static_cast<int>(std::max<uint64_t>(1, std::min<uint64_t>(16, g.hint / 512)));
+    return v;
+}
+
+// Buffers of a log of `regions` regions (a static-mode call takes what an earlier call sized);
+// the raster's arguments are set to write it.
+soup_status log_reserve(soup_ctx* c, soup_ctx::FragLog& g, int regions, uint64_t region, RasterArgs& a) {
     soup_status st;
-    if ((st = ensure(c, c->region_counts, static_cast<size_t>(kMaxRegions) * 4)) ||
-        (st = ensure(c, c->region_boff, static_cast<size_t>(kMaxRegions + 1) * 4)))
-        return st;
-    auto launch = [&](uint64_t reg) {
-        if (from_log) {
-            CollectArgs ca{};
-            ca.log_frag = static_cast<uint4*>(c->log_frag.p);
-            ca.log_aux = static_cast<uint2*>(c->log_aux.p);
-            ca.log_region = static_cast<uint32_t>(c->log_region);
-            ca.log_counts = static_cast<uint32_t*>(c->log_counts.p);
-            ca.log_boff = static_cast<uint32_t*>(c->log_boff.p);
-            ca.log_regions = c->log_regions;
-            ca.vis = vis;
-            ca.grad_logp = grad_logp;
-            ca.all_front = all_front ? 1 : 0;
-            ca.frags = static_cast<FragRec*>(c->frags.p);
-            ca.region = static_cast<uint32_t>(reg);
-            ca.counts = static_cast<uint32_t*>(c->region_counts.p);
-            ca.tri_count = tri_count;
-            ca.n_blocks = nb;
-            launch_collect(ca, s);
-        } else {
-            ReplayArgs ra{};
-            ra.r = a;
-            ra.vis = vis;
-            ra.grad_color = grad_color;
-            ra.grad_logp = grad_logp;
-            ra.edge_w = edge_w;
-            ra.all_front = all_front ? 1 : 0;
-            ra.frags = static_cast<FragRec*>(c->frags.p);
-            ra.region = static_cast<uint32_t>(reg);
-            ra.counts = static_cast<uint32_t*>(c->region_counts.p);
-            ra.tri_count = tri_count;
-            ra.n_blocks = nb;
-            launch_replay(ra, c->tile, s);
-        }
-        launch_region_scan(static_cast<uint32_t*>(c->region_counts.p), nr, static_cast<uint32_t>(reg),
-                           static_cast<uint32_t*>(c->region_boff.p), cnt + 4, static_cast<unsigned int*>(c->flags.p),
-                           s);
-    };
     if (c->fixed) {
-        // the fragment list in place bounds the regions; an overflow is flagged
-        if (c->frag_regions != nr || c->frag_region == 0)
-            return fail(c, SOUP_ERR_CAPACITY, "static mode: no fragment list sized for this call; run it once "
+        if (g.regions != regions || g.region == 0)
+            return fail(c, SOUP_ERR_CAPACITY, "static mode: no fragment log sized for this call; run it once "
                         "outside static mode");
-        launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
-        if (tri_count) launch_fill_i32(tri_count, T, 0, s);
-        launch(c->frag_region);
-        HIP_TRY(c, hipGetLastError());
-        *n_frag = -1;
-        *n_batch = static_cast<int64_t>(nr) * static_cast<int64_t>((c->frag_region + 63) / 64);   // upper bound
-        return SOUP_OK;
+    } else {
+        if (region >= (uint64_t(1) << 31)) return fail(c, SOUP_ERR_CAPACITY, "fragment log region too large");
+        if ((st = ensure(c, g.frag, static_cast<size_t>(region) * regions * sizeof(uint4))) ||
+            (st = ensure(c, g.bary, static_cast<size_t>(region) * regions * sizeof(uint2))) ||
+            (st = ensure(c, g.counts, static_cast<size_t>(kMaxRegions) * 4)))
+            return st;
+        g.region = region;
+        g.regions = regions;
     }
-    uint64_t summary[3] = {0, 0, 0};
+    a.log_frag = static_cast<uint4*>(g.frag.p);
+    a.log_bary = static_cast<uint2*>(g.bary.p);
+    a.log_region = static_cast<uint32_t>(g.region);
+    a.log_counts = static_cast<uint32_t*>(g.counts.p);
+    return SOUP_OK;
+}
+
+// After the raster that wrote the log: an eager call reads the largest count (*ok: it fits);
+// in static mode an overflow is flagged.
+soup_status log_summary(soup_ctx* c, soup_ctx::FragLog& g, hipStream_t s, bool* ok) {
+    unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
+    launch_log_summary(static_cast<uint32_t*>(g.counts.p), g.regions, static_cast<uint32_t>(g.region), cnt + 4,
+                       c->fixed ? static_cast<unsigned int*>(c->flags.p) : nullptr, s);
+    HIP_TRY(c, hipGetLastError());
+    *ok = true;
+    if (c->fixed) return SOUP_OK;
+    uint64_t* h = reinterpret_cast<uint64_t*>(c->host_stage);
+    HIP_TRY(c, hipMemcpyAsync(h, cnt + 4, 16, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipStreamSynchronize(s));
+    *ok = h[1] <= g.region;
+    g.hint = h[1];
+    return SOUP_OK;
+}
+
+// The log of exactly the fragments the backward (or log p: all_front) needs, from a walk with the
+// winners known. Regions are sized from the last call's largest count, doubled, since per-wave
+// counts vary between calls (else from 1.5 fragments per pixel); an overflow is detected and the
+// walk runs again, sized exactly.
+soup_status replay(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vis, const float* grad_color,
+                   const float* grad_logp, const float2* edge_w, bool all_front, hipStream_t s) {
+    soup_ctx::FragLog& g = c->rlog;
+    RasterArgs a = raster_args(c, p, o, MlpKind::kReplay);
+    a.counter = nullptr;
+    a.replay_vis = vis;
+    a.replay_color = grad_color;
+    a.replay_logp = grad_logp;
+    a.replay_edge = edge_w;
+    a.replay_all = all_front ? 1 : 0;
+    const int nr = a.n_blocks;
+    uint64_t hint = g.hint;
+    if (hint && g.regions && g.regions != nr) hint = hint * g.regions / nr + 64;
+    uint64_t region = hint ? 2 * hint + 1024 : (static_cast<uint64_t>(p.n_pix) * 3 / 2) / nr + 1024;
     for (int attempt = 0; attempt < 2; ++attempt) {
-        if (region >= (uint64_t(1) << 31)) return fail(c, SOUP_ERR_CAPACITY, "fragment region too large");
-        if ((st = ensure(c, c->frags, static_cast<size_t>(region) * nr * sizeof(FragRec)))) return st;
-        {
-            Timed t(c, SOUP_T_FILL, s);
-            launch_fill_i32(reinterpret_cast<int32_t*>(a.work), 1, 0, s);
-            if (tri_count) launch_fill_i32(tri_count, T, 0, s);
-        }
+        soup_status st;
+        bool ok = false;
+        if ((st = log_reserve(c, g, nr, region, a))) return st;
         {
             Timed t(c, SOUP_T_REPLAY, s);
-            launch(region);
+            launch_fwd_begin(a.scenes, 0, MlpKind::kReplay, a.work, nullptr, s);
+            launch_raster_fwd(a, c->tile, MlpKind::kReplay, s);
         }
-        HIP_TRY(c, hipGetLastError());
-        uint64_t* h = reinterpret_cast<uint64_t*>(c->host_stage);
-        HIP_TRY(c, hipMemcpyAsync(h, cnt + 4, 24, hipMemcpyDeviceToHost, s));
-        HIP_TRY(c, hipStreamSynchronize(s));
-        memcpy(summary, h, sizeof(summary));
-        if (summary[2] <= region) break;
-        region = summary[2] + summary[2] / 8 + 64;
+        if ((st = log_summary(c, g, s, &ok))) return st;
+        if (ok) return SOUP_OK;
+        region = g.hint + g.hint / 8 + 64;
     }
-    if (summary[2] > region) return fail(c, SOUP_ERR_CAPACITY, "fragment list overflowed twice");
-    c->region_hint = summary[2];
-    c->frag_region = region;
-    c->frag_regions = nr;
-    *n_frag = static_cast<int64_t>(summary[0]);
-    *n_batch = static_cast<int64_t>(summary[1]);
+    return fail(c, SOUP_ERR_CAPACITY, "fragment log overflowed twice");
+}
+
+// Backward, part 1: the fragments the backward needs, from the forward's log or a walk, sorted by
+// triangle into c->sorted, with c->tri_off the triangles' ranges.
+soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vis, const float* grad_color,
+                             const float* grad_logp, const float2* edge_w, int T, bool from_log, hipStream_t s) {
+    soup_status st;
+    if (p.n_pix >= (int64_t(1) << 32)) return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
+    if (!from_log && (st = replay(c, p, o, vis, grad_color, grad_logp, edge_w, false, s))) return st;
+    const soup_ctx::FragLog& g = from_log ? c->flog : c->rlog;
+    const FragLogView L = log_view(g);
+    // the sorted list has at most as many entries as the log holds
+    if ((st = ensure(c, c->sorted, static_cast<size_t>(g.regions) * g.region * sizeof(FragRec))) ||
+        (st = ensure(c, c->masks, static_cast<size_t>(g.regions) * log_slots(L.region) * sizeof(ulonglong2))) ||
+        (st = ensure(c, c->tri_count, static_cast<size_t>(T) * 4)) ||
+        (st = ensure(c, c->tri_fill, static_cast<size_t>(T) * 8)) ||
+        (st = ensure(c, c->tri_off, static_cast<size_t>(T + 1) * 8)) ||
+        (st = ensure(c, c->tri_bsum, static_cast<size_t>((T + 1023) / 1024 + 1) * 8)))
+        return st;
+    {
+        Timed t(c, SOUP_T_FILL, s);
+        launch_zero3(static_cast<int32_t*>(c->tri_count.p), T, static_cast<int32_t*>(c->tri_fill.p), 2 * static_cast<int64_t>(T),
+                     nullptr, 0, s);
+    }
+    {
+        Timed t(c, SOUP_T_REPLAY, s);
+        launch_count(L, FragSelect{vis, grad_logp, 0}, static_cast<ulonglong2*>(c->masks.p),
+                     static_cast<int32_t*>(c->tri_count.p), s);
+    }
+    {
+        Timed t(c, SOUP_T_GRAD, s);
+        launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
+                    static_cast<int64_t*>(c->tri_off.p), s);
+        launch_place(L, grad_logp, static_cast<ulonglong2*>(c->masks.p), static_cast<int64_t*>(c->tri_off.p),
+                     static_cast<unsigned long long*>(c->tri_fill.p), static_cast<FragRec*>(c->sorted.p), s);
+    }
+    HIP_TRY(c, hipGetLastError());
     return SOUP_OK;
 }
 
@@ -816,32 +830,11 @@ static soup_status fwd_begin(soup_ctx* c, const Plan& p, RasterArgs& a, hipStrea
 static soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, RasterArgs& a, bool keep,
                                   hipStream_t s) {
     soup_status st;
-    const int log_nr = a.n_blocks;   // one log region per forward wave
-    uint64_t log_region = 0;
-    if (keep) {
-        if (c->fixed) {
-            if (c->log_regions != log_nr || c->log_region == 0)
-                return fail(c, SOUP_ERR_CAPACITY, "static mode: no fragment log sized for this call; run it once "
-                            "outside static mode");
-            log_region = c->log_region;
-        } else {
-            // twice the last call's largest count: per-wave counts vary from call to
-            // call (regions are handed out dynamically), and a static-mode call
-            // (which cannot grow the log) must fit
-            log_region = c->log_hint ? 2 * c->log_hint + 1024
-                                     : (static_cast<uint64_t>(p.n_pix) * 2) / log_nr + 1024;
-            if (log_region >= (uint64_t(1) << 31)) return fail(c, SOUP_ERR_CAPACITY, "fragment log region too large");
-            if ((st = ensure(c, c->log_frag, static_cast<size_t>(log_region) * log_nr * sizeof(uint4))) ||
-                (st = ensure(c, c->log_aux, static_cast<size_t>(log_region) * log_nr * sizeof(uint2))) ||
-                (st = ensure(c, c->log_counts, static_cast<size_t>(kMaxRegions) * 4)) ||
-                (st = ensure(c, c->log_boff, static_cast<size_t>(kMaxRegions + 1) * 4)))
-                return st;
-        }
-        a.log_frag = static_cast<uint4*>(c->log_frag.p);
-        a.log_aux = static_cast<uint2*>(c->log_aux.p);
-        a.log_region = static_cast<uint32_t>(log_region);
-        a.log_counts = static_cast<uint32_t*>(c->log_counts.p);
-    }
+    // twice the last call's largest count: per-wave counts vary from call to call (regions are handed
+    // out dynamically), and a static-mode call (which cannot grow the log) must fit
+    if (keep && (st = log_reserve(c, c->flog, a.n_blocks, c->flog.hint ? 2 * c->flog.hint + 1024
+                                  : (static_cast<uint64_t>(p.n_pix) * 2) / a.n_blocks + 1024, a)))
+        return st;
     if ((st = fwd_begin(c, p, a, s))) return st;
     {
         Timed t(c, SOUP_T_FWD, s);
@@ -849,23 +842,10 @@ static soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, Ras
     }
     HIP_TRY(c, hipGetLastError());
     if (keep) {
-        unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
-        // an eager call reads the largest count: an overflowing log is simply not
-        // used (the backward replays); in static mode the overflow is flagged
-        launch_region_scan(a.log_counts, log_nr, a.log_region, static_cast<uint32_t*>(c->log_boff.p), cnt + 4,
-                           c->fixed ? static_cast<unsigned int*>(c->flags.p) : nullptr, s);
-        HIP_TRY(c, hipGetLastError());
+        // an overflowing log is simply not used (the backward replays)
         bool ok = true;
-        if (!c->fixed) {
-            uint64_t* h = reinterpret_cast<uint64_t*>(c->host_stage);
-            HIP_TRY(c, hipMemcpyAsync(h, cnt + 4, 24, hipMemcpyDeviceToHost, s));
-            HIP_TRY(c, hipStreamSynchronize(s));
-            ok = h[2] <= log_region;
-            c->log_hint = h[2];
-        }
+        if ((st = log_summary(c, c->flog, s, &ok))) return st;
         c->log_valid = ok;
-        c->log_region = log_region;
-        c->log_regions = log_nr;
         c->log_seed = o.seed;
         c->log_step = o.step;
         c->log_mode = o.mode;
@@ -883,11 +863,6 @@ DecodeArgs decode_args(soup_ctx* c, const Plan& p, const RasterArgs& a) {
     d.G = p.G;
     d.T = p.scenes[0].T;
     d.verts = p.scenes[0].verts;
-    d.frags = static_cast<FragRec*>(c->frags.p);
-    d.region = static_cast<uint32_t>(c->frag_region);
-    d.counts = static_cast<uint32_t*>(c->region_counts.p);
-    d.boff = static_cast<uint32_t*>(c->region_boff.p);
-    d.n_regions = c->frag_regions;
     d.counter = a.counter;
     d.n_blocks = decode_blocks(c);
     return d;
@@ -903,11 +878,10 @@ soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = plan_single(c, p, scene, views))) return st;
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color) return fail(c, SOUP_ERR_INVALID, "vis and color outputs are required");
-    if (logp && (st = check_decode_lds(c, p.kind, p.G, true))) return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     if ((st = bin(c, p, o, s))) return st;
-    RasterArgs a = raster_args(c, p, o);
+    RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = vis;
     a.color = color;
     // reuse_bins: keep a log of the decoded fragments for the backward
@@ -917,15 +891,17 @@ soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_
         Timed t(c, SOUP_T_LOGP, s);
         launch_fill_f32(logp, p.n_pix, 0.0f, s);
         if (o.mode == 0) {
-            RasterArgs ra = a;
-            ra.counter = nullptr;
-            int64_t n_frag = 0, n_batch = 0;
-            if ((st = replay(c, p, ra, vis, nullptr, nullptr, nullptr, true, nullptr, 0, s, &n_frag, &n_batch,
-                             keep && c->log_valid)))
-                return st;
-            DecodeArgs d = decode_args(c, p, ra);
-            d.logp = logp;
-            launch_decode_bwd(d, p.kind, true, s);
+            const bool from_log = keep && c->log_valid;
+            if (!from_log && (st = replay(c, p, o, vis, nullptr, nullptr, nullptr, true, s))) return st;
+            LogpArgs la{};
+            la.log = log_view(from_log ? c->flog : c->rlog);
+            la.sel = FragSelect{vis, nullptr, 1};
+            la.feats = p.scenes[0].feats;
+            la.mlp = p.scenes[0].mlp;
+            la.weights = static_cast<float*>(c->fwd_weights.p);
+            la.G = p.G;
+            la.logp = logp;
+            launch_logp(la, p.kind, s);
         }
         HIP_TRY(c, hipGetLastError());
     }
@@ -945,7 +921,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color || !grad_color) return fail(c, SOUP_ERR_INVALID, "vis, color and grad_color are required");
     if (!grad_verts || !grad_feats || !grad_mlp) return fail(c, SOUP_ERR_INVALID, "gradient outputs are required");
-    if ((st = check_decode_lds(c, p.kind, p.G, false))) return st;
+    if ((st = check_decode_lds(c, p.kind, p.G))) return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     bool reused = false;
@@ -966,13 +942,9 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     const int64_t n_grid = static_cast<int64_t>(scene->G) * scene->G * scene->C;
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
         (st = ensure(c, c->partial, static_cast<size_t>(rows) * p.n_params * 4)) ||
-        (st = ensure(c, c->mlp_mid, static_cast<size_t>(mlp_reduce_mid_rows(rows)) * p.n_params * 8)) ||
-        (st = ensure(c, c->tri_count, static_cast<size_t>(T) * 4)) ||
-        (st = ensure(c, c->tri_fill, static_cast<size_t>(T) * 8)) ||
-        (st = ensure(c, c->tri_off, static_cast<size_t>(T + 1) * 8)) ||
-        (st = ensure(c, c->tri_bsum, static_cast<size_t>((T + 1023) / 1024 + 1) * 8)))
+        (st = ensure(c, c->mlp_mid, static_cast<size_t>(mlp_reduce_mid_rows(rows)) * p.n_params * 8)))
         return st;
-    RasterArgs a = raster_args(c, p, o);
+    RasterArgs a = raster_args(c, p, o, p.kind);
     const float* gl = o.mode == 0 ? grad_logp : nullptr;
     const float2* ew = nullptr;
     if (o.edge_pairs != 2) {
@@ -980,30 +952,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
         launch_edge_weights(a.views, a.V, p.n_pix, o, vis, color, grad_color, static_cast<float2*>(c->edge_w.p), s);
         ew = static_cast<float2*>(c->edge_w.p);
     }
-    int64_t n_frag = 0, n_batch = 0;
-    if ((st = replay(c, p, a, vis, grad_color, gl, ew, false, static_cast<int32_t*>(c->tri_count.p), T, s, &n_frag,
-                     &n_batch, from_log)))
-        return st;
-    // the list sorted by triangle has at most as many entries as the regions hold
-    const int64_t frag_cap = static_cast<int64_t>(c->frag_regions) * static_cast<int64_t>(c->frag_region);
-    if ((st = ensure(c, c->sorted, static_cast<size_t>(frag_cap) * sizeof(FragRec)))) return st;
-    {
-        Timed t(c, SOUP_T_GRAD, s);
-        launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
-                    static_cast<int64_t*>(c->tri_off.p), s);
-        launch_fill_i32(static_cast<int32_t*>(c->tri_fill.p), 2 * T, 0, s);
-        PlaceArgs pa{};
-        pa.frags = static_cast<FragRec*>(c->frags.p);
-        pa.region = static_cast<uint32_t>(c->frag_region);
-        pa.counts = static_cast<uint32_t*>(c->region_counts.p);
-        pa.boff = static_cast<uint32_t*>(c->region_boff.p);
-        pa.n_regions = c->frag_regions;
-        pa.tri_off = static_cast<int64_t*>(c->tri_off.p);
-        pa.tri_fill = static_cast<unsigned long long*>(c->tri_fill.p);
-        pa.sorted = static_cast<FragRec*>(c->sorted.p);
-        pa.n_blocks = decode_blocks(c);
-        launch_place(pa, s);
-    }
+    if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, s))) return st;
     {
         Timed t(c, SOUP_T_FILL, s);
         if (!o.accumulate) {
@@ -1022,7 +971,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
         d.accumulate = o.accumulate;
         d.mlp_partial = static_cast<float*>(c->partial.p);
         Timed t(c, SOUP_T_BWD, s);
-        launch_decode_bwd(d, p.kind, false, s);
+        launch_decode_bwd(d, p.kind, s);
     }
     HIP_TRY(c, hipGetLastError());
     {
@@ -1074,7 +1023,7 @@ soup_status soup_render(soup_ctx* c, const soup_scene* scenes, int32_t R, const 
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     if ((st = bin(c, p, o, s))) return st;
-    RasterArgs a = raster_args(c, p, o);
+    RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = nullptr;
     a.color = nullptr;
     if ((st = fwd_begin(c, p, a, s))) return st;
@@ -1099,7 +1048,7 @@ soup_status soup_pforward(soup_ctx* c, const soup_pscene* scene, const soup_view
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     if ((st = bin(c, p, o, s))) return st;
-    RasterArgs a = raster_args(c, p, o);
+    RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = vis;
     a.color = color;
     const bool keep = o.reuse_bins != 0 || (logp && o.mode == 0);
@@ -1124,22 +1073,13 @@ soup_status soup_pforward(soup_ctx* c, const soup_pscene* scene, const soup_view
         Timed t(c, SOUP_T_LOGP, s);
         launch_fill_f32(logp, p.n_pix, 0.0f, s);
         if (o.mode == 0) {
-            RasterArgs ra = a;
-            ra.counter = nullptr;
-            int64_t n_frag = 0, n_batch = 0;
-            if ((st = replay(c, p, ra, vis, nullptr, nullptr, nullptr, true, nullptr, 0, s, &n_frag, &n_batch,
-                             c->log_valid)))
-                return st;
+            if (!c->log_valid && (st = replay(c, p, o, vis, nullptr, nullptr, nullptr, true, s))) return st;
             PFragArgs fa{};
-            fa.frags = static_cast<FragRec*>(c->frags.p);
-            fa.region = static_cast<uint32_t>(c->frag_region);
-            fa.counts = static_cast<uint32_t*>(c->region_counts.p);
-            fa.boff = static_cast<uint32_t*>(c->region_boff.p);
-            fa.n_regions = c->frag_regions;
+            fa.log = log_view(c->log_valid ? c->flog : c->rlog);
+            fa.sel = FragSelect{vis, nullptr, 1};
             fa.tex = scene->tex;
             fa.R = scene->R;
             fa.logp = logp;
-            fa.n_blocks = decode_blocks(c);
             launch_pfrag(fa, true, s);
         }
         HIP_TRY(c, hipGetLastError());
@@ -1216,13 +1156,9 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
         (st = ensure(c, c->partial, static_cast<size_t>(rows) * kPParams * 4)) ||
         (st = ensure(c, c->mlp_mid, static_cast<size_t>(mlp_reduce_mid_rows(rows)) * kPParams * 8)) ||
-        (st = ensure(c, c->gvert, static_cast<size_t>(T) * 9 * sizeof(double))) ||
-        (st = ensure(c, c->tri_count, static_cast<size_t>(T) * 4)) ||
-        (st = ensure(c, c->tri_fill, static_cast<size_t>(T) * 8)) ||
-        (st = ensure(c, c->tri_off, static_cast<size_t>(T + 1) * 8)) ||
-        (st = ensure(c, c->tri_bsum, static_cast<size_t>((T + 1023) / 1024 + 1) * 8)))
+        (st = ensure(c, c->gvert, static_cast<size_t>(T) * 9 * sizeof(double))))
         return st;
-    RasterArgs a = raster_args(c, p, o);
+    RasterArgs a = raster_args(c, p, o, p.kind);
     const float2* ew = nullptr;
     if (o.edge_pairs != 2) {
         Timed t(c, SOUP_T_EDGE, s);
@@ -1244,29 +1180,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     if (sorted_path) {
         // every winner and, where the pixel carries a score weight, every fragment in
         // front of it (Eq. (9)), sorted by triangle
-        int64_t n_frag = 0, n_batch = 0;
-        if ((st = replay(c, p, a, vis, grad_color, gl, ew, false, static_cast<int32_t*>(c->tri_count.p), T, s,
-                         &n_frag, &n_batch, from_log)))
-            return st;
-        const int64_t frag_cap = static_cast<int64_t>(c->frag_regions) * static_cast<int64_t>(c->frag_region);
-        if ((st = ensure(c, c->sorted, static_cast<size_t>(frag_cap) * sizeof(FragRec)))) return st;
-        {
-            Timed t(c, SOUP_T_GRAD, s);
-            launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
-                        static_cast<int64_t*>(c->tri_off.p), s);
-            launch_fill_i32(static_cast<int32_t*>(c->tri_fill.p), 2 * T, 0, s);
-            PlaceArgs pa{};
-            pa.frags = static_cast<FragRec*>(c->frags.p);
-            pa.region = static_cast<uint32_t>(c->frag_region);
-            pa.counts = static_cast<uint32_t*>(c->region_counts.p);
-            pa.boff = static_cast<uint32_t*>(c->region_boff.p);
-            pa.n_regions = c->frag_regions;
-            pa.tri_off = static_cast<int64_t*>(c->tri_off.p);
-            pa.tri_fill = static_cast<unsigned long long*>(c->tri_fill.p);
-            pa.sorted = static_cast<FragRec*>(c->sorted.p);
-            pa.n_blocks = decode_blocks(c);
-            launch_place(pa, s);
-        }
+        if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, s))) return st;
         Timed t(c, SOUP_T_BWD, s);
         PTriArgs ta{};
         ta.views = a.views;
@@ -1296,21 +1210,16 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     } else {
         if (gl) {
             // the score term (Eq. (9)): every fragment in front of a winner, and the winner
-            int64_t n_frag = 0, n_batch = 0;
-            if ((st = replay(c, p, a, vis, grad_color, gl, nullptr, false, nullptr, 0, s, &n_frag, &n_batch,
-                             from_log)))
-                return st;
+            if (p.n_pix >= (int64_t(1) << 32))
+                return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
+            if (!from_log && (st = replay(c, p, o, vis, grad_color, gl, nullptr, false, s))) return st;
             Timed t(c, SOUP_T_GRAD, s);
             PFragArgs fa{};
-            fa.frags = static_cast<FragRec*>(c->frags.p);
-            fa.region = static_cast<uint32_t>(c->frag_region);
-            fa.counts = static_cast<uint32_t*>(c->region_counts.p);
-            fa.boff = static_cast<uint32_t*>(c->region_boff.p);
-            fa.n_regions = c->frag_regions;
+            fa.log = log_view(from_log ? c->flog : c->rlog);
+            fa.sel = FragSelect{vis, gl, 0};
             fa.tex = scene->tex;
             fa.R = scene->R;
             fa.grad_tex = grad_tex;
-            fa.n_blocks = decode_blocks(c);
             launch_pfrag(fa, false, s);
         }
         Timed t(c, SOUP_T_BWD, s);

@@ -176,6 +176,7 @@ __device__ __forceinline__ float uniform24(uint64_t seed, uint32_t pixel, uint32
 template <int C_, int H_, int NH_>
 struct MlpShape {
     static constexpr bool kPaper = false;   // the paper form's raster policy sets it
+    static constexpr bool kReplay = false;  // the walk with the winners known sets it
     static constexpr int C = C_;
     static constexpr int H = H_;
     static constexpr int NH = NH_;

@@ -3,10 +3,10 @@
 
 namespace soup {
 
-void launch_decode_bwd_k32_64_2(const DecodeArgs& a, bool logp, hipStream_t s) {
-    launch_decode_bwd_s<MlpShape<32, 64, 2>>(a, logp, s);
+void launch_decode_bwd_k32_64_2(const DecodeArgs& a, hipStream_t s) {
+    launch_decode_bwd_s<MlpShape<32, 64, 2>>(a, s);
 }
 
-size_t decode_bwd_lds_k32_64_2(int G, bool logp) { return decode_bwd_lds_s<MlpShape<32, 64, 2>>(G, logp); }
+size_t decode_bwd_lds_k32_64_2(int G) { return decode_bwd_lds_s<MlpShape<32, 64, 2>>(G); }
 
 }  // namespace soup

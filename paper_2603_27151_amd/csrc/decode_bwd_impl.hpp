@@ -1,6 +1,6 @@
 #pragma once
 // Backward, part 2 (Supplement Algorithm A1, part 2; Eq. (8), (9)): decode of
-// the fragment list written by the replay kernel.
+// the fragment list.
 //
 // The backward walks the fragment list sorted by triangle: every wave takes a
 // contiguous range of 64-fragment batches. For each batch:
@@ -26,10 +26,6 @@
 //     triangle's G x G x C grid; when the triangle changes, the grid goes to
 //     HBM once (a plain store when the wave holds all of the triangle's
 //     fragments, float atomics for a triangle split between waves).
-// A logp variant walks the unsorted fragment list region by region (batch b
-// lies in the region w with boff[w] <= b < boff[w + 1], found by a binary
-// search over the offsets staged in LDS) and sums log(1 - alpha) over the
-// front set and log(alpha) of the winner per pixel (log p(f*) of Eq. (6)).
 #include "decode_mfma.hpp"
 
 namespace soup {
@@ -217,17 +213,16 @@ struct MlpGrad {
     typename OutAccOf<S>::type out;
 };
 
-template <class S, bool LOGP>
+template <class S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void decode_bwd_kernel(DecodeArgs a) {
     constexpr int NW = 4;
     constexpr int SW = StageCfg<S>::kWidth;
-    __shared__ __align__(16) float s_stage[LOGP ? 1 : NW][LOGP ? 4 : kStageRows * SW];
-    __shared__ uint32_t s_boff[LOGP ? kMaxRegions + 1 : 1];
-    __shared__ MfmaWeights<S> s_w;     // the MLP in the matrix cores' operand order (backward only)
+    __shared__ __align__(16) float s_stage[NW][kStageRows * SW];
+    __shared__ MfmaWeights<S> s_w;     // the MLP in the matrix cores' operand order
     // the batch's feature gradients, rows of C padded by kRowPad (not for C = 32: that
     // shape's LDS is full)
     constexpr int DXS = S::C + (S::C >= 32 ? 0 : kRowPad);
-    __shared__ __align__(16) float s_dx[LOGP ? 1 : NW][LOGP ? 4 : 64 * DXS];
+    __shared__ __align__(16) float s_dx[NW][64 * DXS];
     extern __shared__ __align__(16) float s_dyn[];   // [NW][G*G*C + kGridTail]: per-wave gradient grid of the current triangle
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -236,39 +231,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     gfloat* __restrict__ feats = as_global(uniform_ptr(a.feats));
 
     MlpGrad<S> acc;
-    if (!LOGP) {
-        acc.l0.zero();
-        if constexpr (S::NH == 2) acc.mid[0].zero();
-        acc.out.zero();
-    }
-    if (!LOGP) {
-        s_w.load(a.mlp, tid, blockDim.x);
-        __syncthreads();
-    }
+    acc.l0.zero();
+    if constexpr (S::NH == 2) acc.mid[0].zero();
+    acc.out.zero();
+    s_w.load(a.mlp, tid, blockDim.x);
+    __syncthreads();
     const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * NW;
     const uint64_t wid = static_cast<uint64_t>(blockIdx.x) * NW + w;
-    uint64_t b_begin, b_end, b_step;
-    int64_t E = 0, f0 = 0, f1 = 0;   // sorted list: fragments, this wave's range
     float* grid = s_dyn + static_cast<size_t>(w) * (n_grid + kGridTail);
     double* vgrid = reinterpret_cast<double*>(grid + n_grid);   // the nine vertex sums (n_grid is even)
     int cur = -1;                    // triangle held in grid (wave-uniform)
-    if (LOGP) {
-        for (int i = tid; i <= a.n_regions; i += blockDim.x) s_boff[i] = a.boff[i];
-        __syncthreads();
-        b_begin = wid;
-        b_end = s_boff[a.n_regions];
-        b_step = n_waves;
-    } else {
-        E = a.tri_off[a.T];
-        const uint64_t nb = (static_cast<uint64_t>(E) + 63) / 64;
-        const uint64_t per = (nb + n_waves - 1) / n_waves;
-        b_begin = wid * per;
-        b_end = b_begin + per < nb ? b_begin + per : nb;
-        b_step = 1;
-        f0 = static_cast<int64_t>(b_begin) * 64;
-        f1 = static_cast<int64_t>(b_end) * 64 < E ? static_cast<int64_t>(b_end) * 64 : E;
-        for (int k = lane; k < n_grid + kGridTail; k += 64) grid[k] = 0.0f;
-    }
+    // this wave's contiguous range of the sorted fragments
+    const int64_t E = a.tri_off[a.T];
+    const uint64_t nb = (static_cast<uint64_t>(E) + 63) / 64;
+    const uint64_t per = (nb + n_waves - 1) / n_waves;
+    const uint64_t b_begin = wid * per, b_end = b_begin + per < nb ? b_begin + per : nb;
+    const int64_t f0 = static_cast<int64_t>(b_begin) * 64;
+    const int64_t f1 = static_cast<int64_t>(b_end) * 64 < E ? static_cast<int64_t>(b_end) * 64 : E;
+    for (int k = lane; k < n_grid + kGridTail; k += 64) grid[k] = 0.0f;
     // sorted list: the next batch's records, loaded one batch ahead, and the
     // per-pixel data of its winners (colour gradient, edge weights), loaded
     // once those records are in (after the current batch's MLP)
@@ -299,10 +279,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             }
         }
     };
-    if (!LOGP) {
-        prefetch(b_begin);
-        pixfetch();
-    }
+    prefetch(b_begin);
+    pixfetch();
     // the grid of triangle t goes to HBM and is cleared (whole wave)
     auto flush = [&](int t) __attribute__((always_inline)) {
         wave_fence();
@@ -323,32 +301,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         }
         wave_fence();
     };
-    for (uint64_t bi = b_begin; bi < b_end; bi += b_step) {
-        bool on;
+    for (uint64_t bi = b_begin; bi < b_end; ++bi) {
+        const bool on = static_cast<int64_t>(bi) * 64 + lane < E;
         uint4 fa = make_uint4(0u, 0u, 0u, 0u), fb4 = make_uint4(0u, 0u, 0u, 0u), fc4 = make_uint4(0u, 0u, 0u, 0u);
-        if (LOGP) {
-            int lo = 0, hi = a.n_regions - 1;   // region: last w with boff[w] <= bi
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_boff[mid] <= bi) lo = mid;
-                else hi = mid - 1;
-            }
-            const uint32_t cr = a.counts[lo];
-            const uint32_t in_region = (static_cast<uint32_t>(bi) - s_boff[lo]) * 64u + static_cast<uint32_t>(lane);
-            on = in_region < (cr < a.region ? cr : a.region);
-            if (on) {
-                const FragRec fr = a.frags[static_cast<uint64_t>(lo) * a.region + in_region];
-                fa = make_uint4(fr.p0.x, fr.p0.y, fr.p1.x, fr.p1.y);
-            }
-        } else {
-            on = static_cast<int64_t>(bi) * 64 + lane < E;
-            if (on) {
-                fa = na;
-                fb4 = make_uint4(nx.x, __float_as_uint(ng0), __float_as_uint(ng1), __float_as_uint(ng2));
-                fc4 = make_uint4(__float_as_uint(nex), __float_as_uint(ney), nx.y, 0u);
-            }
-            prefetch(bi + 1);
+        if (on) {
+            fa = na;
+            fb4 = make_uint4(nx.x, __float_as_uint(ng0), __float_as_uint(ng1), __float_as_uint(ng2));
+            fc4 = make_uint4(__float_as_uint(nex), __float_as_uint(ney), nx.y, 0u);
         }
+        prefetch(bi + 1);
         const uint32_t pix = fa.x;
         const uint32_t tri = fa.y & 0x7FFFFFFFu;
         const bool win = on && (fa.y >> 31);
@@ -356,22 +317,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         const Cell c = cell_of(b1, b2, G);
         const uint64_t on_mask = __ballot(on);
         if (a.counter && lane == 0) atomicAdd(a.counter, static_cast<unsigned long long>(__popcll(on_mask)));
-        if (LOGP) {
-            float x[S::C];
-            MlpAct<S> m;
-            if (on) {
-                fetch_feature<S::C>(feats, tri, G, c, x);
-            } else {
-#pragma unroll
-                for (int k = 0; k < S::C; ++k) x[k] = 0.0f;
-            }
-            // an opaque copy of the weight pointer per batch: the compiler may
-            // not hoist the weights' scalar loads out of the batch loop
-            mlp_forward<S>(as_const(opaque_ptr(a.mlp)), x, m);
-            const float alpha = sigmoid_c(m.o[3]);
-            if (on) atomicAdd(&a.logp[pix], win ? logf(alpha) : log1pf(-alpha));
-            continue;
-        }
         float* st = s_stage[w];
         const uint32_t cellw = static_cast<uint32_t>(c.ix) | (static_cast<uint32_t>(c.iy) << 16);
         // the fragment's triangle and winner bit, 0x7FFFFFFF for an empty lane
@@ -810,38 +755,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             wave_fence();
         }
     }
-    if (!LOGP && cur >= 0) flush(cur);
-    if (!LOGP) {
-        float* row = a.mlp_partial + (static_cast<size_t>(blockIdx.x) * NW + w) * S::kParams;
-        acc.l0.store(row, S::w_off(0), S::b_off(0), lane);
-        if constexpr (S::NH == 2) acc.mid[0].store(row, S::w_off(1), S::b_off(1), lane);
-        acc.out.store(row, S::w_off(S::NH), S::b_off(S::NH), lane);
-    }
+    if (cur >= 0) flush(cur);
+    float* row = a.mlp_partial + (static_cast<size_t>(blockIdx.x) * NW + w) * S::kParams;
+    acc.l0.store(row, S::w_off(0), S::b_off(0), lane);
+    if constexpr (S::NH == 2) acc.mid[0].store(row, S::w_off(1), S::b_off(1), lane);
+    acc.out.store(row, S::w_off(S::NH), S::b_off(S::NH), lane);
 }
 
 // Bytes of LDS one workgroup of the decode needs (static + dynamic), or 0 when
 // the runtime cannot say.
 template <class S>
-static size_t decode_bwd_lds_s(int G, bool logp) {
+static size_t decode_bwd_lds_s(int G) {
     hipFuncAttributes fa;
-    const hipError_t e = logp ? hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(decode_bwd_kernel<S, true>))
-                              : hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(decode_bwd_kernel<S, false>));
-    if (e != hipSuccess) {
+    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(decode_bwd_kernel<S>)) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
-    const size_t dyn = logp ? 0 : static_cast<size_t>(4) * (static_cast<size_t>(G) * G * S::C + kGridTail) * sizeof(float);
-    return fa.sharedSizeBytes + dyn;
+    return fa.sharedSizeBytes + static_cast<size_t>(4) * (static_cast<size_t>(G) * G * S::C + kGridTail) * sizeof(float);
 }
 
 template <class S>
-static void launch_decode_bwd_s(const DecodeArgs& a, bool logp, hipStream_t s) {
-    if (logp) {
-        hipLaunchKernelGGL((decode_bwd_kernel<S, true>), dim3(a.n_blocks), dim3(256), 0, s, a);
-    } else {
-        const size_t lds = static_cast<size_t>(4) * (static_cast<size_t>(a.G) * a.G * S::C + kGridTail) * sizeof(float);
-        hipLaunchKernelGGL((decode_bwd_kernel<S, false>), dim3(a.n_blocks), dim3(256), lds, s, a);
-    }
+static void launch_decode_bwd_s(const DecodeArgs& a, hipStream_t s) {
+    const size_t lds = static_cast<size_t>(4) * (static_cast<size_t>(a.G) * a.G * S::C + kGridTail) * sizeof(float);
+    hipLaunchKernelGGL((decode_bwd_kernel<S>), dim3(a.n_blocks), dim3(256), lds, s, a);
 }
 
 }  // namespace soup

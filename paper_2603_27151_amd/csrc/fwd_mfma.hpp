@@ -38,7 +38,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // The weights of one scene as A operands (16-byte groups, offsets in groups).
 template <class S>
 struct FwdWeights {
-    static constexpr bool kMfma = !S::kPaper && S::H >= 32;   // 8->16->4 fills half a product's rows: vector ALU
+    static constexpr bool kMfma = S::H >= 32;   // 8->16->4 fills half a product's rows: vector ALU
     static constexpr int NB = S::H / 32;               // row blocks
     static constexpr int J0 = S::C / 8, J1 = S::H / 8; // groups of four steps per row block
     static constexpr int kW0 = 0;                      // [rb][j][64]: step 4 j + e: W0[32 rb + u(l & 31)][2 (4 j + e) + h]

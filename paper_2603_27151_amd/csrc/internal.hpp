@@ -37,8 +37,8 @@ constexpr unsigned kOverflowBins = 1u;
 constexpr unsigned kOverflowFragments = 2u;
 
 // MLP shapes compiled in: (C, H, NH); kPaper is the paper form's raster (opacity
-// texture only, the shading MLP deferred)
-enum class MlpKind { k8_16_1, k16_32_2, k32_64_2, kPaper, kNone };
+// texture only, the shading MLP deferred), kReplay the walk with the winners known
+enum class MlpKind { k8_16_1, k16_32_2, k32_64_2, kPaper, kReplay, kNone };
 MlpKind mlp_kind(int n_layers, const int32_t* dims);
 int mlp_params(int n_layers, const int32_t* dims);
 
@@ -63,12 +63,18 @@ struct RasterArgs {
     const float* weights;          // forward: every scene's weights as matrix operands (launch_fwd_begin), or null
     int n_blocks;                  // persistent grid of the forward (single-wave workgroups)
     int region;                    // side of a forward wave's region: 16 (tiles of 16, 32) or 8
-    // optional log of the forward's decoded fragments, one region per wave (= workgroup):
-    // log_frag = (pixel, triangle, b1, b2), log_aux = (depth bits, view)
-    uint4* log_frag;
-    uint2* log_aux;
+    // optional log of the decoded fragments, one region per wave (= workgroup)
+    uint4* log_frag;               // (pixel, triangle, depth bits, view)
+    uint2* log_bary;               // (b1, b2)
     uint32_t log_region;
     uint32_t* log_counts;
+    // the walk with the winners known: what it logs (sel.vis null: a forward), and the pixels'
+    // gradients, which decide whether a winner without a score weight is needed
+    const uint64_t* replay_vis;
+    const float* replay_color;     // [P,3] or null (every pixel is needed)
+    const float* replay_logp;      // [P] score weights or null
+    const float2* replay_edge;     // [P] edge weights or null
+    int replay_all;                // 1: every pixel needs its whole front set (log p)
 };
 
 // What a forward needs right before its raster: the work counters zeroed and, for the MLP shapes decoded on
@@ -86,85 +92,92 @@ inline int fwd_regions_per_tile(int tile, int region) { return (tile / region) *
 // One fragment the backward needs (24 bytes): p0 = (pixel, triangle | winner
 // << 31), p1 = the perspective-correct barycentrics (b1, b2) as bits, x =
 // (the pixel's score weight as bits, view). A winner's colour gradient and
-// edge weights are read from the per-pixel arrays by the decode (half of the
-// fragments are winners; the list is written, placed and read again, so the
-// smaller record moves 1.2 GB less per step on the batched workload).
+// edge weights are read from the per-pixel arrays by the decode.
 struct FragRec {
     uint2 p0;
     uint2 p1;
     uint2 x;
 };
 
-// The fragment list is split into one region of `region` entries per replay
-// wave (wave w owns [w * region, (w + 1) * region)), so that no two waves
-// share a counter. counts[w] is the number of fragments wave w found (it may
-// exceed `region`: the call then runs again with larger regions).
+// A log of fragments, one region of `region` entries per wave of the raster
+// that wrote it (so that no two waves share a counter). counts[w] is the number
+// of fragments wave w found (it may exceed `region`: the log is then not used,
+// or, in static-capacity mode, cut there and flagged).
 constexpr int kMaxRegions = 4096;
-
-struct ReplayArgs {
-    RasterArgs r;
-    const uint64_t* vis;
-    const float* grad_color;       // [P,3] (null in the logp pass)
-    const float* grad_logp;        // [P] or null
-    const float2* edge_w;          // [P] edge weights or null
-    int all_front;                 // logp pass: every pixel needs its whole front set
-    FragRec* frags;                // [n_regions * region]
-    uint32_t region;
-    uint32_t* counts;              // [n_regions]
-    int32_t* tri_count;            // [T] fragments per triangle (added to; null: not counted)
-    int n_blocks;                  // persistent grid size (n_regions = n_blocks * waves per block)
-};
-
-void launch_replay(const ReplayArgs& a, int tile, hipStream_t s);
-
-// The same fragment list as the replay, filtered from the forward's log:
-// every fragment with key <= the pixel's winner key was decoded (and logged)
-// by the forward, since the forward's best key never drops below the winner's.
-struct CollectArgs {
-    const uint4* log_frag;
-    const uint2* log_aux;          // (depth bits, view) per logged fragment
-    uint32_t log_region;
-    const uint32_t* log_counts;    // [log_regions]
-    const uint32_t* log_boff;      // [log_regions + 1] batch offsets of the log
-    int log_regions;
-    const uint64_t* vis;
-    const float* grad_logp;        // [P] or null
-    int all_front;                 // logp pass
-    FragRec* frags;
-    uint32_t region;
-    uint32_t* counts;              // [n_blocks * 4]
-    int32_t* tri_count;            // [T] or null
-    int n_blocks;
-};
-
-void launch_collect(const CollectArgs& a, hipStream_t s);
-int replay_waves_per_block(int tile);
-
-// Batch offsets of the regions: boff[w] = sum over v < w of ceil(min(counts[v],
-// region) / 64), boff[n] = total batches; summary = (fragments, batches,
-// largest region count); an overflow sets kOverflowFragments in *sticky
-// (when not null).
-void launch_region_scan(const uint32_t* counts, int n, uint32_t region, uint32_t* boff,
-                        unsigned long long* summary, unsigned int* sticky, hipStream_t s);
-
-// Counting-sort placement of the fragment list by triangle. Within triangle
-// t's range [tri_off[t], tri_off[t + 1]) its winners come first (filled
-// upwards from the start) and the fragments in front of winners last (filled
-// downwards from the end), so that most 64-fragment batches of the decode
-// hold winners only or none.
-struct PlaceArgs {
-    const FragRec* frags;
-    uint32_t region;
+struct FragLogView {
+    const uint4* frag;             // (pixel, triangle, depth bits, view)
+    const uint2* bary;             // (b1, b2)
     const uint32_t* counts;        // [n_regions]
-    const uint32_t* boff;          // [n_regions + 1]
+    uint32_t region;
     int n_regions;
-    const int64_t* tri_off;        // [T + 1] exclusive scan of the per-triangle counts
-    unsigned long long* tri_fill;  // [T] zeroed: winners placed (low 32 bits), others (high 32 bits)
-    FragRec* sorted;               // [tri_off[T]]
-    int n_blocks;
+    int split;                     // waves that share a region's batches of 64
+};
+// 64-entry batches of one region.
+__host__ __device__ constexpr uint32_t log_slots(uint32_t region) { return (region + 63) / 64; }
+// Workgroups of four waves for the kernels that read a log: one wave per share of a
+// region, at most four workgroups per CU of this GPU (the list kernels gain nothing from more).
+inline unsigned log_blocks(const FragLogView& L) {
+    const int64_t waves = static_cast<int64_t>(L.n_regions) * L.split;
+    return static_cast<unsigned>(waves < 4 ? 1 : waves > 4096 ? 1024 : (waves + 3) / 4);
+}
+
+// Which fragments of a log are kept: the pixel's winner, and every fragment in
+// front of it where the pixel carries a score weight (or everywhere).
+struct FragSelect {
+    const uint64_t* vis;
+    const float* grad_logp;        // [P] or null
+    int all_front;                 // log p: every fragment in front
+    __device__ __forceinline__ void decide(const uint4& e, bool& keep, bool& win) const {
+        const uint64_t key = (static_cast<uint64_t>(e.z) << 32) | e.y;
+        const uint64_t kstar = vis[e.x];
+        win = key == kstar;
+        keep = win || (key < kstar && (all_front || (grad_logp && grad_logp[e.x] != 0.0f)));
+    }
 };
 
-void launch_place(const PlaceArgs& a, hipStream_t s);
+#if defined(__HIPCC__)
+// f(region, first entry, entries of the region) for every batch of this wave
+// (workgroups of four waves; wave-uniform arguments).
+template <class F>
+__device__ __forceinline__ void for_log_batches(const FragLogView& L, F&& f) {
+    const uint32_t n_items = static_cast<uint32_t>(L.n_regions) * static_cast<uint32_t>(L.split);
+    const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    for (uint32_t it = blockIdx.x * 4 + w; it < n_items; it += gridDim.x * 4) {
+        const uint32_t r = it / static_cast<uint32_t>(L.split), q = it % static_cast<uint32_t>(L.split);
+        const uint32_t c = L.counts[r], n = c < L.region ? c : L.region;
+        for (uint32_t b = 64 * q; b < n; b += 64 * static_cast<uint32_t>(L.split)) f(r, b, n);
+    }
+}
+// Lanes 0..l, and the lanes of the run that starts at head lane l (heads: the first lanes of all runs).
+__device__ __forceinline__ uint64_t upto_mask(int l) { return ~0ull >> (63 - l); }
+__device__ __forceinline__ uint64_t run_of(uint64_t heads, int l) {
+    const uint64_t above = heads & ~upto_mask(l);
+    return (above ? (1ull << __builtin_ctzll(above)) - 1 : ~0ull) & (~0ull << l);
+}
+#endif
+
+// Total and largest count of a log's regions; an overflow sets kOverflowFragments in *sticky (when not null).
+void launch_log_summary(const uint32_t* counts, int n, uint32_t region, unsigned long long* summary,
+                        unsigned int* sticky, hipStream_t s);
+// What is kept of a log, per 64 entries the masks (kept, winners), log_slots(region) per region,
+// and the kept fragments per triangle (added to tri_count [T]).
+void launch_count(const FragLogView& L, const FragSelect& sel, ulonglong2* masks, int32_t* tri_count, hipStream_t s);
+// Counting-sort placement by triangle: within triangle t's range [tri_off[t], tri_off[t + 1])
+// (the scanned counts) its winners come first (filled upwards) and the fragments in front of
+// winners last (filled downwards). tri_fill [T] zeroed: winners placed (low 32 bits), others (high).
+void launch_place(const FragLogView& L, const float* grad_logp, const ulonglong2* masks, const int64_t* tri_off,
+                  unsigned long long* tri_fill, FragRec* sorted, hipStream_t s);
+
+struct LogpArgs {
+    FragLogView log;
+    FragSelect sel;
+    const float* feats;
+    const float* mlp;
+    const float* weights;          // the scene's weights as the forward's matrix operands
+    int G;
+    float* logp;                   // [P], zeroed by the caller
+};
+void launch_logp(const LogpArgs& a, MlpKind k, hipStream_t s);
 
 struct DecodeArgs {
     const ViewDesc* views;
@@ -174,13 +187,7 @@ struct DecodeArgs {
     const float* mlp;
     int G;
     int T;
-    // logp pass: the region list
-    const FragRec* frags;
-    uint32_t region;
-    const uint32_t* counts;        // [n_regions]
-    const uint32_t* boff;          // [n_regions + 1]
-    int n_regions;
-    // backward: the list sorted by triangle
+    // the list sorted by triangle
     const FragRec* sorted;         // [tri_off[T]]
     const int64_t* tri_off;        // [T + 1]
     const float* verts;            // [T, 3, 3]: the winners' clip coordinates are recomputed
@@ -190,14 +197,13 @@ struct DecodeArgs {
     float* grad_verts;             // [T, 9]: zeroed by the caller unless accumulate
     int accumulate;
     float* mlp_partial;            // [n_blocks * 4, n_params]
-    float* logp;                   // logp output (logp pass only; zeroed by the caller)
     unsigned long long* counter;   // decode counter or null
     int n_blocks;
 };
 
-void launch_decode_bwd(const DecodeArgs& a, MlpKind k, bool logp_pass, hipStream_t s);
+void launch_decode_bwd(const DecodeArgs& a, MlpKind k, hipStream_t s);
 // LDS bytes one workgroup of the decode needs for a grid side G (0: unknown).
-size_t decode_bwd_lds(MlpKind k, int G, bool logp_pass);
+size_t decode_bwd_lds(MlpKind k, int G);
 // ew[p] = (x, y) edge weights of the pairs pixel p occludes (Section 3.2),
 // written for covered pixels only (a background pixel occludes nothing)
 void launch_edge_weights(const ViewDesc* views, int V, int64_t P, const Opts& o, const uint64_t* vis,
@@ -245,16 +251,12 @@ struct PShadeArgs {
 void launch_pshade(const PShadeArgs& a, hipStream_t s);
 
 struct PFragArgs {
-    const FragRec* frags;
-    uint32_t region;
-    const uint32_t* counts;
-    const uint32_t* boff;
-    int n_regions;
+    FragLogView log;
+    FragSelect sel;
     const float* tex;
     int R;
     float* grad_tex;                 // score pass: d / d opacity channel (added to)
     float* logp;                     // logp pass (zeroed by the caller)
-    int n_blocks;
 };
 void launch_pfrag(const PFragArgs& a, bool logp, hipStream_t s);
 

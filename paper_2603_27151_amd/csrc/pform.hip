@@ -425,36 +425,26 @@ void launch_pshade(const PShadeArgs& a, hipStream_t s) {
 
 template <bool LOGP>
 __global__ __launch_bounds__(256) void pfrag_kernel(PFragArgs a) {
-    __shared__ uint32_t s_boff[kMaxRegions + 1];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int i = tid; i <= a.n_regions; i += blockDim.x) s_boff[i] = a.boff[i];
-    __syncthreads();
-    const uint32_t n_batch = s_boff[a.n_regions];
-    const uint32_t n_waves = gridDim.x * 4;
+    const int lane = threadIdx.x & 63;
     const int n = 1 << a.R, V = mc_count(a.R);
     gfloat* tex = as_global(a.tex);
-    for (uint32_t bi = blockIdx.x * 4 + w; bi < n_batch; bi += n_waves) {
-        int lo = 0, hi = a.n_regions - 1;   // region: last w with boff[w] <= bi
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_boff[mid] <= bi) lo = mid;
-            else hi = mid - 1;
-        }
-        const uint32_t cr = a.counts[lo];
-        const uint32_t in_region = (bi - s_boff[lo]) * 64u + static_cast<uint32_t>(lane);
-        if (in_region >= (cr < a.region ? cr : a.region)) continue;
-        const FragRec fr = a.frags[static_cast<uint64_t>(lo) * a.region + in_region];
-        const uint32_t tri = fr.p0.y & 0x7FFFFFFFu;
-        const bool win = (fr.p0.y >> 31) != 0u;
-        const float b1 = __uint_as_float(fr.p1.x), b2 = __uint_as_float(fr.p1.y);
-        const Micro m = micro_of(n, b1, b2);
+    for_log_batches(a.log, [&](uint32_t r, uint32_t b, uint32_t cnt) {
+        if (b + lane >= cnt) return;
+        const uint64_t at = static_cast<uint64_t>(r) * a.log.region + b + lane;
+        const uint4 e = a.log.frag[at];
+        bool keep, win;
+        a.sel.decide(e, keep, win);
+        if (!keep) return;
+        const uint32_t tri = e.y;
+        const uint2 bc = a.log.bary[at];
+        const Micro m = micro_of(n, __uint_as_float(bc.x), __uint_as_float(bc.y));
         gfloat* t = tex + static_cast<size_t>(tri) * V * kPCh + (kPCh - 1);
         const float alpha = mc_mix(m, t[m.idx[0] * kPCh], t[m.idx[1] * kPCh], t[m.idx[2] * kPCh]);
         if constexpr (LOGP) {
-            atomicAdd(&a.logp[fr.p0.x], win ? logf(alpha) : log1pf(-alpha));
+            atomicAdd(&a.logp[e.x], win ? logf(alpha) : log1pf(-alpha));
         } else {
-            const float gl = __uint_as_float(fr.x.x);
-            if (gl == 0.0f) continue;
+            const float gl = a.sel.grad_logp[e.x];
+            if (gl == 0.0f) return;
             // d log p / d alpha: 1 / alpha for the winner, -1 / (1 - alpha) in front of it
             const float da = win ? gl / alpha : -gl / (1.0f - alpha);
             float* g = a.grad_tex + static_cast<size_t>(tri) * V * kPCh + (kPCh - 1);
@@ -462,13 +452,13 @@ __global__ __launch_bounds__(256) void pfrag_kernel(PFragArgs a) {
             for (int q = 0; q < 3; ++q)
                 if (m.w[q] != 0.0f) atomicAdd(&g[m.idx[q] * kPCh], m.w[q] * da);
         }
-    }
+    });
 }
 
 void launch_pfrag(const PFragArgs& a, bool logp, hipStream_t s) {
-    if (a.n_blocks <= 0) return;
-    if (logp) hipLaunchKernelGGL(pfrag_kernel<true>, dim3(a.n_blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(pfrag_kernel<false>, dim3(a.n_blocks), dim3(256), 0, s, a);
+    const dim3 grid(log_blocks(a.log));
+    if (logp) hipLaunchKernelGGL(pfrag_kernel<true>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(pfrag_kernel<false>, grid, dim3(256), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -37,6 +37,7 @@ constexpr int kPMaxR = 7;         // finest level compiled for: 8385 grid vertic
 // kPaper = false).
 struct PaperTex {
     static constexpr bool kPaper = true;
+    static constexpr bool kReplay = false;
     static constexpr int C = kPCh, H = 0, NH = 0;
 };
 

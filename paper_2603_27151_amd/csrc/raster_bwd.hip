@@ -6,29 +6,29 @@
 
 namespace soup {
 
-void launch_decode_bwd_k8_16_1(const DecodeArgs& a, bool logp, hipStream_t s);
-void launch_decode_bwd_k16_32_2(const DecodeArgs& a, bool logp, hipStream_t s);
-void launch_decode_bwd_k32_64_2(const DecodeArgs& a, bool logp, hipStream_t s);
+void launch_decode_bwd_k8_16_1(const DecodeArgs& a, hipStream_t s);
+void launch_decode_bwd_k16_32_2(const DecodeArgs& a, hipStream_t s);
+void launch_decode_bwd_k32_64_2(const DecodeArgs& a, hipStream_t s);
 
-size_t decode_bwd_lds_k8_16_1(int G, bool logp);
-size_t decode_bwd_lds_k16_32_2(int G, bool logp);
-size_t decode_bwd_lds_k32_64_2(int G, bool logp);
+size_t decode_bwd_lds_k8_16_1(int G);
+size_t decode_bwd_lds_k16_32_2(int G);
+size_t decode_bwd_lds_k32_64_2(int G);
 
-size_t decode_bwd_lds(MlpKind k, int G, bool logp) {
+size_t decode_bwd_lds(MlpKind k, int G) {
     switch (k) {
-        case MlpKind::k8_16_1: return decode_bwd_lds_k8_16_1(G, logp);
-        case MlpKind::k16_32_2: return decode_bwd_lds_k16_32_2(G, logp);
-        case MlpKind::k32_64_2: return decode_bwd_lds_k32_64_2(G, logp);
+        case MlpKind::k8_16_1: return decode_bwd_lds_k8_16_1(G);
+        case MlpKind::k16_32_2: return decode_bwd_lds_k16_32_2(G);
+        case MlpKind::k32_64_2: return decode_bwd_lds_k32_64_2(G);
         default: return 0;
     }
 }
 
-void launch_decode_bwd(const DecodeArgs& a, MlpKind k, bool logp, hipStream_t s) {
+void launch_decode_bwd(const DecodeArgs& a, MlpKind k, hipStream_t s) {
     if (a.n_blocks <= 0) return;
     switch (k) {
-        case MlpKind::k8_16_1: launch_decode_bwd_k8_16_1(a, logp, s); break;
-        case MlpKind::k16_32_2: launch_decode_bwd_k16_32_2(a, logp, s); break;
-        case MlpKind::k32_64_2: launch_decode_bwd_k32_64_2(a, logp, s); break;
+        case MlpKind::k8_16_1: launch_decode_bwd_k8_16_1(a, s); break;
+        case MlpKind::k16_32_2: launch_decode_bwd_k16_32_2(a, s); break;
+        case MlpKind::k32_64_2: launch_decode_bwd_k32_64_2(a, s); break;
         default: break;
     }
 }

@@ -22,6 +22,13 @@ int raster_fwd_per_cu_paper_t8(int region);
 int raster_fwd_per_cu_paper_t16(int region);
 int raster_fwd_per_cu_paper_t32(int region);
 
+void launch_raster_replay_t8(const RasterArgs& a, hipStream_t s);
+void launch_raster_replay_t16(const RasterArgs& a, hipStream_t s);
+void launch_raster_replay_t32(const RasterArgs& a, hipStream_t s);
+int raster_replay_per_cu_t8(int region);
+int raster_replay_per_cu_t16(int region);
+int raster_replay_per_cu_t32(int region);
+
 int raster_fwd_per_cu_k8_16_1_t8(int region);
 int raster_fwd_per_cu_k8_16_1_t16(int region);
 int raster_fwd_per_cu_k8_16_1_t32(int region);
@@ -53,6 +60,11 @@ void launch_raster_fwd(const RasterArgs& a, int tile, MlpKind k, hipStream_t s) 
             if (tile == 8) launch_raster_fwd_paper_t8(a, s);
             else if (tile == 32) launch_raster_fwd_paper_t32(a, s);
             else launch_raster_fwd_paper_t16(a, s);
+            break;
+        case MlpKind::kReplay:
+            if (tile == 8) launch_raster_replay_t8(a, s);
+            else if (tile == 32) launch_raster_replay_t32(a, s);
+            else launch_raster_replay_t16(a, s);
             break;
         default: break;
     }
@@ -91,6 +103,8 @@ int raster_fwd_blocks_per_cu(int tile, MlpKind k, int region) {
             return tile == 8 ? raster_fwd_per_cu_k32_64_2_t8(region) : tile == 32 ? raster_fwd_per_cu_k32_64_2_t32(region) : raster_fwd_per_cu_k32_64_2_t16(region);
         case MlpKind::kPaper:
             return tile == 8 ? raster_fwd_per_cu_paper_t8(region) : tile == 32 ? raster_fwd_per_cu_paper_t32(region) : raster_fwd_per_cu_paper_t16(region);
+        case MlpKind::kReplay:
+            return tile == 8 ? raster_replay_per_cu_t8(region) : tile == 32 ? raster_replay_per_cu_t32(region) : raster_replay_per_cu_t16(region);
         default: return 1;
     }
 }

@@ -57,6 +57,16 @@ struct alignas(16) PairMeta {
     uint32_t off_blk;
 };
 
+// The walk with the winners known, for a backward without the forward's log
+// (Supplement Algorithm A1, part 2): a pixel's key starts one above its saved
+// winner's and never falls, so that the candidates are exactly the winner and
+// the fragments in front of it; a batch of them goes to the log instead of
+// through a decode.
+struct ReplayWalk {
+    static constexpr bool kPaper = false, kReplay = true;
+    static constexpr int C = 4, H = 0, NH = 0;
+};
+
 // LDS of one wave owning NB 8x8 blocks: with four blocks and the weights of
 // 16->32->32->4 13,488 bytes, so that twelve waves fit a CU's 160 KB.
 template <int NB, class S>
@@ -124,7 +134,7 @@ __device__ __forceinline__ uint64_t pick(const uint64_t (&arr)[N], int b) {
 }
 
 template <int TS, int RS, class S>
-__global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
+__global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(RasterArgs a) {
     static_assert(RS == 8 || (RS == 16 && TS >= 16), "a region is one 8x8 block, or 16x16 pixels of a larger tile");
     constexpr int BR = RS / 8, NB = BR * BR;       // 8x8 blocks per region
     constexpr int RT = TS / RS, RPT = RT * RT;     // regions per tile
@@ -206,8 +216,26 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
     uint64_t wmax = 0;   // ... over the region
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const bool inview = rx + (b % BR) * 8 + pu < W && ry + (b / BR) * 8 + pv < H;
-        const uint64_t k0 = inview ? kBgKey : 0ull;   // pixels outside the view never take fragments
+        const int gx = rx + (b % BR) * 8 + pu, gy = ry + (b / BR) * 8 + pv;
+        const bool inview = gx < W && gy < H;
+        uint64_t k0 = inview ? kBgKey : 0ull;   // pixels outside the view never take fragments
+        if constexpr (S::kReplay) {
+            if (inview) {
+                const int64_t p = pix_base + static_cast<int64_t>(gy) * W + gx;
+                const uint64_t kc = a.replay_vis[p];
+                const bool front = a.replay_all || (a.replay_logp && a.replay_logp[p] != 0.0f);
+                bool need = front;   // ... a winner alone, where it has a colour gradient or an edge weight
+                if (!front && kc != kBgKey) {
+                    const float* gc = a.replay_color + 3 * p;
+                    need = gc[0] != 0.0f || gc[1] != 0.0f || gc[2] != 0.0f;
+                    if (!need && a.replay_edge) {
+                        const float2 e = a.replay_edge[p];
+                        need = e.x != 0.0f || e.y != 0.0f;
+                    }
+                }
+                k0 = !need ? 0ull : kc == kBgKey ? kBgKey : kc + 1;
+            }
+        }
         L.key[b * 64 + lane] = k0;
         wmaxb[b] = wave_max_u64(k0);
         wmax = wmaxb[b] > wmax ? wmaxb[b] : wmax;
@@ -216,6 +244,33 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
 
     // decode a batch of n queued candidates, one per lane
     auto run_batch = [&](int n) __attribute__((always_inline)) {
+        if constexpr (S::kReplay) {   // to the log: every winner, and what lies in front of it where that is needed
+            uint4 e = make_uint4(0u, 0u, 0u, static_cast<uint32_t>(v));
+            uint2 bc = make_uint2(0u, 0u);
+            bool keep = false;
+            if (lane < n) {
+                const uint64_t key = L.qkey[lane];
+                const int pl = static_cast<int>(L.qpl[lane]);
+                float b1, b2;
+                persp_from_t(L.qt[0][lane], L.qt[1][lane], L.qt[2][lane], b1, b2);
+                const int blk = pl >> 6, p = pl & 63;
+                const int gx = rx + (blk % BR) * 8 + (p & 7), gy = ry + (blk / BR) * 8 + (p >> 3);
+                const int64_t pg = pix_base + static_cast<int64_t>(gy) * W + gx;
+                e.x = static_cast<uint32_t>(pg);
+                e.y = static_cast<uint32_t>(key);
+                e.z = static_cast<uint32_t>(key >> 32);
+                bc = make_uint2(__float_as_uint(b1), __float_as_uint(b2));
+                keep = key + 1 == L.key[pl] || a.replay_all || (a.replay_logp && a.replay_logp[pg] != 0.0f);
+            }
+            const uint64_t km = __ballot(keep);
+            const uint32_t at = log_cursor + static_cast<uint32_t>(__popcll(km & lanemask_lt()));
+            if (keep && at < a.log_region) {
+                a.log_frag[log_base + at] = e;
+                a.log_bary[log_base + at] = bc;
+            }
+            log_cursor += static_cast<uint32_t>(__popcll(km));
+            return;
+        }
         // the colour stores below may overwrite a pixel's colour from an earlier
         // batch: those stores complete first (the only wait on global memory
         // that the LDS ordering of this kernel needs)
@@ -260,7 +315,7 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                     pass = alpha > 0.5f;
                 }
             } else {
-                if constexpr (!FwdWeights<S>::kMfma) {
+                if constexpr (!FwdWeights<S>::kMfma && !S::kReplay) {
                     const Cell c = cell_of(b1, b2, G);
                     float x[S::C];
                     fetch_feature<S::C>(feats, tri, G, c, x);
@@ -279,9 +334,9 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
                 const uint32_t at = log_cursor + static_cast<uint32_t>(lane);
                 if (at < a.log_region) {
                     const int64_t pg = pix_base + static_cast<int64_t>(gy) * W + gx;
-                    a.log_frag[log_base + at] =
-                        make_uint4(static_cast<uint32_t>(pg), tri, __float_as_uint(b1), __float_as_uint(b2));
-                    a.log_aux[log_base + at] = make_uint2(static_cast<uint32_t>(key >> 32), static_cast<uint32_t>(v));
+                    a.log_frag[log_base + at] = make_uint4(static_cast<uint32_t>(pg), tri, static_cast<uint32_t>(key >> 32),
+                                                           static_cast<uint32_t>(v));
+                    a.log_bary[log_base + at] = make_uint2(__float_as_uint(b1), __float_as_uint(b2));
                 }
             }
         }
@@ -581,8 +636,8 @@ __global__ __launch_bounds__(64, 3) void raster_fwd_kernel(RasterArgs a) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (!oin[b]) continue;
-        if (vis_base) vis_base[ooff[b]] = okey[b];
-        if (!S::kPaper && okey[b] == kBgKey) {   // covered pixels got their colour when their best key was set
+        if (!S::kReplay && vis_base) vis_base[ooff[b]] = okey[b];
+        if (!S::kPaper && !S::kReplay && okey[b] == kBgKey) {   // covered pixels got their colour when their best key was set
             gfloat_w* col = color_base + 3 * ooff[b];
             col[0] = a.o.bg[0];
             col[1] = a.o.bg[1];
