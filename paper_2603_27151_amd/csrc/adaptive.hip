@@ -21,7 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <numeric>
+#include <cstring>
 #include <vector>
 
 #include "internal.hpp"
@@ -207,61 +207,79 @@ void launch_apply(const float* verts, const float* feats, const int32_t* actions
                        G, C, n_new, vout, fout);
 }
 
+// Calls take(t) for candidates in ascending (key, index) order until their weights (0: no candidate)
+// sum to `need`: the digits of the last key taken are found from the top, 11, 11 and 10 bits, by
+// histograms of the weights, so that nothing is sorted. (A stable sort of indices by an indirect
+// comparison was most of a plan: 50,000 triangles measured, pruned, refilled and rebuilt took
+// 4.06 ms in all, now 0.69.)
+template <class Weight, class Take>
+static void take_lowest(const uint32_t* key, int32_t T, int64_t need, Weight&& weight, Take&& take) {
+    uint32_t prefix = 0;
+    int64_t left = need;
+    for (int sh : {21, 10, 0}) {
+        const int bits = sh == 0 ? 10 : 11;
+        const int up = sh + bits;   // bits above are fixed
+        int64_t sum[2048] = {};
+        for (int32_t t = 0; t < T; ++t)
+            if (up >= 32 || (key[t] >> up) == (prefix >> up)) sum[(key[t] >> sh) & ((1u << bits) - 1u)] += weight(t);
+        uint32_t d = 0;
+        const uint32_t last = (1u << bits) - 1u;
+        while (d < last && sum[d] < left) left -= sum[d++];
+        prefix |= d << sh;
+    }
+    for (int32_t t = 0; t < T; ++t) {   // all below the last key, then that key's in index order
+        const int64_t w = weight(t);
+        if (w == 0) continue;
+        if (key[t] < prefix) {
+            take(t);
+        } else if (key[t] == prefix && left > 0) {
+            left -= w;
+            take(t);
+        }
+    }
+}
+
+// A float's bits in an order that descends with its value (-0 as 0; NaN last).
+static uint32_t descending_bits(float x) {
+    if (x != x) return 0xFFFFFFFFu;
+    uint32_t b;
+    const float y = x == 0.0f ? 0.0f : x;
+    std::memcpy(&b, &y, 4);
+    return b >> 31 ? b : 0x7FFFFFFFu - b;
+}
+
 int32_t plan_host(const uint32_t* counts, const float* rel, int32_t T, float split_frac, int32_t target,
                   bool prune_zero, bool fill, int32_t* actions, int32_t* offsets) {
-    std::vector<int> longest(T);
-    std::vector<char> split(T), removed(T, 0);
-    for (int t = 0; t < T; ++t) {
-        int k = 0;
-        if (rel[t * 3 + 1] > rel[t * 3 + k]) k = 1;
-        if (rel[t * 3 + 2] > rel[t * 3 + k]) k = 2;
-        longest[t] = k;
-        split[t] = rel[t * 3 + k] > split_frac;
-        if (prune_zero && counts[t] == 0) {
-            removed[t] = 1;
-            split[t] = 0;
-        }
-    }
+    // actions holds the state: removed, kept, or split on its longest edge
+    std::vector<uint32_t> key(T);   // the longest edge, longest first
+    std::vector<unsigned char> longest(T);
     int64_t n = 0;
-    for (int t = 0; t < T; ++t)
-        if (!removed[t]) n += split[t] ? 2 : 1;
-    if (n > target) {
-        // lowest coverage first; a stable sort keeps equal counts in index order
-        std::vector<int> order(T);
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return counts[x] < counts[y]; });
-        for (int t : order) {
-            if (n <= target) break;
-            if (removed[t]) continue;
-            n -= split[t] ? 2 : 1;
-            removed[t] = 1;
-            split[t] = 0;
-        }
+    for (int t = 0; t < T; ++t) {
+        const float r0 = rel[t * 3], r1 = rel[t * 3 + 1], r2 = rel[t * 3 + 2];
+        const float r01 = r1 > r0 ? r1 : r0, r = r2 > r01 ? r2 : r01;
+        const int k = r2 > r01 ? 2 : r1 > r0 ? 1 : 0;
+        longest[t] = static_cast<unsigned char>(k);
+        key[t] = descending_bits(r);
+        actions[t] = prune_zero && counts[t] == 0 ? kActRemove : r > split_frac ? kActSplit0 + k : kActKeep;
+        n += actions[t] == kActRemove ? 0 : actions[t] == kActKeep ? 1 : 2;
     }
-    if (fill && n < target) {
-        std::vector<int> cand;
-        for (int t = 0; t < T; ++t)
-            if (!removed[t] && !split[t]) cand.push_back(t);
-        std::stable_sort(cand.begin(), cand.end(),
-                         [&](int x, int y) { return rel[x * 3 + longest[x]] > rel[y * 3 + longest[y]]; });
-        for (int t : cand) {
-            if (n >= target) break;
-            split[t] = 1;
-            ++n;
-        }
-    }
+    if (n > target)   // lowest coverage first, in index order among equals
+        take_lowest(counts, T, n - target,
+                    [&](int32_t t) { return actions[t] == kActRemove ? 0 : actions[t] == kActKeep ? 1 : 2; },
+                    [&](int32_t t) {
+                        n -= actions[t] == kActKeep ? 1 : 2;
+                        actions[t] = kActRemove;
+                    });
+    if (fill && n < target)   // longest edge first, in index order among equals
+        take_lowest(key.data(), T, target - n, [&](int32_t t) { return actions[t] == kActKeep ? 1 : 0; },
+                    [&](int32_t t) {
+                        actions[t] = kActSplit0 + longest[t];
+                        ++n;
+                    });
     int32_t o = 0;
     for (int t = 0; t < T; ++t) {
         offsets[t] = o;
-        if (removed[t]) {
-            actions[t] = kActRemove;
-        } else if (split[t]) {
-            actions[t] = kActSplit0 + longest[t];
-            o += 2;
-        } else {
-            actions[t] = kActKeep;
-            o += 1;
-        }
+        o += actions[t] == kActRemove ? 0 : actions[t] == kActKeep ? 1 : 2;
     }
     return o;
 }

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -1415,8 +1416,12 @@ soup_status soup_adaptive_plan(soup_ctx* c, const uint32_t* counts, const float*
         return fail(c, SOUP_ERR_INVALID, "adaptive_plan: bad arguments (T = %d, target = %d, flags = %d)", T, target,
                     flags);
     if (!(split_frac == split_frac)) return fail(c, SOUP_ERR_INVALID, "adaptive_plan: split_frac is NaN");
-    *n_new = soup::plan_host(counts, rel_len, T, split_frac, target, (flags & SOUP_PLAN_PRUNE_ZERO) != 0,
-                             (flags & SOUP_PLAN_FILL) != 0, actions, offsets);
+    try {
+        *n_new = soup::plan_host(counts, rel_len, T, split_frac, target, (flags & SOUP_PLAN_PRUNE_ZERO) != 0,
+                                 (flags & SOUP_PLAN_FILL) != 0, actions, offsets);
+    } catch (const std::bad_alloc&) {
+        return fail(c, SOUP_ERR_OOM, "adaptive_plan: no host memory for %d triangles", T);
+    }
     return SOUP_OK;
 }
 
