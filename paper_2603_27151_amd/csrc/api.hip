@@ -59,6 +59,7 @@ struct soup_ctx {
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
     DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, sorted, flags;
     DevBuf ssim;                                      // SSIM statistics of the training loss
+    DevBuf sum;                                       // the losses' parts (one double per workgroup)
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
     DevBuf gtex;                                      // its texture gradient when levels are asked for and the sorted path cannot fold them in
     void* host_stage = nullptr;      // pinned: descriptors up, totals down
@@ -521,7 +522,8 @@ namespace {
 // device, kept in noalloc_scratch_ptr.
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 constexpr int kNoAllocMaxDevices = 64;
-static __device__ __align__(256) float scratch[kNoAllocScratchBytes / sizeof(float)];
+// ... and behind it the loss's parts
+static __device__ __align__(256) float scratch[kNoAllocScratchBytes / sizeof(float) + 2 * kSumParts];
 
 std::mutex noalloc_scratch_mu;
 float* noalloc_scratch_ptr[kNoAllocMaxDevices] = {};
@@ -571,7 +573,10 @@ soup_status soup_ctx_create(soup_ctx** out, int device) {
     // error messages are formatted into a 512-byte buffer: with this capacity in
     // place, reporting one allocates no memory
     c->err.reserve(512);
-    if (noalloc_scratch_setup(c) != SOUP_OK) {
+    // the losses' parts: allocated here, so that a loss allocates nothing
+    c->sum.bytes = kSumParts * sizeof(double);
+    if (noalloc_scratch_setup(c) != SOUP_OK || hipMalloc(&c->sum.p, c->sum.bytes) != hipSuccess) {
+        (void)hipGetLastError();
         delete c;
         return SOUP_ERR_HIP;
     }
@@ -587,7 +592,7 @@ void soup_ctx_destroy(soup_ctx* c) {
                       &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
                       &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
                       &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
-                      &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
+                      &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
@@ -672,7 +677,7 @@ soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
                             &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
                             &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
                             &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
-                            &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
+                            &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     int64_t n = 0;
     for (const DevBuf* b : bufs) n += static_cast<int64_t>(b->bytes);
     *bytes = n;
@@ -1357,7 +1362,7 @@ soup_status soup_loss_l2(soup_ctx* c, const float* color, const float* target, i
     HIP_TRY(c, hipSetDevice(c->device));
     {
         Timed t(c, SOUP_T_LOSS, static_cast<hipStream_t>(stream));
-        launch_loss_l2(color, target, P, grad_color, grad_logp, loss, static_cast<hipStream_t>(stream));
+        launch_loss_l2(color, target, P, grad_color, grad_logp, loss, static_cast<double*>(c->sum.p), static_cast<hipStream_t>(stream));
     }
     HIP_TRY(c, hipGetLastError());
     return SOUP_OK;
@@ -1470,12 +1475,12 @@ soup_status check_loss_l1_ssim(soup_ctx* c, const float* color, const float* tar
     return SOUP_OK;
 }
 
-// The loss's launches, view by view, with the statistics record in `stats`
-// (12 floats per pixel of the largest view). Allocates nothing when `timed`
+// The loss's launches, with the statistics record in `stats` (12 floats per pixel for
+// stat_pixels pixels, at least the largest view's). Allocates nothing when `timed`
 // is false (the timing events come from a pool that may grow).
 void loss_l1_ssim_launch(soup_ctx* c, const float* color, const float* target, const soup_views* v, float lambda,
-                         float* grad_color, float* grad_logp, float* loss, int64_t P, float* stats, bool timed,
-                         hipStream_t s) {
+                         float* grad_color, float* grad_logp, float* loss, int64_t P, float* stats,
+                         int64_t stat_pixels, double* parts, bool timed, hipStream_t s) {
     // the window: normalised 1-D Gaussian, sigma 1.5, summed in double
     soup::SsimWindow win{};
     double g[2 * soup::kSsimR + 1], sum = 0.0;
@@ -1487,14 +1492,32 @@ void loss_l1_ssim_launch(soup_ctx* c, const float* color, const float* target, c
     for (int i = 0; i <= 2 * soup::kSsimR; ++i) win.g[i] = static_cast<float>(g[i] / sum);
     const float inv_n = static_cast<float>(1.0 / (3.0 * static_cast<double>(P)));
     auto run = [&]() {
-        if (loss) launch_fill_f32(loss, 1, 0.0f, s);
-        int64_t off = 0;
+        // views in order, as many per batch as the record and the kernel argument hold
+        soup::SsimBatch b{};
+        b.color = color;
+        b.target = target;
+        b.grad_color = grad_color;
+        b.grad_logp = grad_logp;
+        b.stats = stats;
+        int64_t off = 0, in_batch = 0;
         for (int i = 0; i < v->V; ++i) {
             const int64_t np = static_cast<int64_t>(v->width[i]) * v->height[i];
-            launch_loss_l1_ssim(color + off * 3, target + off * 3, v->width[i], v->height[i], lambda, inv_n, win,
-                                stats, grad_color + off * 3, grad_logp + off, loss, s);
+            if (b.n > 0 && (b.n == soup::kSsimViews || in_batch + np > stat_pixels)) {
+                launch_loss_l1_ssim(b, lambda, inv_n, win, loss, parts, s);
+                b.n = 0;
+                b.add = 1;
+                in_batch = 0;
+            }
+            b.pix[b.n] = off;
+            b.w[b.n] = v->width[i];
+            b.h[b.n] = v->height[i];
+            if (b.n == 0) b.tile[0] = 0;
+            b.tile[b.n + 1] = b.tile[b.n] + soup::ssim_tiles(v->width[i], v->height[i]);
+            ++b.n;
             off += np;
+            in_batch += np;
         }
+        launch_loss_l1_ssim(b, lambda, inv_n, win, loss, parts, s);
     };
     if (timed) {
         Timed t(c, SOUP_T_TLOSS, s);
@@ -1514,9 +1537,11 @@ soup_status soup_loss_l1_ssim(soup_ctx* c, const float* color, const float* targ
     soup_status st = check_loss_l1_ssim(c, color, target, v, lambda, grad_color, grad_logp, &P, &maxp);
     if (st != SOUP_OK) return st;
     HIP_TRY(c, hipSetDevice(c->device));
-    if ((st = ensure(c, c->ssim, static_cast<size_t>(maxp) * 12 * sizeof(float)))) return st;
+    // records for the largest view, or for as many views as 4 Mpixel hold (192 MB) where that is more
+    const int64_t stat_pixels = std::max(maxp, std::min<int64_t>(P, int64_t(1) << 22));
+    if ((st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * 12 * sizeof(float)))) return st;
     loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P, static_cast<float*>(c->ssim.p),
-                        true, static_cast<hipStream_t>(stream));
+                        stat_pixels, static_cast<double*>(c->sum.p), true, static_cast<hipStream_t>(stream));
     HIP_TRY(c, hipGetLastError());
     return SOUP_OK;
 }
@@ -1535,7 +1560,9 @@ soup_status soup_loss_l1_ssim_noalloc(soup_ctx* c, const float* color, const flo
                     kNoAllocScratchBytes >> 20, static_cast<long long>(max_pixels));
     if (!c->scratch) return fail(c, SOUP_ERR_HIP, "loss_l1_ssim_noalloc: the static scratch has no device address");
     HIP_TRY(c, hipSetDevice(c->device));
-    loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P, c->scratch, false,
+    double* parts = reinterpret_cast<double*>(c->scratch + kNoAllocScratchBytes / sizeof(float));
+    loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P, c->scratch, max_pixels,
+                        parts, false,
                         static_cast<hipStream_t>(stream));
     HIP_TRY(c, hipGetLastError());
     return SOUP_OK;

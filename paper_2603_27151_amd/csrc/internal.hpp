@@ -212,7 +212,7 @@ void launch_mlp_reduce(const float* partial, int n_rows, int n_params, double* m
                        hipStream_t s);
 int mlp_reduce_mid_rows(int n_rows);
 void launch_loss_l2(const float* color, const float* target, int64_t P, float* gc, float* gl, float* loss,
-                    hipStream_t s);
+                    double* parts, hipStream_t s);
 void launch_selftest_sigmoid(const float* x, float* y, int64_t n, hipStream_t s);
 void launch_selftest_uniform(uint64_t seed, const uint32_t* pixel, const uint32_t* tri, uint32_t view_id,
                              uint32_t step, float* u, int64_t n, hipStream_t s);
@@ -338,9 +338,26 @@ constexpr int kSsimR = 5;  // 11 x 11 window
 struct SsimWindow {
     float g[2 * kSsimR + 1];   // normalised 1-D Gaussian, sigma 1.5; the window is its outer product
 };
-void launch_loss_l1_ssim(const float* color, const float* target, int W, int H, float lam, float inv_n,
-                         const SsimWindow& win, float* stats, float* grad_color, float* grad_logp, float* loss,
-                         hipStream_t s);
+// out = (add: the value there +) parts[0..n), n <= kSumParts, added in a fixed order.
+void launch_sum_parts(const double* parts, int n, int add, float* out, hipStream_t s);
+
+// Views whose loss one pair of launches evaluates (consecutive views of a call).
+constexpr int kSsimViews = 32;
+struct SsimBatch {
+    const float* color;
+    const float* target;
+    float* grad_color;
+    float* grad_logp;
+    float* stats;                    // 12 floats per pixel of the batch
+    int64_t pix[kSsimViews];         // first pixel of each view in the caller's arrays
+    int w[kSsimViews], h[kSsimViews];
+    int tile[kSsimViews + 1];        // first tile of each view, and their number
+    int n;
+    int add;                         // 1: the loss of earlier batches is added to
+};
+int ssim_tiles(int W, int H);
+void launch_loss_l1_ssim(const SsimBatch& b, float lam, float inv_n, const SsimWindow& win, float* loss,
+                         double* parts, hipStream_t s);
 void launch_adam(float* p, const float* g, float* m, float* v, int64_t nvec, int vec, float lr, float b1, float omb1,
                  float b2, float omb2, float eps, float bc1, float bc2, hipStream_t s);
 

@@ -158,10 +158,10 @@ void launch_mlp_reduce(const float* partial, int n_rows, int n_params, double* m
 // at a time.
 __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ color, const float* __restrict__ target,
                                                       int64_t P, float* __restrict__ gc, float* __restrict__ gl,
-                                                      float* __restrict__ loss, int vec4) {
-    __shared__ float red[4];
+                                                      double* __restrict__ parts, int vec4) {
+    __shared__ double red[4];
     const float inv = 1.0f / (3.0f * static_cast<float>(P));
-    float part = 0.0f;
+    double part = 0.0;   // (a float32 sum with one atomic per workgroup was up to 2e-6 off)
     const int64_t tid = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t P4 = vec4 ? P / 4 : 0;
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ 
                 sq = __builtin_fmaf(d, d, sq);
             }
             l[k] = sq * inv;
-            part += sq * inv;
+            part += static_cast<double>(l[k]);
         }
         float4* g4 = reinterpret_cast<float4*>(gc) + 3 * q;
         g4[0] = make_float4(g[0], g[1], g[2], g[3]);
@@ -200,28 +200,51 @@ __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ 
             sq = __builtin_fmaf(d, d, sq);
         }
         gl[p] = sq * inv;
-        part += sq * inv;
+        part += static_cast<double>(sq * inv);
     }
-    if (loss) {
+    if (parts) {   // the workgroup's sum in double
+        double sum = part;
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) part += __shfl_xor(part, d, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
+        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
         __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(loss, red[0] + red[1] + red[2] + red[3]);
+        if (threadIdx.x == 0) parts[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
     }
 }
 
 void launch_loss_l2(const float* color, const float* target, int64_t P, float* gc, float* gl, float* loss,
-                    hipStream_t s) {
+                    double* parts, hipStream_t s) {
     if (P <= 0) return;
-    if (loss) launch_fill_f32(loss, 1, 0.0f, s);
     const uintptr_t al = reinterpret_cast<uintptr_t>(color) | reinterpret_cast<uintptr_t>(target) |
                          reinterpret_cast<uintptr_t>(gc) | reinterpret_cast<uintptr_t>(gl);
     const int vec4 = (al & 15) == 0 ? 1 : 0;
     int64_t g = ((vec4 ? (P + 3) / 4 : P) + 255) / 256;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(loss_l2_kernel, dim3(static_cast<unsigned>(g)), dim3(256), 0, s, color, target, P, gc, gl, loss,
-                       vec4);
+    if (g > kSumParts) g = kSumParts;
+    hipLaunchKernelGGL(loss_l2_kernel, dim3(static_cast<unsigned>(g)), dim3(256), 0, s, color, target, P, gc, gl,
+                       loss ? parts : nullptr, vec4);
+    if (loss) launch_sum_parts(parts, static_cast<int>(g), 0, loss, s);
+}
+
+// out = (add: the value there +) the parts, added in a fixed order.
+__global__ __launch_bounds__(256) void sum_parts_kernel(const double* __restrict__ parts, int n, int add,
+                                                        float* __restrict__ out) {
+    __shared__ double s_sum[4];
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSumParts / 256; ++i) {
+        const int k = i * 256 + threadIdx.x;
+        v += k < n ? parts[k] : 0.0;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *out = static_cast<float>((add ? static_cast<double>(*out) : 0.0) + ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])));
+}
+
+void launch_sum_parts(const double* parts, int n, int add, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(256), 0, s, parts, n, add, out);
 }
 
 __global__ void selftest_sigmoid_kernel(const float* __restrict__ x, float* __restrict__ y, int64_t n) {
