@@ -38,10 +38,18 @@ struct soup_ctx {
     struct FragLog {
         DevBuf frag, bary, counts;
         uint64_t region = 0, hint = 0;
+        uint64_t total = 0;          // fragments of the last eager call
         int regions = 0;
+        bool pending = false;        // the counts of the last eager raster have not been read yet
+        bool fits = false;           // ... and whether they fitted the regions
     };
     FragLog flog, rlog;              // the forward's, and that of the walk with the winners known
     DevBuf masks;                    // what is kept of a log
+    // pinned: the tile lists' length, then (total, largest) of either log, written by kernels
+    // and read after the event behind them
+    int64_t* host_res = nullptr;
+    hipEvent_t ev_total = nullptr, ev_log = nullptr;
+    bool staging_busy = false;       // an upload from host_stage may be in flight
     // the draws the forward's log was made with (valid only with bins_valid)
     bool log_valid = false;
     uint64_t log_seed = 0;
@@ -54,10 +62,11 @@ struct soup_ctx {
     std::vector<char> desc_cache;    // descriptors of the last upload (static mode reuses them)
     std::string err;
     soup_stats stats{};
-    DevBuf views, scenes, recs, tile_count, tile_fill, tile_start, bsum, entries, edge_w, partial, counters;
+    DevBuf views;        // view descriptors, then scene descriptors
+    DevBuf recs, tile_count, tile_fill, tile_start, bsum, entries, edge_w, partial, counters;
     DevBuf fwd_weights;  // every scene's MLP weights as the forward's matrix operands
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
-    DevBuf tri_count, tri_fill, tri_off, tri_bsum, mlp_mid, sorted, flags;
+    DevBuf tri_count, tri_fill, tri_off, tri_bsum, sorted, flags;
     DevBuf ssim;                                      // SSIM statistics of the training loss
     DevBuf sum;                                       // the losses' parts (one double per workgroup)
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
@@ -308,27 +317,31 @@ bool same_descriptors(const soup_ctx* c, const Plan& p) {
            memcmp(c->desc_cache.data() + vbytes, p.scenes.data(), sbytes) == 0;
 }
 
-// Upload descriptors, run setup + scan, read the list size, scatter + sort.
-soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
+// Upload descriptors, run setup + scan, scatter + sort. An eager call scatters and sorts into the
+// entries buffer in place while the host waits for the lists' length (an event behind the scan); lists
+// that need a larger buffer are made again. forward: the raster's work counters and weight operands are
+// made ready by the first launch.
+soup_status bin(soup_ctx* c, Plan& p, const Opts& o, bool forward, hipStream_t s) {
     const size_t vbytes = p.views.size() * sizeof(ViewDesc), sbytes = p.scenes.size() * sizeof(SceneDesc);
     const int chunk = bin_chunk_size(static_cast<int>(p.views.size()), p.maxT, c->num_cus);
     const int stride = bin_stride(chunk, p.n_tiles);
     soup_status st;
-    // the forward counts its regions in 32 bits (with room for the waves' last draws)
+    // the forward counts its regions in 32 bits
     if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >= (int64_t(1) << 32))
         return fail(c, SOUP_ERR_CAPACITY, "too many pixels in one call (2^32 forward regions)");
-    if ((st = ensure(c, c->views, vbytes)) || (st = ensure(c, c->scenes, sbytes)) ||
+    if ((st = ensure(c, c->views, vbytes + sbytes)) ||
         (st = ensure(c, c->recs, static_cast<size_t>(p.n_recs) * sizeof(TriRec))) ||
         (st = ensure(c, c->tile_count, static_cast<size_t>(p.n_tiles) * stride * 4)) ||
         (st = ensure(c, c->tile_fill, static_cast<size_t>(p.n_tiles) * stride * 4)) ||
-        // per-chunk tile slots exist only for the LDS-histogram chunks (a small render's
-        // one-triangle-per-thread chunks count with global atomics and need none)
+        // per-chunk tile slots exist only for the LDS-histogram chunks (small chunks count with
+        // global atomics and need none)
         (st = ensure(c, c->chunk_base,
                      chunk >= kBinChunk ? static_cast<size_t>(bin_chunks(p.maxT, chunk)) * p.n_tiles * 4 : 0)) ||
         (st = ensure(c, c->tile_start, static_cast<size_t>(p.n_tiles + 1) * 8)) ||
         (st = ensure(c, c->bsum, static_cast<size_t>((p.n_tiles + 1023) / 1024 + 1) * 8)) ||
-        (st = ensure(c, c->counters, kCountersBytes + kWorkCounters * kWorkStride * 4)) || (st = ensure(c, c->flags, 256)) ||
-        (st = ensure_host(c, vbytes + sbytes + 64)))
+        (st = ensure(c, c->counters, kCountersBytes + kWorkCounters * kWorkStride * 4)) ||
+        (st = ensure(c, c->flags, 256)) || (st = ensure_host(c, vbytes + sbytes)) ||
+        (forward && (st = ensure(c, c->fwd_weights, fwd_weights_bytes(p.kind) * p.scenes.size()))))
         return st;
     if (!c->flags_ready) {   // first allocation (never in static mode): clear the sticky flags
         launch_fill_i32(static_cast<int32_t*>(c->flags.p), 64, 0, s);
@@ -337,62 +350,76 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, hipStream_t s) {
     const bool same = same_descriptors(c, p);
     c->bins_valid = false;
     c->log_valid = false;
+    ViewDesc* const views = static_cast<ViewDesc*>(c->views.p);
+    SceneDesc* const scenes = reinterpret_cast<SceneDesc*>(static_cast<char*>(c->views.p) + vbytes);
     if (c->fixed) {
         // a captured call must not depend on host memory at replay time
         if (!same) return fail(c, SOUP_ERR_INVALID, "static mode needs the views and scenes of the previous call");
     } else {
-        // the previous call has drained this stream's use of the staging buffer
-        HIP_TRY(c, hipStreamSynchronize(s));
+        // every call that uploads waits below for an event behind the upload, so that the staging
+        // buffer is free, unless that call failed in between
+        if (c->staging_busy) HIP_TRY(c, hipDeviceSynchronize());
         char* hs = static_cast<char*>(c->host_stage);
         memcpy(hs, p.views.data(), vbytes);
         memcpy(hs + vbytes, p.scenes.data(), sbytes);
-        HIP_TRY(c, hipMemcpyAsync(c->views.p, hs, vbytes, hipMemcpyHostToDevice, s));
-        HIP_TRY(c, hipMemcpyAsync(c->scenes.p, hs + vbytes, sbytes, hipMemcpyHostToDevice, s));
         c->desc_cache.assign(hs, hs + vbytes + sbytes);
+        c->staging_busy = true;
+        HIP_TRY(c, hipMemcpyAsync(c->views.p, hs, vbytes + sbytes, hipMemcpyHostToDevice, s));
     }
-    char* hs = static_cast<char*>(c->host_stage);
     unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
+    int32_t* const count = static_cast<int32_t*>(c->tile_count.p);
+    int32_t* const fill = static_cast<int32_t*>(c->tile_fill.p);
+    int64_t* const start = static_cast<int64_t*>(c->tile_start.p);
     {
         Timed t(c, SOUP_T_FILL, s);
-        launch_zero3(reinterpret_cast<int32_t*>(cnt), 32, static_cast<int32_t*>(c->tile_count.p), p.n_tiles * stride,
-                     static_cast<int32_t*>(c->tile_fill.p), p.n_tiles * stride, s);
+        ZeroList z;
+        z.add(cnt, (kCountersBytes + kWorkCounters * kWorkStride * 4) / 4);
+        z.add(count, p.n_tiles * stride);
+        z.add(fill, p.n_tiles * stride);
+        launch_begin(z, scenes, static_cast<int>(p.scenes.size()), forward ? p.kind : MlpKind::kNone,
+                     static_cast<float*>(c->fwd_weights.p), s);
     }
     {
-    Timed t_setup(c, SOUP_T_SETUP, s);
-    launch_setup(static_cast<ViewDesc*>(c->views.p), static_cast<int>(p.views.size()), p.maxT, chunk,
-                 static_cast<SceneDesc*>(c->scenes.p), o, c->tile, static_cast<TriRec*>(c->recs.p),
-                 static_cast<int32_t*>(c->tile_count.p), static_cast<int32_t*>(c->chunk_base.p), p.n_tiles,
-                 c->counting ? cnt + 1 : nullptr, s);
+        Timed t_setup(c, SOUP_T_SETUP, s);
+        launch_setup(views, static_cast<int>(p.views.size()), p.maxT, chunk, scenes, o, c->tile,
+                     static_cast<TriRec*>(c->recs.p), count, static_cast<int32_t*>(c->chunk_base.p), p.n_tiles,
+                     c->counting ? cnt + 1 : nullptr, s);
     }
     {
         Timed t(c, SOUP_T_SCAN, s);
-        launch_scan(static_cast<int32_t*>(c->tile_count.p), p.n_tiles, stride, static_cast<int64_t*>(c->bsum.p),
-                    static_cast<int64_t*>(c->tile_start.p), s);
+        launch_scan(count, p.n_tiles, stride, static_cast<int64_t*>(c->bsum.p), start, c->fixed ? nullptr : c->host_res, s);
     }
+    auto lists = [&]() {
+        const int64_t cap = static_cast<int64_t>(c->entries.bytes / 8);
+        uint64_t* const entries = static_cast<uint64_t*>(c->entries.p);
+        {
+            Timed t(c, SOUP_T_SCATTER, s);
+            launch_scatter(views, static_cast<int>(p.views.size()), p.maxT, chunk, c->tile,
+                           static_cast<TriRec*>(c->recs.p), start, p.n_tiles, static_cast<int32_t*>(c->chunk_base.p),
+                           fill, entries, cap, s);
+        }
+        Timed t(c, SOUP_T_SORT, s);
+        launch_sort(start, p.n_tiles, entries, cap, s);
+    };
     int64_t total = -1;
     if (c->fixed) {
         // the capacity in place bounds the lists; an overflow empties them and is flagged
-        launch_clip(static_cast<int64_t*>(c->tile_start.p), p.n_tiles, static_cast<int64_t>(c->entries.bytes / 8),
+        launch_clip(start, p.n_tiles, static_cast<int64_t>(c->entries.bytes / 8),
                     reinterpret_cast<unsigned int*>(cnt + 7), static_cast<unsigned int*>(c->flags.p), s);
+        lists();
     } else {
-        int64_t* htotal = reinterpret_cast<int64_t*>(hs + vbytes + sbytes);
-        HIP_TRY(c, hipMemcpyAsync(htotal, static_cast<int64_t*>(c->tile_start.p) + p.n_tiles, 8,
-                                  hipMemcpyDeviceToHost, s));
+        HIP_TRY(c, hipEventRecord(c->ev_total, s));
+        const bool ahead = c->entries.p != nullptr;
+        if (ahead) lists();
         HIP_TRY(c, hipGetLastError());
-        HIP_TRY(c, hipStreamSynchronize(s));
-        total = *htotal;
-        if ((st = ensure(c, c->entries, static_cast<size_t>(total) * 8))) return st;
-    }
-    {
-        Timed t(c, SOUP_T_SCATTER, s);
-        launch_scatter(static_cast<ViewDesc*>(c->views.p), static_cast<int>(p.views.size()), p.maxT, chunk, c->tile,
-                       static_cast<TriRec*>(c->recs.p), static_cast<int64_t*>(c->tile_start.p), p.n_tiles,
-                       static_cast<int32_t*>(c->chunk_base.p), static_cast<int32_t*>(c->tile_fill.p),
-                       static_cast<uint64_t*>(c->entries.p), s);
-    }
-    {
-        Timed t(c, SOUP_T_SORT, s);
-        launch_sort(static_cast<int64_t*>(c->tile_start.p), p.n_tiles, static_cast<uint64_t*>(c->entries.p), s);
+        HIP_TRY(c, hipEventSynchronize(c->ev_total));
+        c->staging_busy = false;
+        total = *static_cast<volatile int64_t*>(c->host_res);
+        if (!ahead || total > static_cast<int64_t>(c->entries.bytes / 8)) {
+            if ((st = ensure(c, c->entries, static_cast<size_t>(total) * 8))) return st;
+            if (ahead) launch_fill_i32(fill, p.n_tiles * stride, 0, s);
+            lists();
+        }
     }
     HIP_TRY(c, hipGetLastError());
     c->stats.pixels = p.n_pix;
@@ -408,7 +435,8 @@ RasterArgs raster_args(soup_ctx* c, const Plan& p, const Opts& o, MlpKind kind) 
     RasterArgs a{};
     a.views = static_cast<ViewDesc*>(c->views.p);
     a.V = static_cast<int>(p.views.size());
-    a.scenes = static_cast<SceneDesc*>(c->scenes.p);
+    a.scenes = reinterpret_cast<SceneDesc*>(static_cast<char*>(c->views.p) + p.views.size() * sizeof(ViewDesc));
+    a.weights = static_cast<float*>(c->fwd_weights.p);
     a.o = o;
     a.G = p.G;
     a.recs = static_cast<TriRec*>(c->recs.p);
@@ -547,6 +575,8 @@ soup_status noalloc_scratch_setup(soup_ctx* c) {
     return SOUP_OK;
 }
 
+soup_status log_read(soup_ctx* c, soup_ctx::FragLog& g);
+
 }  // namespace
 
 extern "C" {
@@ -575,9 +605,12 @@ soup_status soup_ctx_create(soup_ctx** out, int device) {
     c->err.reserve(512);
     // the losses' parts: allocated here, so that a loss allocates nothing
     c->sum.bytes = kSumParts * sizeof(double);
-    if (noalloc_scratch_setup(c) != SOUP_OK || hipMalloc(&c->sum.p, c->sum.bytes) != hipSuccess) {
+    if (noalloc_scratch_setup(c) != SOUP_OK || hipMalloc(&c->sum.p, c->sum.bytes) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&c->host_res), 64, hipHostMallocCoherent) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_total, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_log, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
-        delete c;
+        soup_ctx_destroy(c);
         return SOUP_ERR_HIP;
     }
     *out = c;
@@ -588,14 +621,17 @@ void soup_ctx_destroy(soup_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    DevBuf* bufs[] = {&c->views,      &c->scenes,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
+    DevBuf* bufs[] = {&c->views,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
                       &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
-                      &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
+                      &c->tri_fill,   &c->tri_off,     &c->tri_bsum,     &c->sorted,      &c->flags,
                       &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
                       &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
+    if (c->host_res) (void)hipHostFree(c->host_res);
+    if (c->ev_total) (void)hipEventDestroy(c->ev_total);
+    if (c->ev_log) (void)hipEventDestroy(c->ev_log);
     for (auto& m : c->marks) {
         (void)hipEventDestroy(m.a);
         (void)hipEventDestroy(m.b);
@@ -643,6 +679,9 @@ soup_status soup_ctx_set_static(soup_ctx* c, int32_t on) {
     if (!c) return SOUP_ERR_INVALID;
     if (on && (c->counting || c->timing))
         return fail(c, SOUP_ERR_INVALID, "static mode excludes counting and timing (both synchronise)");
+    // counts that an eager call left to be read size the log's views; none is read in static mode
+    soup_status st;
+    if ((st = log_read(c, c->flog)) || (st = log_read(c, c->rlog))) return st;
     c->fixed = on != 0;
     return SOUP_OK;
 }
@@ -673,9 +712,9 @@ soup_status soup_ctx_set_counting(soup_ctx* c, int32_t on) {
 
 soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
     if (!c || !bytes) return SOUP_ERR_INVALID;
-    const DevBuf* bufs[] = {&c->views,      &c->scenes,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
+    const DevBuf* bufs[] = {&c->views,      &c->recs,      &c->tile_count, &c->tile_fill,   &c->tile_start,
                             &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
-                            &c->tri_fill,   &c->tri_off,     &c->tri_bsum,  &c->mlp_mid,    &c->sorted,      &c->flags,
+                            &c->tri_fill,   &c->tri_off,     &c->tri_bsum,     &c->sorted,      &c->flags,
                             &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
                             &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     int64_t n = 0;
@@ -690,8 +729,18 @@ soup_status soup_last_stats(const soup_ctx* c, soup_stats* out) {
     return SOUP_OK;
 }
 
-// Persistent grid of the decode kernel: 4 waves per workgroup, 4 workgroups per CU.
-int decode_blocks(soup_ctx* c) { return std::max(1, std::min(c->num_cus * 4, kMaxRegions / 4)); }
+}  // extern "C"
+
+namespace {
+
+// Persistent grid of the decode kernel, workgroups of four waves: as many as are resident
+// with the 16->32->32->4 decoder, two per CU (64 views: 2.71 ms; four 2.75, and twice the rows
+// of partial sums; three 3.35, the third waits for the first two), fewer where the
+// fragments (an upper bound; -1: unknown) give each wave less than a batch of 64.
+int decode_blocks(soup_ctx* c, int64_t fragments) {
+    const int64_t most = 2 * static_cast<int64_t>(std::max(1, c->num_cus));
+    return static_cast<int>(fragments < 0 ? most : std::max<int64_t>(1, std::min(most, (fragments + 255) / 256)));
+}
 
 // The view of a log that its readers take. A region's batches are shared by as many waves as
 // give each about eight (a wave per region where the regions are short).
@@ -730,21 +779,38 @@ soup_status log_reserve(soup_ctx* c, soup_ctx::FragLog& g, int regions, uint64_t
     return SOUP_OK;
 }
 
-// After the raster that wrote the log: an eager call reads the largest count (*ok: it fits);
-// in static mode an overflow is flagged.
-soup_status log_summary(soup_ctx* c, soup_ctx::FragLog& g, hipStream_t s, bool* ok) {
-    unsigned long long* cnt = static_cast<unsigned long long*>(c->counters.p);
-    launch_log_summary(static_cast<uint32_t*>(g.counts.p), g.regions, static_cast<uint32_t>(g.region), cnt + 4,
-                       c->fixed ? static_cast<unsigned int*>(c->flags.p) : nullptr, s);
+// After the raster that wrote the log: an eager call leaves the counts to be read behind an event; in
+// static mode an overflow is flagged.
+soup_status log_written(soup_ctx* c, soup_ctx::FragLog& g, hipStream_t s) {
+    unsigned long long* res = reinterpret_cast<unsigned long long*>(c->host_res) + (&g == &c->flog ? 2 : 4);
+    launch_log_summary(static_cast<uint32_t*>(g.counts.p), g.regions, static_cast<uint32_t>(g.region),
+                       c->fixed ? nullptr : res, c->fixed ? static_cast<unsigned int*>(c->flags.p) : nullptr, s);
     HIP_TRY(c, hipGetLastError());
-    *ok = true;
-    if (c->fixed) return SOUP_OK;
-    uint64_t* h = reinterpret_cast<uint64_t*>(c->host_stage);
-    HIP_TRY(c, hipMemcpyAsync(h, cnt + 4, 16, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
-    *ok = h[1] <= g.region;
-    g.hint = h[1];
+    g.fits = c->fixed;
+    g.pending = !c->fixed;
+    if (g.pending) HIP_TRY(c, hipEventRecord(c->ev_log, s));
     return SOUP_OK;
+}
+
+// The counts of the last eager raster that wrote the log (waits for it).
+soup_status log_read(soup_ctx* c, soup_ctx::FragLog& g) {
+    if (!g.pending) return SOUP_OK;
+    HIP_TRY(c, hipEventSynchronize(c->ev_log));
+    const volatile uint64_t* res = reinterpret_cast<uint64_t*>(c->host_res) + (&g == &c->flog ? 2 : 4);
+    g.total = res[0];
+    g.hint = res[1];
+    g.fits = g.hint <= g.region;
+    g.pending = false;
+    return SOUP_OK;
+}
+
+// Whether the forward's log is there (for these bins) and whole.
+soup_status log_usable(soup_ctx* c, bool* ok) {
+    *ok = false;
+    if (!c->log_valid) return SOUP_OK;
+    const soup_status st = log_read(c, c->flog);
+    *ok = !st && c->flog.fits;
+    return st;
 }
 
 // The log of exactly the fragments the backward (or log p: all_front) needs, from a walk with the
@@ -767,24 +833,26 @@ soup_status replay(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vi
     uint64_t region = hint ? 2 * hint + 1024 : (static_cast<uint64_t>(p.n_pix) * 3 / 2) / nr + 1024;
     for (int attempt = 0; attempt < 2; ++attempt) {
         soup_status st;
-        bool ok = false;
         if ((st = log_reserve(c, g, nr, region, a))) return st;
         {
             Timed t(c, SOUP_T_REPLAY, s);
-            launch_fwd_begin(a.scenes, 0, MlpKind::kReplay, a.work, nullptr, s);
+            launch_fill_i32(reinterpret_cast<int32_t*>(a.work), kWorkCounters * kWorkStride, 0, s);
             launch_raster_fwd(a, c->tile, MlpKind::kReplay, s);
         }
-        if ((st = log_summary(c, g, s, &ok))) return st;
-        if (ok) return SOUP_OK;
+        // the forward's counts are read before the event is recorded again
+        if ((st = log_read(c, c->flog)) || (st = log_written(c, g, s)) || (st = log_read(c, g))) return st;
+        if (g.fits) return SOUP_OK;
         region = g.hint + g.hint / 8 + 64;
     }
     return fail(c, SOUP_ERR_CAPACITY, "fragment log overflowed twice");
 }
 
 // Backward, part 1: the fragments the backward needs, from the forward's log or a walk, sorted by
-// triangle into c->sorted, with c->tri_off the triangles' ranges.
+// triangle into c->sorted, with c->tri_off the triangles' ranges. z: what else the backward needs
+// cleared before its decode.
 soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vis, const float* grad_color,
-                             const float* grad_logp, const float2* edge_w, int T, bool from_log, hipStream_t s) {
+                             const float* grad_logp, const float2* edge_w, int T, bool from_log, ZeroList& z,
+                             hipStream_t s) {
     soup_status st;
     if (p.n_pix >= (int64_t(1) << 32)) return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
     if (!from_log && (st = replay(c, p, o, vis, grad_color, grad_logp, edge_w, false, s))) return st;
@@ -800,8 +868,9 @@ soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const ui
         return st;
     {
         Timed t(c, SOUP_T_FILL, s);
-        launch_zero3(static_cast<int32_t*>(c->tri_count.p), T, static_cast<int32_t*>(c->tri_fill.p), 2 * static_cast<int64_t>(T),
-                     nullptr, 0, s);
+        z.add(c->tri_count.p, T);
+        z.add(c->tri_fill.p, 2 * static_cast<int64_t>(T));
+        launch_zero(z, s);
     }
     {
         Timed t(c, SOUP_T_REPLAY, s);
@@ -811,7 +880,7 @@ soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const ui
     {
         Timed t(c, SOUP_T_GRAD, s);
         launch_scan(static_cast<int32_t*>(c->tri_count.p), T, 1, static_cast<int64_t*>(c->tri_bsum.p),
-                    static_cast<int64_t*>(c->tri_off.p), s);
+                    static_cast<int64_t*>(c->tri_off.p), nullptr, s);
         launch_place(L, grad_logp, static_cast<ulonglong2*>(c->masks.p), static_cast<int64_t*>(c->tri_off.p),
                      static_cast<unsigned long long*>(c->tri_fill.p), static_cast<FragRec*>(c->sorted.p), s);
     }
@@ -819,39 +888,26 @@ soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const ui
     return SOUP_OK;
 }
 
-// The forward's work counter and weight operands.
-static soup_status fwd_begin(soup_ctx* c, const Plan& p, RasterArgs& a, hipStream_t s) {
-    soup_status st;
-    if ((st = ensure(c, c->fwd_weights, fwd_weights_bytes(p.kind) * p.scenes.size()))) return st;
-    a.weights = static_cast<float*>(c->fwd_weights.p);
-    launch_fwd_begin(a.scenes, static_cast<int>(p.scenes.size()), p.kind, a.work, static_cast<float*>(c->fwd_weights.p), s);
-    return SOUP_OK;
-}
-
 // The forward raster, with the log of its decoded fragments when `keep`: the
 // log is sized from the last call's largest region count (twice, so that a
-// static-mode call fits), its counts are scanned, and an eager call reads
-// whether it overflowed (an overflowing log is simply not used: the backward
-// replays).
-static soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, RasterArgs& a, bool keep,
+// static-mode call fits); whether it overflowed is read by who uses it.
+soup_status raster_forward(soup_ctx* c, const Plan& p, const Opts& o, RasterArgs& a, bool keep,
                                   hipStream_t s) {
     soup_status st;
     // twice the last call's largest count: per-wave counts vary from call to call (regions are handed
     // out dynamically), and a static-mode call (which cannot grow the log) must fit
-    if (keep && (st = log_reserve(c, c->flog, a.n_blocks, c->flog.hint ? 2 * c->flog.hint + 1024
-                                  : (static_cast<uint64_t>(p.n_pix) * 2) / a.n_blocks + 1024, a)))
+    if (keep && ((st = log_read(c, c->flog)) || (st = log_reserve(c, c->flog, a.n_blocks, c->flog.hint ? 2 * c->flog.hint + 1024
+                                  : (static_cast<uint64_t>(p.n_pix) * 2) / a.n_blocks + 1024, a))))
         return st;
-    if ((st = fwd_begin(c, p, a, s))) return st;
     {
         Timed t(c, SOUP_T_FWD, s);
         launch_raster_fwd(a, c->tile, p.kind, s);
     }
     HIP_TRY(c, hipGetLastError());
     if (keep) {
-        // an overflowing log is simply not used (the backward replays)
-        bool ok = true;
-        if ((st = log_summary(c, c->flog, s, &ok))) return st;
-        c->log_valid = ok;
+        // (an overflowing log is simply not used: the backward replays)
+        if ((st = log_written(c, c->flog, s))) return st;
+        c->log_valid = true;
         c->log_seed = o.seed;
         c->log_step = o.step;
         c->log_mode = o.mode;
@@ -870,9 +926,12 @@ DecodeArgs decode_args(soup_ctx* c, const Plan& p, const RasterArgs& a) {
     d.T = p.scenes[0].T;
     d.verts = p.scenes[0].verts;
     d.counter = a.counter;
-    d.n_blocks = decode_blocks(c);
     return d;
 }
+
+}  // namespace
+
+extern "C" {
 
 soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_views* views, const soup_opts* opts,
                                uint64_t* vis, float* color, float* logp, void* stream) {
@@ -886,7 +945,7 @@ soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_
     if (!vis || !color) return fail(c, SOUP_ERR_INVALID, "vis and color outputs are required");
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
-    if ((st = bin(c, p, o, s))) return st;
+    if ((st = bin(c, p, o, true, s))) return st;
     RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = vis;
     a.color = color;
@@ -897,7 +956,8 @@ soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_
         Timed t(c, SOUP_T_LOGP, s);
         launch_fill_f32(logp, p.n_pix, 0.0f, s);
         if (o.mode == 0) {
-            const bool from_log = keep && c->log_valid;
+            bool from_log = false;
+            if (keep && (st = log_usable(c, &from_log))) return st;
             if (!from_log && (st = replay(c, p, o, vis, nullptr, nullptr, nullptr, true, s))) return st;
             LogpArgs la{};
             la.log = log_view(from_log ? c->flog : c->rlog);
@@ -934,21 +994,15 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     if (o.reuse_bins && c->bins_valid && c->bins_tile == c->tile && c->bins_near_w == o.near_w &&
         same_descriptors(c, p)) {
         // the last forward's setup records and tile lists are those of these inputs
-        launch_fill_i32(static_cast<int32_t*>(c->counters.p), 32, 0, s);
+        if (c->counting) launch_fill_i32(static_cast<int32_t*>(c->counters.p), kCountersBytes / 4, 0, s);
         reused = true;
-    } else if ((st = bin(c, p, o, s))) {
+    } else if ((st = bin(c, p, o, false, s))) {
         return st;
     }
-    // ... and its fragment log, if it was made with these draws
-    const bool from_log = reused && c->log_valid && c->log_seed == o.seed && c->log_step == o.step &&
-                          c->log_mode == o.mode;
-    const int nb = decode_blocks(c);
-    const int rows = nb * 4;
     const int T = scene->T;
     const int64_t n_grid = static_cast<int64_t>(scene->G) * scene->G * scene->C;
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
-        (st = ensure(c, c->partial, static_cast<size_t>(rows) * p.n_params * 4)) ||
-        (st = ensure(c, c->mlp_mid, static_cast<size_t>(mlp_reduce_mid_rows(rows)) * p.n_params * 8)))
+        (st = ensure(c, c->partial, static_cast<size_t>(decode_blocks(c, -1)) * 4 * p.n_params * 4)))
         return st;
     RasterArgs a = raster_args(c, p, o, p.kind);
     const float* gl = o.mode == 0 ? grad_logp : nullptr;
@@ -958,16 +1012,21 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
         launch_edge_weights(a.views, a.V, p.n_pix, o, vis, color, grad_color, static_cast<float2*>(c->edge_w.p), s);
         ew = static_cast<float2*>(c->edge_w.p);
     }
-    if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, s))) return st;
-    {
-        Timed t(c, SOUP_T_FILL, s);
-        if (!o.accumulate) {
-            launch_fill_f32(grad_feats, static_cast<int64_t>(T) * n_grid, 0.0f, s);
-            launch_fill_f32(grad_verts, static_cast<int64_t>(T) * 9, 0.0f, s);
-        }
+    // the last forward's fragment log, if it was made with these draws
+    bool from_log = false;
+    if (reused && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode &&
+        (st = log_usable(c, &from_log)))
+        return st;
+    ZeroList z;
+    if (!o.accumulate) {
+        z.add(grad_feats, static_cast<int64_t>(T) * n_grid);
+        z.add(grad_verts, static_cast<int64_t>(T) * 9);
     }
+    if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, z, s))) return st;
+    const int nb = decode_blocks(c, c->fixed ? -1 : static_cast<int64_t>((from_log ? c->flog : c->rlog).total));
     {
         DecodeArgs d = decode_args(c, p, a);
+        d.n_blocks = nb;
         d.sorted = static_cast<FragRec*>(c->sorted.p);
         d.tri_off = static_cast<int64_t*>(c->tri_off.p);
         d.grad_color = grad_color;
@@ -982,8 +1041,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     HIP_TRY(c, hipGetLastError());
     {
         Timed t(c, SOUP_T_REDUCE, s);
-        launch_mlp_reduce(static_cast<float*>(c->partial.p), rows, p.n_params, static_cast<double*>(c->mlp_mid.p),
-                          grad_mlp, o.accumulate != 0, s);
+        launch_mlp_reduce(static_cast<float*>(c->partial.p), nb * 4, p.n_params, grad_mlp, o.accumulate != 0, s);
     }
     HIP_TRY(c, hipGetLastError());
     return finish_stats(c, s, false);
@@ -1028,11 +1086,10 @@ soup_status soup_render(soup_ctx* c, const soup_scene* scenes, int32_t R, const 
     for (int r = 0; r < R; ++r) p.views[r].color_out = color[r];
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
-    if ((st = bin(c, p, o, s))) return st;
+    if ((st = bin(c, p, o, true, s))) return st;
     RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = nullptr;
     a.color = nullptr;
-    if ((st = fwd_begin(c, p, a, s))) return st;
     {
         Timed t(c, SOUP_T_FWD, s);
         launch_raster_fwd(a, c->tile, p.kind, s);
@@ -1053,7 +1110,7 @@ soup_status soup_pforward(soup_ctx* c, const soup_pscene* scene, const soup_view
     if (!vis || !color) return fail(c, SOUP_ERR_INVALID, "vis and color outputs are required");
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
-    if ((st = bin(c, p, o, s))) return st;
+    if ((st = bin(c, p, o, true, s))) return st;
     RasterArgs a = raster_args(c, p, o, p.kind);
     a.vis = vis;
     a.color = color;
@@ -1079,9 +1136,11 @@ soup_status soup_pforward(soup_ctx* c, const soup_pscene* scene, const soup_view
         Timed t(c, SOUP_T_LOGP, s);
         launch_fill_f32(logp, p.n_pix, 0.0f, s);
         if (o.mode == 0) {
-            if (!c->log_valid && (st = replay(c, p, o, vis, nullptr, nullptr, nullptr, true, s))) return st;
+            bool from_log = false;
+            if ((st = log_usable(c, &from_log))) return st;
+            if (!from_log && (st = replay(c, p, o, vis, nullptr, nullptr, nullptr, true, s))) return st;
             PFragArgs fa{};
-            fa.log = log_view(c->log_valid ? c->flog : c->rlog);
+            fa.log = log_view(from_log ? c->flog : c->rlog);
             fa.sel = FragSelect{vis, nullptr, 1};
             fa.tex = scene->tex;
             fa.R = scene->R;
@@ -1136,13 +1195,11 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     bool reused = false;
     if (o.reuse_bins && c->bins_valid && c->bins_tile == c->tile && c->bins_near_w == o.near_w &&
         same_descriptors(c, p)) {
-        launch_fill_i32(static_cast<int32_t*>(c->counters.p), 32, 0, s);
+        if (c->counting) launch_fill_i32(static_cast<int32_t*>(c->counters.p), kCountersBytes / 4, 0, s);
         reused = true;
-    } else if ((st = bin(c, p, o, s))) {
+    } else if ((st = bin(c, p, o, false, s))) {
         return st;
     }
-    const bool from_log = reused && c->log_valid && c->log_seed == o.seed && c->log_step == o.step &&
-                          c->log_mode == o.mode;
     const int T = scene->T;
     const int64_t n_tex = static_cast<int64_t>(T) * mc_count(scene->R) * kPCh;
     // the triangle-sorted path keeps one triangle's texture gradient per wave in LDS
@@ -1161,7 +1218,6 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     const int rows = sorted_path ? nb : nb * 4;
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
         (st = ensure(c, c->partial, static_cast<size_t>(rows) * kPParams * 4)) ||
-        (st = ensure(c, c->mlp_mid, static_cast<size_t>(mlp_reduce_mid_rows(rows)) * kPParams * 8)) ||
         (st = ensure(c, c->gvert, static_cast<size_t>(T) * 9 * sizeof(double))))
         return st;
     RasterArgs a = raster_args(c, p, o, p.kind);
@@ -1171,22 +1227,24 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         launch_edge_weights(a.views, a.V, p.n_pix, o, vis, color, grad_color, static_cast<float2*>(c->edge_w.p), s);
         ew = static_cast<float2*>(c->edge_w.p);
     }
-    {
-        Timed t(c, SOUP_T_FILL, s);
-        if (fused) {
-            if (!o.accumulate)
-                for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l)
-                    launch_fill_f32(lv->graw[l], static_cast<int64_t>(T) * mc_count(lv->Rmin + l) * kPCh, 0.0f, s);
-        } else if (!o.accumulate || lv) {   // the workspace starts from zero
-            launch_fill_f32(grad_tex, n_tex, 0.0f, s);
-        }
-        launch_fill_i32(static_cast<int32_t*>(c->gvert.p), static_cast<int64_t>(T) * 18, 0, s);
+    bool from_log = false;
+    if (reused && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode &&
+        (st = log_usable(c, &from_log)))
+        return st;
+    ZeroList z;
+    z.add(c->gvert.p, static_cast<int64_t>(T) * 18);
+    if (fused) {
+        if (!o.accumulate)
+            for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l)
+                z.add(lv->graw[l], static_cast<int64_t>(T) * mc_count(lv->Rmin + l) * kPCh);
+    } else if (!o.accumulate || lv) {   // the workspace starts from zero
+        z.add(grad_tex, n_tex);
     }
     const float* gl = o.mode == 0 ? grad_logp : nullptr;
     if (sorted_path) {
         // every winner and, where the pixel carries a score weight, every fragment in
         // front of it (Eq. (9)), sorted by triangle
-        if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, s))) return st;
+        if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, z, s))) return st;
         Timed t(c, SOUP_T_BWD, s);
         PTriArgs ta{};
         ta.views = a.views;
@@ -1214,6 +1272,10 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         ta.n_blocks = nb;
         launch_ptri_bwd(ta, s);
     } else {
+        {
+            Timed t(c, SOUP_T_FILL, s);
+            launch_zero(z, s);
+        }
         if (gl) {
             // the score term (Eq. (9)): every fragment in front of a winner, and the winner
             if (p.n_pix >= (int64_t(1) << 32))
@@ -1268,8 +1330,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         Timed t(c, SOUP_T_REDUCE, s);
         launch_pvert_finish(static_cast<double*>(c->gvert.p), grad_verts, static_cast<int64_t>(T) * 9,
                             o.accumulate != 0, s);
-        launch_mlp_reduce(static_cast<float*>(c->partial.p), rows, kPParams, static_cast<double*>(c->mlp_mid.p),
-                          grad_mlp, o.accumulate != 0, s);
+        launch_mlp_reduce(static_cast<float*>(c->partial.p), rows, kPParams, grad_mlp, o.accumulate != 0, s);
     }
     HIP_TRY(c, hipGetLastError());
     return finish_stats(c, s, false);

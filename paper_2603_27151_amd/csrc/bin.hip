@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const ViewDesc* __restrict
                                                       const int64_t* __restrict__ tile_start, int64_t n_tiles,
                                                       const int32_t* __restrict__ chunk_base,
                                                       int32_t* __restrict__ tile_fill,
-                                                      uint64_t* __restrict__ entries) {
+                                                      uint64_t* __restrict__ entries, int64_t cap) {
     __shared__ unsigned long long cur[kHistBins];
     const ViewDesc& vd = views[blockIdx.y];
     const int t_beg = blockIdx.x * chunk;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const ViewDesc* __restrict
                     const int64_t g = vd.tile_base + b;
                     at = tile_start[g] + atomicAdd(&tile_fill[g], 1);
                 }
-                if (at < total) entries[at] = e;   // always true: the lists hold exactly these entries
+                if (at < cap) entries[at] = e;   // false only in lists longer than the buffer (which are made again)
             }
     }
 }
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256) void scatter_small_kernel(const ViewDesc* __re
                                                             const TriRec* __restrict__ recs,
                                                             const int64_t* __restrict__ tile_start, int64_t n_tiles,
                                                             int32_t* __restrict__ tile_fill, int stride,
-                                                            uint64_t* __restrict__ entries) {
+                                                            uint64_t* __restrict__ entries, int64_t cap) {
     __shared__ PairRuns s;
     __shared__ uint32_t zmin[256];
     const ViewDesc& vd = views[blockIdx.y];
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void scatter_small_kernel(const ViewDesc* __re
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p0 + u * 256;
-            at[u] = n_entries;
+            at[u] = cap;
             e[u] = 0;
             if (p < total) {
                 int b;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void scatter_small_kernel(const ViewDesc* __re
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (at[u] < n_entries) entries[at[u]] = e[u];   // false only past the pairs: the lists hold exactly these
+            if (at[u] < cap) entries[at[u]] = e[u];   // false past the pairs, and in lists longer than the buffer
     }
 }
 
@@ -364,10 +364,11 @@ constexpr int kWaveSortMax = 256;   // longest list sorted by one wave
 // longer lists are then sorted by the whole workgroup, bitonic in LDS, in
 // blocks of kSortBlock.
 __global__ __launch_bounds__(256) void sort_kernel(const int64_t* __restrict__ tile_start, int64_t n_tiles,
-                                                   uint64_t* __restrict__ entries) {
+                                                   uint64_t* __restrict__ entries, int64_t cap) {
     __shared__ uint64_t s[kSortBlock];
     const int w = threadIdx.x >> 6;
     const int64_t stride = gridDim.x;
+    if (tile_start[n_tiles] > cap) return;   // lists longer than the buffer are made again
     {
         const int64_t tile = blockIdx.x + w * stride;
         if (tile < n_tiles) {
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(256) void scan_bsum_kernel(int64_t* __restrict__ bs
 
 __global__ __launch_bounds__(256) void scan_apply_kernel(const int32_t* __restrict__ in, int64_t n, int stride,
                                                          const int64_t* __restrict__ bsum,
-                                                         int64_t* __restrict__ out) {
+                                                         int64_t* __restrict__ out, int64_t* __restrict__ host_total) {
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanBlock;
     int64_t vals[4];
     int64_t v = 0;
@@ -488,13 +489,17 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(const int32_t* __restri
         if (i < n) out[i] = ex;
         ex += vals[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 255) out[n] = ex;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 255) {
+        out[n] = ex;
+        store_host(host_total, ex);
+    }
 }
 
 // The same scan by one workgroup, for up to kScanOne values: four consecutive
 // values per thread and round, the rounds' totals carried along.
 constexpr int64_t kScanOne = 16384;
-__global__ __launch_bounds__(1024) void scan_one_kernel(const int32_t* __restrict__ in, int n, int stride, int64_t* __restrict__ out) {
+__global__ __launch_bounds__(1024) void scan_one_kernel(const int32_t* __restrict__ in, int n, int stride, int64_t* __restrict__ out,
+                                                        int64_t* __restrict__ host_total) {
     __shared__ int64_t wsum[16];
     const int tid = threadIdx.x, w = tid >> 6, lane = lane_id();
     int32_t v[4][4];
@@ -533,7 +538,10 @@ __global__ __launch_bounds__(1024) void scan_one_kernel(const int32_t* __restric
             x += v[r][k];
         }
     }
-    if (tid == 0) out[n] = carry;
+    if (tid == 0) {
+        out[n] = carry;
+        store_host(host_total, carry);
+    }
 }
 
 __global__ void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
@@ -542,14 +550,14 @@ __global__ void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
         p[i] = v;
 }
 
-// Three ranges cleared by one launch.
-__global__ void zero3_kernel(int32_t* __restrict__ p0, int64_t n0, int32_t* __restrict__ p1, int64_t n1,
-                             int32_t* __restrict__ p2, int64_t n2) {
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n0 + n1 + n2;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        if (i < n0) p0[i] = 0;
-        else if (i < n0 + n1) p1[i - n0] = 0;
-        else p2[i - n0 - n1] = 0;
+// Ranges cleared by one launch, in 16-byte stores where a range is aligned.
+__global__ __launch_bounds__(256) void zero_kernel(ZeroList z) {
+    const int64_t tid = blockIdx.x * static_cast<int64_t>(256) + threadIdx.x, step = static_cast<int64_t>(gridDim.x) * 256;
+    for (int r = 0; r < z.k; ++r) {
+        int32_t* p = z.p[r];
+        const int64_t n = z.n[r], n4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n / 4 : 0;
+        for (int64_t i = tid; i < n4; i += step) reinterpret_cast<int4*>(p)[i] = make_int4(0, 0, 0, 0);
+        for (int64_t i = 4 * n4 + tid; i < n; i += step) p[i] = 0;
     }
 }
 
@@ -575,9 +583,11 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
     hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(n)), dim3(256), 0, s, p, n, v);
 }
 
-void launch_zero3(int32_t* p0, int64_t n0, int32_t* p1, int64_t n1, int32_t* p2, int64_t n2, hipStream_t s) {
-    if (n0 + n1 + n2 <= 0) return;
-    hipLaunchKernelGGL(zero3_kernel, dim3(grid_for(n0 + n1 + n2)), dim3(256), 0, s, p0, n0, p1, n1, p2, n2);
+void launch_zero(const ZeroList& z, hipStream_t s) {
+    int64_t n = 0;
+    for (int r = 0; r < z.k; ++r) n += z.n[r];
+    if (n <= 0) return;
+    hipLaunchKernelGGL(zero_kernel, dim3(grid_for((n + 3) / 4)), dim3(256), 0, s, z);
 }
 
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t s) {
@@ -619,33 +629,35 @@ void launch_setup(const ViewDesc* views, int V, int maxT, int chunk, const Scene
                        chunk_base, n_tiles, visible);
 }
 
-void launch_scan(const int32_t* in, int64_t n, int stride, int64_t* bsum, int64_t* out, hipStream_t s) {
+void launch_scan(const int32_t* in, int64_t n, int stride, int64_t* bsum, int64_t* out, int64_t* host_total,
+                 hipStream_t s) {
     if (n <= 0) {   // empty input: the single offset is 0
         launch_fill_i32(reinterpret_cast<int32_t*>(out), 2, 0, s);
         return;
     }
     if (n <= kScanOne) {
-        hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, in, static_cast<int>(n), stride, out);
+        hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, in, static_cast<int>(n), stride, out, host_total);
         return;
     }
     const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
     hipLaunchKernelGGL(scan_reduce_kernel, dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, in, n, stride, bsum);
     hipLaunchKernelGGL(scan_bsum_kernel, dim3(1), dim3(256), 0, s, bsum, nb);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, in, n, stride, bsum, out);
+    hipLaunchKernelGGL(scan_apply_kernel, dim3(static_cast<unsigned>(nb)), dim3(256), 0, s, in, n, stride, bsum, out,
+                       host_total);
 }
 
 void launch_scatter(const ViewDesc* views, int V, int maxT, int chunk, int tile, const TriRec* recs,
                     const int64_t* tile_start, int64_t n_tiles, const int32_t* chunk_base, int32_t* tile_fill,
-                    uint64_t* entries, hipStream_t s) {
+                    uint64_t* entries, int64_t cap, hipStream_t s) {
     if (maxT <= 0) return;
     dim3 grid(bin_chunks(maxT, chunk), V);
     if (chunk < kBinChunk) {
         hipLaunchKernelGGL(scatter_small_kernel, grid, dim3(256), 0, s, views, tile, chunk, recs, tile_start, n_tiles,
-                           tile_fill, bin_stride(chunk, n_tiles), entries);
+                           tile_fill, bin_stride(chunk, n_tiles), entries, cap);
         return;
     }
     hipLaunchKernelGGL(scatter_kernel, grid, dim3(256), 0, s, views, tile, chunk, recs, tile_start, n_tiles,
-                       chunk_base, tile_fill, entries);
+                       chunk_base, tile_fill, entries, cap);
 }
 
 // Static-capacity mode: when the lists need more than `cap` entries, flag the
@@ -671,10 +683,10 @@ void launch_clip(int64_t* tile_start, int64_t n_tiles, int64_t cap, unsigned int
                        tile_start, n_tiles, local);
 }
 
-void launch_sort(const int64_t* tile_start, int64_t n_tiles, uint64_t* entries, hipStream_t s) {
+void launch_sort(const int64_t* tile_start, int64_t n_tiles, uint64_t* entries, int64_t cap, hipStream_t s) {
     if (n_tiles <= 0) return;
     hipLaunchKernelGGL(sort_kernel, dim3(static_cast<unsigned>((n_tiles + 3) / 4)), dim3(256), 0, s, tile_start,
-                       n_tiles, entries);
+                       n_tiles, entries, cap);
 }
 
 }  // namespace soup

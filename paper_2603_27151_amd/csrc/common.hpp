@@ -324,6 +324,12 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// A value for the host, to pinned memory that it reads after an event behind the launch (p may be null).
+template <class T>
+__device__ __forceinline__ void store_host(T* p, T v) {
+    if (p) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // A scalar sum over a launch: every workgroup leaves its part, in double, and a
 // one-workgroup launch adds them in order. (A float32 atomic per workgroup left
 // the losses up to 2e-6 off; the last workgroup to arrive adding the parts in

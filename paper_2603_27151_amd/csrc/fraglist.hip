@@ -48,8 +48,10 @@ __global__ __launch_bounds__(1024) void log_summary_kernel(const uint32_t* __res
             tot += s_tot[i];
             mx = s_max[i] > mx ? s_max[i] : mx;
         }
-        summary[0] = tot;
-        summary[1] = mx;
+        if (summary) {
+            store_host(&summary[0], tot);
+            store_host(&summary[1], static_cast<unsigned long long>(mx));
+        }
         if (sticky && mx > region) atomicOr(sticky, kOverflowFragments);
     }
 }

@@ -6,8 +6,17 @@
 namespace soup {
 
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-// Clears three ranges (any of them empty) in one launch.
-void launch_zero3(int32_t* p0, int64_t n0, int32_t* p1, int64_t n1, int32_t* p2, int64_t n2, hipStream_t s);
+// Ranges of 4-byte words that one launch clears.
+struct ZeroList {
+    int32_t* p[12];
+    int64_t n[12];
+    int k = 0;
+    void add(void* q, int64_t words) {
+        p[k] = static_cast<int32_t*>(q);
+        n[k++] = words;
+    }
+};
+void launch_zero(const ZeroList& z, hipStream_t s);
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);
 // Binning works on chunks of triangles per view. Large chunks (kBinChunk) of
 // a view with at most kHistBins tiles are counted in an LDS histogram, and
@@ -24,11 +33,14 @@ void launch_setup(const ViewDesc* views, int V, int maxT, int chunk, const Scene
                   unsigned long long* visible, hipStream_t s);
 // Distance of two tiles' counters in the count and fill arrays.
 int bin_stride(int chunk, int64_t n_tiles);
-void launch_scan(const int32_t* in, int64_t n, int stride, int64_t* bsum, int64_t* out, hipStream_t s);
+// host_total: pinned memory that receives the sum of all values, or null.
+void launch_scan(const int32_t* in, int64_t n, int stride, int64_t* bsum, int64_t* out, int64_t* host_total,
+                 hipStream_t s);
 void launch_scatter(const ViewDesc* views, int V, int maxT, int chunk, int tile, const TriRec* recs,
                     const int64_t* tile_start, int64_t n_tiles, const int32_t* chunk_base, int32_t* tile_fill,
-                    uint64_t* entries, hipStream_t s);
-void launch_sort(const int64_t* tile_start, int64_t n_tiles, uint64_t* entries, hipStream_t s);
+                    uint64_t* entries, int64_t cap, hipStream_t s);
+// entries holds cap entries: a scatter of more writes no further, and the sort of more does nothing.
+void launch_sort(const int64_t* tile_start, int64_t n_tiles, uint64_t* entries, int64_t cap, hipStream_t s);
 void launch_clip(int64_t* tile_start, int64_t n_tiles, int64_t cap, unsigned int* local, unsigned int* sticky,
                  hipStream_t s);
 
@@ -60,7 +72,7 @@ struct RasterArgs {
     unsigned long long* counter;   // counters or null: [0] decodes, [8] pixels that some fragment covers
     unsigned int* work;            // persistent-kernel work counters (zeroed by the launcher's caller)
     uint32_t fixed;                // forward: regions below it are dealt by stride (a multiple of n_blocks)
-    const float* weights;          // forward: every scene's weights as matrix operands (launch_fwd_begin), or null
+    const float* weights;          // forward: every scene's weights as matrix operands (launch_begin), or null
     int n_blocks;                  // persistent grid of the forward (single-wave workgroups)
     int region;                    // side of a forward wave's region: 16 (tiles of 16, 32) or 8
     // optional log of the decoded fragments, one region per wave (= workgroup)
@@ -77,11 +89,10 @@ struct RasterArgs {
     int replay_all;                // 1: every pixel needs its whole front set (log p)
 };
 
-// What a forward needs right before its raster: the work counters zeroed and, for the MLP shapes decoded on
-// the matrix cores, the weights of each scene in their operand order (fwd_weights_bytes per scene).
+// The first launch of a binning: clears z and, for the MLP shapes decoded on the matrix cores, lays
+// out the weights of each scene in their operand order (fwd_weights_bytes per scene; 0: none).
 size_t fwd_weights_bytes(MlpKind k);
-void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned int* work, float* weights,
-                      hipStream_t s);
+void launch_begin(const ZeroList& z, const SceneDesc* scenes, int n_scenes, MlpKind k, float* weights, hipStream_t s);
 void launch_raster_fwd(const RasterArgs& a, int tile, MlpKind k, hipStream_t s);
 // Resident single-wave workgroups per CU of the forward kernel for a tile side, MLP shape and
 // region side (16: 16x16 pixels of a tile of 16 or 32; 8: one 8x8 block).
@@ -157,6 +168,7 @@ __device__ __forceinline__ uint64_t run_of(uint64_t heads, int l) {
 #endif
 
 // Total and largest count of a log's regions; an overflow sets kOverflowFragments in *sticky (when not null).
+// summary: pinned memory that receives (total, largest), or null.
 void launch_log_summary(const uint32_t* counts, int n, uint32_t region, unsigned long long* summary,
                         unsigned int* sticky, hipStream_t s);
 // What is kept of a log, per 64 entries the masks (kept, winners), log_slots(region) per region,
@@ -208,9 +220,7 @@ size_t decode_bwd_lds(MlpKind k, int G);
 // written for covered pixels only (a background pixel occludes nothing)
 void launch_edge_weights(const ViewDesc* views, int V, int64_t P, const Opts& o, const uint64_t* vis,
                          const float* color, const float* grad_color, float2* ew, hipStream_t s);
-void launch_mlp_reduce(const float* partial, int n_rows, int n_params, double* mid, float* out, bool accumulate,
-                       hipStream_t s);
-int mlp_reduce_mid_rows(int n_rows);
+void launch_mlp_reduce(const float* partial, int n_rows, int n_params, float* out, bool accumulate, hipStream_t s);
 void launch_loss_l2(const float* color, const float* target, int64_t P, float* gc, float* gl, float* loss,
                     double* parts, hipStream_t s);
 void launch_selftest_sigmoid(const float* x, float* y, int64_t n, hipStream_t s);

@@ -78,17 +78,20 @@ size_t fwd_weights_bytes(MlpKind k) {
     }
 }
 
-void launch_fwd_begin(const SceneDesc* scenes, int n_scenes, MlpKind k, unsigned int* work, float* weights,
-                      hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>(n_scenes), 8), block(256);
+template <class S>
+static void launch_begin_s(const ZeroList& z, const SceneDesc* scenes, int n_scenes, float* weights, hipStream_t s) {
+    int64_t n = 0;
+    for (int r = 0; r < z.k; ++r) n += z.n[r];
+    const int64_t zb = n + 1023 < int64_t(4096) * 1024 ? (n + 1023) / 1024 : 4096;
+    hipLaunchKernelGGL(begin_kernel<S>, dim3(static_cast<unsigned>(zb + 8 * n_scenes)), dim3(256), 0, s, z,
+                       static_cast<int>(zb), scenes, weights);
+}
+
+void launch_begin(const ZeroList& z, const SceneDesc* scenes, int n_scenes, MlpKind k, float* weights, hipStream_t s) {
     switch (k) {
-        case MlpKind::k16_32_2:
-            hipLaunchKernelGGL((fwd_weights_kernel<MlpShape<16, 32, 2>>), grid, block, 0, s, scenes, work, weights);
-            break;
-        case MlpKind::k32_64_2:
-            hipLaunchKernelGGL((fwd_weights_kernel<MlpShape<32, 64, 2>>), grid, block, 0, s, scenes, work, weights);
-            break;
-        default: launch_fill_i32(reinterpret_cast<int32_t*>(work), kWorkCounters * kWorkStride, 0, s); break;
+        case MlpKind::k16_32_2: launch_begin_s<MlpShape<16, 32, 2>>(z, scenes, n_scenes, weights, s); break;
+        case MlpKind::k32_64_2: launch_begin_s<MlpShape<32, 64, 2>>(z, scenes, n_scenes, weights, s); break;
+        default: launch_zero(z, s); break;
     }
 }
 

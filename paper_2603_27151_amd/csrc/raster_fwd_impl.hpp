@@ -684,16 +684,24 @@ static void launch_fwd_t(const RasterArgs& a, hipStream_t s) {
 }
 
 
-// Before the raster: the work counters at zero and every scene's weights as
-// matrix operands (a column of workgroups per scene).
+// The first launch of a forward's binning: the ranges of z cleared by the first
+// zero_blocks workgroups, and every scene's weights as matrix operands by eight
+// workgroups each.
 template <class S>
-__global__ __launch_bounds__(256) void fwd_weights_kernel(const SceneDesc* __restrict__ scenes,
-                                                          unsigned int* __restrict__ work, float* __restrict__ out) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWorkCounters) work[kWorkStride * threadIdx.x] = 0u;
-    const SceneDesc& sc = scenes[blockIdx.x];
+__global__ __launch_bounds__(256) void begin_kernel(ZeroList z, int zero_blocks, const SceneDesc* __restrict__ scenes,
+                                                    float* __restrict__ out) {
+    const int b = static_cast<int>(blockIdx.x);
+    if (b < zero_blocks) {
+        for (int r = 0; r < z.k; ++r)
+            for (int64_t i = b * 256 + static_cast<int>(threadIdx.x); i < z.n[r]; i += static_cast<int64_t>(zero_blocks) * 256)
+                z.p[r][i] = 0;
+        return;
+    }
+    const int scene = (b - zero_blocks) >> 3, part = (b - zero_blocks) & 7;
+    const SceneDesc& sc = scenes[scene];
     if (sc.T <= 0) return;   // an empty scene may have no parameters, and decodes nothing
-    float* o = out + static_cast<size_t>(blockIdx.x) * FwdWeights<S>::kGroups * 4;
-    for (int i = blockIdx.y * 256 + threadIdx.x; i < FwdWeights<S>::kGroups * 4; i += gridDim.y * 256)
+    float* o = out + static_cast<size_t>(scene) * FwdWeights<S>::kGroups * 4;
+    for (int i = part * 256 + threadIdx.x; i < FwdWeights<S>::kGroups * 4; i += 2048)
         o[i] = sc.mlp[FwdWeights<S>::source(i >> 2, i & 3)];
 }
 
