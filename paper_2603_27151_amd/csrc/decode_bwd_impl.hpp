@@ -26,6 +26,18 @@
 //     triangle's G x G x C grid; when the triangle changes, the grid goes to
 //     HBM once (a plain store when the wave holds all of the triangle's
 //     fragments, float atomics for a triangle split between waves).
+//
+// What bounds it: the products themselves and the vector instructions between
+// them. A SIMD's float32 matrix and vector instructions take turns, also where
+// they come from two waves (a wave of products beside a wave of fused
+// multiply-adds took 447 us where each alone took 228 and 237), so a batch costs
+// the sum of both: the steps around the products are kept few (per-fragment
+// data through LDS instead of lane moves, ReLU in one instruction), and within
+// a block the stage of each weight gradient is written before, and read behind,
+// a data backward. 64 views of 50,000 triangles, 16-32-32-4: 2.71 -> 2.65 ms;
+// 200,000 triangles, 32-64-64-4: 8.60 -> 8.55 ms (its products alone: 5.6 ms).
+// Two blocks side by side spilled registers; the grid as a matrix product
+// (texels x fragments x channels) took 2.83 and 8.66 ms.
 #include "decode_mfma.hpp"
 
 namespace soup {
@@ -89,25 +101,30 @@ struct LayerAcc {
         }
     }
     // kStageRows (16) staged fragments: in[r][DIN] and d[r][DOUT] in LDS, rows
-    // padded by kRowPad; every step's operands are read before the first product
-    __device__ __forceinline__ void accumulate(const float* __restrict__ in, const float* __restrict__ d, int lane) {
-        constexpr int KS = kStageRows / 4;
-        const int col = lane & 15, kq = lane >> 4;
+    // padded by kRowPad. The operands of all steps are read first: their wait
+    // can then lie behind other products.
+    static constexpr int KS = kStageRows / 4;
+    struct Operands {
         float av[KS][BO], bv[KS][BI];
+    };
+    __device__ __forceinline__ static void load(Operands& o, const float* __restrict__ in, const float* __restrict__ d, int lane) {
+        const int col = lane & 15, kq = lane >> 4;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const int r = 4 * kk + kq;
 #pragma unroll
             for (int bo = 0; bo < BO; ++bo) {
                 const int m = 16 * bo + col;
-                av[kk][bo] = m < DOUT ? d[r * (DOUT + kRowPad) + m] : 0.0f;
+                o.av[kk][bo] = m < DOUT ? d[r * (DOUT + kRowPad) + m] : 0.0f;
             }
 #pragma unroll
             for (int bi = 0; bi < BI; ++bi) {
                 const int n = 16 * bi + col;
-                bv[kk][bi] = n < DIN ? in[r * (DIN + kRowPad) + n] : 0.0f;
+                o.bv[kk][bi] = n < DIN ? in[r * (DIN + kRowPad) + n] : 0.0f;
             }
         }
+    }
+    __device__ __forceinline__ void accumulate(const Operands& o) {
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
@@ -115,7 +132,7 @@ struct LayerAcc {
 #pragma unroll
                 for (int bi = 0; bi < BI; ++bi)
                     w[bo * BI + bi] =
-                        __builtin_amdgcn_mfma_f32_16x16x4f32(av[kk][bo], bv[kk][bi], w[bo * BI + bi], 0, 0, 0);
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(o.av[kk][bo], o.bv[kk][bi], w[bo * BI + bi], 0, 0, 0);
     }
     // D of a 16x16 block: lane l holds column l % 16, rows 4 (l / 16) + i
     __device__ __forceinline__ void store(float* __restrict__ row, int w_off, int b_off, int lane) const {
@@ -168,17 +185,21 @@ struct OutAcc {
         bs[0] = f4v{0.f, 0.f, 0.f, 0.f};
     }
     __device__ __forceinline__ void add_bias(const f4v (&d)[1]) { bs[0][0] += d[0][0]; }
-    __device__ __forceinline__ void accumulate(const float* __restrict__ in, const float* __restrict__ d, int lane) {
-        const int x = lane & 3, t = (lane >> 2) & 7, half = lane >> 5;
+    struct Operands {
         float av[8], bv[8];
+    };
+    __device__ __forceinline__ static void load(Operands& o, const float* __restrict__ in, const float* __restrict__ d, int lane) {
+        const int x = lane & 3, t = (lane >> 2) & 7, half = lane >> 5;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int f = 8 * half + k;
-            av[k] = d[f * (4 + kRowPad) + x];
-            bv[k] = in[f * (DIN + kRowPad) + 4 * t + x];
+            o.av[k] = d[f * (4 + kRowPad) + x];
+            o.bv[k] = in[f * (DIN + kRowPad) + 4 * t + x];
         }
+    }
+    __device__ __forceinline__ void accumulate(const Operands& o) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) w = mfma4x4(av[k], bv[k], w);
+        for (int k = 0; k < 8; ++k) w = mfma4x4(o.av[k], o.bv[k], w);
     }
     __device__ __forceinline__ void store(float* __restrict__ row, int w_off, int b_off, int lane) const {
         // lanes 0..31 (the first half) add the second half's tiles
@@ -319,55 +340,63 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         if (a.counter && lane == 0) atomicAdd(a.counter, static_cast<unsigned long long>(__popcll(on_mask)));
         float* st = s_stage[w];
         const uint32_t cellw = static_cast<uint32_t>(c.ix) | (static_cast<uint32_t>(c.iy) << 16);
-        // the fragment's triangle and winner bit, 0x7FFFFFFF for an empty lane
-        // (no triangle has that index: T is below 2^31)
-        const uint32_t fkey = on ? fa.y : 0x7FFFFFFFu;
+        // Each fragment's data for the MLP goes to its row of s_dx, which its
+        // feature gradient takes later: the lanes of its block read it back from
+        // there (moving it between lanes took five instructions per value).
+        // Triangle and winner bit are 0x7FFFFFFF for an empty lane (no triangle has
+        // that index: T is below 2^31); an empty fragment has zero weights,
+        // colour gradient and score weight, so that it adds nothing.
+        {
+            float* info = s_dx[w] + lane * DXS;
+            *reinterpret_cast<float4*>(info) =
+                make_float4(__uint_as_float(on ? fa.y : 0x7FFFFFFFu),
+                            __uint_as_float(static_cast<uint32_t>(c.iy * G + c.ix)), c.fx, c.fy);
+            *reinterpret_cast<float4*>(info + 4) = make_float4(__uint_as_float(fb4.x), __uint_as_float(fb4.y),
+                                                               __uint_as_float(fb4.z), __uint_as_float(fb4.w));
+        }
+        wave_fence();
         float my_dfx = 0.0f, my_dfy = 0.0f;   // this lane's fragment: d loss / d (fx, fy), colour logits
-        {   // ---- the batch's MLP on the matrix cores, one 16-fragment block at a time ----
+        {   // ---- the batch's MLP on the matrix cores, 16-fragment block by block ----
             constexpr int CB = MfmaWeights<S>::CB, HB = MfmaWeights<S>::HB;
             const int col = lane & 15, grp = lane >> 4;
             const MfmaWeights<S>& Wt = s_w;
-            // The four corners of block nb's texels are loaded one block ahead:
+            const float inf = opaque_inf();
+            // The four corners of the block's texels are loaded one block ahead:
             // they are in flight while the previous block runs on the matrix
             // cores. Lane (col, grp) takes channels 16 cb + 4 grp .. + 3 of
             // fragment 16 nb + col.
             float4 qv[CB][4];
-            float qw[4];
-            float qfx = 0.0f, qfy = 0.0f;   // the block fragment's position in its texture cell
+            float qfx, qfy;        // the block fragment's position in its texture cell
+            uint32_t qkey;         // its triangle and winner bit
             auto gather = [&](int nb) __attribute__((always_inline)) {
-                const uint32_t key_n = row_bcast(fkey, nb);
-                const uint32_t tri_n = key_n & 0x7FFFFFFFu;
-                const bool on_n = tri_n != 0x7FFFFFFFu;
-                const uint32_t cw = row_bcast(cellw, nb);
-                const float fx = row_bcast(c.fx, nb), fy = row_bcast(c.fy, nb);
-                qfx = fx;
-                qfy = fy;
-                // an empty lane's weights are zero, so that its input is zero
-                const float ox = on_n ? 1.0f - fx : 0.0f, oy = 1.0f - fy;
-                qw[0] = ox * oy;
-                qw[1] = on_n ? fx * oy : 0.0f;
-                qw[2] = ox * fy;
-                qw[3] = on_n ? fx * fy : 0.0f;
+                const float4 q = *reinterpret_cast<const float4*>(s_dx[w] + (16 * nb + col) * DXS);
+                qkey = __float_as_uint(q.x);
+                qfx = q.z;
+                qfy = q.w;
                 // unconditional loads (an empty lane reads texel 0 of triangle
                 // 0 and its input is zeroed), so that the wait before their use
                 // can leave the next block's loads in flight
-                const size_t t00 =
-                    on_n ? ((static_cast<size_t>(tri_n) * G + (cw >> 16)) * G + (cw & 0xFFFFu)) * S::C : 0;
+                const uint32_t tri_n = qkey & 0x7FFFFFFFu;
+                const size_t t00 = tri_n != 0x7FFFFFFFu
+                                       ? (static_cast<size_t>(tri_n) * G * G + __float_as_uint(q.y)) * S::C : 0;
                 const size_t toff[4] = {0, S::C, static_cast<size_t>(G) * S::C, static_cast<size_t>(G + 1) * S::C};
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
                     const int ch = 16 * cb + 4 * grp < S::C ? 16 * cb + 4 * grp : 0;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) qv[cb][q] = *reinterpret_cast<gfloat4*>(feats + t00 + toff[q] + ch);
+                    for (int q4 = 0; q4 < 4; ++q4) qv[cb][q4] = *reinterpret_cast<gfloat4*>(feats + t00 + toff[q4] + ch);
                 }
             };
             gather(0);
             // While a wave runs its chains of products it issues ahead of the other
-            // wave of its SIMD, whose LDS and VALU work then fills the gaps between
-            // them: priority 2 for the MLP, 1 for the grid adds, the default for the
-            // vertex chain and the record loads (decode 2.95 -> 2.91 ms).
+            // wave of its SIMD: priority 2 for the MLP, 1 for the grid adds, the
+            // default for the vertex chain and the record loads (decode 2.95 -> 2.91 ms).
             __builtin_amdgcn_s_setprio(2);
-            for (int nb = 0; nb < 4; ++nb) {   // fragment 16 nb + col (lane 16 nb + col holds its record)
+            for (int nb = 0; nb < 4; ++nb) {   // fragments 16 nb + col
+                const bool on_n = (qkey & 0x7FFFFFFFu) != 0x7FFFFFFFu, win_n = (qkey >> 31) != 0;
+                // score weight, and lane group j < 3's channel j of the colour gradient
+                const float4 g4 = *reinterpret_cast<const float4*>(s_dx[w] + (16 * nb + col) * DXS + 4);
+                const float gl_n = g4.x, gcol = grp == 0 ? g4.y : grp == 1 ? g4.z : g4.w;
                 // inputs, unit-major: channels 16 cb + 4 grp .. + 3 (an empty lane's
                 // weights are zero; channels past C enter no step of layer 0)
                 f4v xin[CB];
@@ -376,38 +405,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                 // move its texture sample (an empty lane's are multiplied by a
                 // zero feature gradient)
                 f4v tgx[CB], tgy[CB];
+                {
+                    const float fx = qfx, fy = qfy, ax = 1.0f - fy, ay = 1.0f - fx;
+                    const float qw[4] = {on_n ? ay * ax : 0.0f, on_n ? fx * ax : 0.0f, on_n ? ay * fy : 0.0f,
+                                         on_n ? fx * fy : 0.0f};
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    const float4 q00 = qv[cb][0], q10 = qv[cb][1], q01 = qv[cb][2], q11 = qv[cb][3];
-                    const float ax = 1.0f - qfy, ay = 1.0f - qfx;
-                    const float a00[4] = {q00.x, q00.y, q00.z, q00.w}, a10[4] = {q10.x, q10.y, q10.z, q10.w};
-                    const float a01[4] = {q01.x, q01.y, q01.z, q01.w}, a11[4] = {q11.x, q11.y, q11.z, q11.w};
+                    for (int cb = 0; cb < CB; ++cb) {
+                        const float4 q00 = qv[cb][0], q10 = qv[cb][1], q01 = qv[cb][2], q11 = qv[cb][3];
+                        const float a00[4] = {q00.x, q00.y, q00.z, q00.w}, a10[4] = {q10.x, q10.y, q10.z, q10.w};
+                        const float a01[4] = {q01.x, q01.y, q01.z, q01.w}, a11[4] = {q11.x, q11.y, q11.z, q11.w};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        xin[cb][i] = __builtin_fmaf(qw[3], a11[i], __builtin_fmaf(qw[2], a01[i],
-                                                    __builtin_fmaf(qw[1], a10[i], qw[0] * a00[i])));
-                        tgx[cb][i] = __builtin_fmaf(ax, a10[i] - a00[i], qfy * (a11[i] - a01[i]));
-                        tgy[cb][i] = __builtin_fmaf(ay, a01[i] - a00[i], qfx * (a11[i] - a10[i]));
+                        for (int i = 0; i < 4; ++i) {
+                            xin[cb][i] = __builtin_fmaf(qw[3], a11[i], __builtin_fmaf(qw[2], a01[i],
+                                                        __builtin_fmaf(qw[1], a10[i], qw[0] * a00[i])));
+                            tgx[cb][i] = __builtin_fmaf(ax, a10[i] - a00[i], fy * (a11[i] - a01[i]));
+                            tgy[cb][i] = __builtin_fmaf(ay, a01[i] - a00[i], fx * (a11[i] - a10[i]));
+                        }
+                        // channels in the order of the layer's steps
+                        xin[cb] = transpose_rows(xin[cb]);
                     }
                 }
-                if (nb < 3) gather(nb + 1);
-                // channels in the order of the layer's steps
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) xin[cb] = transpose_rows(xin[cb]);
+                if (nb + 1 < 4) gather(nb + 1);
                 // forward
-                f4v h0[HB];
-                mfma_layer<HB, CB, S::C>(Wt.l0, Wt.b0, xin, h0, lane);
-                f4v h1[S::NH == 2 ? HB : 1];
-                if constexpr (S::NH == 2) mfma_layer<HB, HB, S::H>(Wt.l1, Wt.b1, h0, h1, lane);
-                const f4v (&hl)[HB] = *reinterpret_cast<const f4v (*)[HB]>(S::NH == 2 ? &h1[0] : &h0[0]);
+                f4v h0[HB], h1[S::NH == 2 ? HB : 1];
+                mfma_layer<HB, CB, S::C>(Wt.l0, Wt.b0, xin, h0, lane, inf);
+                if constexpr (S::NH == 2) mfma_layer<HB, HB, S::H>(Wt.l1, Wt.b1, h0, h1, lane, inf);
+                const f4v (&hl)[HB] = *reinterpret_cast<const f4v (*)[HB]>(S::NH == 2 ? h1 : h0);
                 // output layer and the logit gradients (Eq. (9) through the sigmoid for the score term)
                 float dO;   // lane group j: output j of the fragment
-                // an empty fragment has zero colour gradient and score weight, so its dO is zero
-                const bool win_n = (row_bcast(fkey, nb) >> 31) != 0;
-                const float gl_n = row_bcast(__uint_as_float(fb4.x), nb);
                 {
                     // lane group g: outputs 0..3 summed over its own units 16 ib + 4 s + g
-                    f4v pr = {0.f, 0.f, 0.f, 0.f};
+                    f4v pr = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int ib = 0; ib < HB; ++ib) {
                         const f4v wv = Wt.lo[ib][lane];
@@ -416,103 +444,106 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                     }
                     // the four lane groups' parts summed, output g to lane group g
                     const float og = pair16f(pair32f(pr[0], pr[2]), pair32f(pr[1], pr[3])) + Wt.bo[lane];
-                    const float g0 = row_bcast(__uint_as_float(fb4.y), nb), g1 = row_bcast(__uint_as_float(fb4.z), nb),
-                                g2 = row_bcast(__uint_as_float(fb4.w), nb);
                     const float sg = sigmoid_fast(og);
-                    float d;
-                    if (grp == 3) d = win_n ? gl_n * (1.0f - sg) : -gl_n * sg;
-                    else d = win_n ? (grp == 0 ? g0 : (grp == 1 ? g1 : g2)) * sg * (1.0f - sg) : 0.0f;
-                    dO = d;
+                    const float ds = win_n ? gl_n * (1.0f - sg) : -gl_n * sg;
+                    const float dc = win_n ? gcol * sg * (1.0f - sg) : 0.0f;
+                    dO = grp == 3 ? ds : dc;
                 }
+                // The backward of the block. Every weight gradient's stage is written
+                // before, and its operands are read back behind, a data backward's
+                // products, which do not wait for it.
+                auto back = [&](auto with_split) __attribute__((always_inline)) {
+                    constexpr bool kSplit = decltype(with_split)::value;
+                    float* __restrict__ const st_h = st + kStageRows * (S::H + kRowPad);
+                    float* __restrict__ const st_c = st + kStageRows * (S::C + kRowPad);
+                    // output layer: its weight gradient's rows, and back through it: K =
+                    // the four outputs, one step (with split, the colour logits' beside it)
+                    stage_rows<HB>(st, S::H, hl, lane);
+                    st_h[col * (4 + kRowPad) + grp] = dO;
+                    f4v dl[HB], dlc[HB];
+                    const float dOc = grp == 3 ? 0.0f : dO;
+#pragma unroll
+                    for (int ob = 0; ob < HB; ++ob) {
+                        const float wl = Wt.loT[ob][lane];
+                        f4v v = mfma4(wl, dO, f4v{0.f, 0.f, 0.f, 0.f}), vc = v;
+                        if (kSplit) vc = mfma4(wl, dOc, f4v{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            v[i] = hl[ob][i] > 0.0f ? v[i] : 0.0f;
+                            vc[i] = hl[ob][i] > 0.0f ? vc[i] : 0.0f;
+                        }
+                        dl[ob] = v;
+                        dlc[ob] = vc;
+                    }
+                    wave_fence();
+                    typename OutAccOf<S>::type::Operands opo;
+                    acc.out.load(opo, st, st_h, lane);
+                    const f4v db[1] = {f4v{dO, 0.f, 0.f, 0.f}};
+                    acc.out.add_bias(db);
+                    wave_fence();
+                    f4v dh0[HB], dh0c[HB];
+                    if constexpr (S::NH == 2) {
+                        // hidden layer 1
+                        stage_rows<HB>(st, S::H, h0, lane);
+                        stage_rows<HB>(st_h, S::H, dl, lane);
+                        acc.out.accumulate(opo);
+                        acc.mid[0].add_bias(dl);
+                        wave_fence();
+                        typename LayerAcc<S::H, S::H, true>::Operands op1;
+                        acc.mid[0].load(op1, st, st_h, lane);
+                        mfma_back<HB, HB, true, kSplit>(Wt.l1T, dl, dlc, h0, dh0, dh0c, lane);
+                        acc.mid[0].accumulate(op1);
+                        wave_fence();
+                    } else {
+                        acc.out.accumulate(opo);
+#pragma unroll
+                        for (int ob = 0; ob < HB; ++ob) {
+                            dh0[ob] = dl[ob];
+                            dh0c[ob] = dlc[ob];
+                        }
+                    }
+                    // layer 0: its weight gradient, and the feature gradients into the
+                    // fragments' rows of s_dx; the winners' vertices move with those of
+                    // the colour logits alone
+                    stage_channels<CB>(st, S::C, xin, lane);
+                    stage_rows<HB>(st_c, S::H, dh0, lane);
+                    acc.l0.add_bias(dh0);
+                    wave_fence();
+                    typename LayerAcc<S::C, S::H, false>::Operands op0;
+                    acc.l0.load(op0, st, st_c, lane);
+                    f4v dxv[CB], dxc[CB];
+                    mfma_back<CB, HB, false, kSplit>(Wt.l0T, dh0, dh0c, nullptr, dxv, dxc, lane);
+                    acc.l0.accumulate(op0);
+                    wave_fence();
+                    float pfx = 0.0f, pfy = 0.0f;   // this lane's channels of d logits / d (fx, fy)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+                        const int ch = 16 * cb + 4 * grp;
+                        if (ch < S::C)
+                            *reinterpret_cast<float4*>(s_dx[w] + (16 * nb + col) * DXS + ch) =
+                                make_float4(dxv[cb][0], dxv[cb][1], dxv[cb][2], dxv[cb][3]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            pfx = __builtin_fmaf(dxc[cb][i], tgx[cb][i], pfx);
+                            pfy = __builtin_fmaf(dxc[cb][i], tgy[cb][i], pfy);
+                        }
+                    }
+                    // sum over the four lane groups' channels; lane 16 nb + col keeps
+                    // the values of its own fragment
+                    pfx = rows_sum(pfx);
+                    pfy = rows_sum(pfy);
+                    if (grp == nb) {
+                        my_dfx = pfx;
+                        my_dfy = pfy;
+                    }
+                };
                 // A winner's vertices move with the feature gradient of its colour
                 // logits only: the score logit reaches texture and MLP but no vertex
                 // (Section 3.2). Where a winner of the block carries a score weight,
                 // the colour logits get a data backward of their own; otherwise the
-                // full one below is the same thing.
-                const bool split = __ballot(win_n && gl_n != 0.0f) != 0;
-                const float dOc = grp == 3 ? 0.0f : dO;
-                float pfx = 0.0f, pfy = 0.0f;   // this lane's channels of d logits / d (fx, fy)
-                // output-layer weight gradient (rows = this block's fragments)
-                stage_rows<HB>(st, S::H, hl, lane);
-                st[kStageRows * (S::H + kRowPad) + col * (4 + kRowPad) + grp] = dO;
-                wave_fence();
-                acc.out.accumulate(st, st + kStageRows * (S::H + kRowPad), lane);
-                {
-                    const f4v db[1] = {f4v{dO, 0.f, 0.f, 0.f}};
-                    acc.out.add_bias(db);
-                }
-                wave_fence();
-                // back through the output layer: K = the four outputs, one step
-                // (with split, the colour logits' backward runs beside it)
-                f4v dl[HB], dlc[HB];
-#pragma unroll
-                for (int ob = 0; ob < HB; ++ob) {
-                    const float wl = Wt.loT[ob][lane];
-                    f4v v = mfma4(wl, dO, f4v{0.f, 0.f, 0.f, 0.f});
-                    f4v vc = split ? mfma4(wl, dOc, f4v{0.f, 0.f, 0.f, 0.f}) : f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        v[i] = hl[ob][i] > 0.0f ? v[i] : 0.0f;
-                        vc[i] = hl[ob][i] > 0.0f ? vc[i] : 0.0f;
-                    }
-                    dl[ob] = v;
-                    dlc[ob] = vc;
-                }
-                f4v dh0[HB], dh0c[HB];
-                if constexpr (S::NH == 2) {
-                    // hidden layer 1 weight gradient, then back to layer 0
-                    stage_rows<HB>(st, S::H, h0, lane);
-                    stage_rows<HB>(st + kStageRows * (S::H + kRowPad), S::H, dl, lane);
-                    wave_fence();
-                    acc.mid[0].accumulate(st, st + kStageRows * (S::H + kRowPad), lane);
-                    acc.mid[0].add_bias(dl);
-                    wave_fence();
-                    if (split) mfma_back2<HB, HB, true>(Wt.l1T, dl, dlc, h0, dh0, dh0c, lane);
-                    else mfma_back<HB, HB, true>(Wt.l1T, dl, h0, dh0, lane);
-                } else {
-#pragma unroll
-                    for (int ob = 0; ob < HB; ++ob) {
-                        dh0[ob] = dl[ob];
-                        dh0c[ob] = dlc[ob];
-                    }
-                }
-                // first-layer weight gradient
-                stage_channels<CB>(st, S::C, xin, lane);
-                stage_rows<HB>(st + kStageRows * (S::C + kRowPad), S::H, dh0, lane);
-                wave_fence();
-                acc.l0.accumulate(st, st + kStageRows * (S::C + kRowPad), lane);
-                acc.l0.add_bias(dh0);
-                wave_fence();
-                // feature gradients into the rows [fragment][C] kept past the stage's working rows;
-                // the winners' vertices move with those of the colour logits alone
-                f4v dxv[CB], dxc[CB];
-                if (split) {
-                    mfma_back2<CB, HB, false>(Wt.l0T, dh0, dh0c, nullptr, dxv, dxc, lane);
-                } else {
-                    mfma_back<CB, HB, false>(Wt.l0T, dh0, nullptr, dxv, lane);
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) dxc[cb] = dxv[cb];
-                }
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    const int ch = 16 * cb + 4 * grp;
-                    if (ch < S::C)
-                        *reinterpret_cast<float4*>(s_dx[w] + (16 * nb + col) * DXS + ch) =
-                            make_float4(dxv[cb][0], dxv[cb][1], dxv[cb][2], dxv[cb][3]);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        pfx = __builtin_fmaf(dxc[cb][i], tgx[cb][i], pfx);
-                        pfy = __builtin_fmaf(dxc[cb][i], tgy[cb][i], pfy);
-                    }
-                }
-                // sum over the four lane groups' channels; lane 16 nb + col keeps
-                // the values of its own fragment
-                pfx = rows_sum(pfx);
-                pfy = rows_sum(pfy);
-                if (grp == nb) {
-                    my_dfx = pfx;
-                    my_dfy = pfy;
-                }
+                // full one is the same thing.
+                if (__ballot(win_n && gl_n != 0.0f)) back(std::true_type{});
+                else back(std::false_type{});
             }
             wave_fence();
         }

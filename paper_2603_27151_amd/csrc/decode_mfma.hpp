@@ -86,18 +86,6 @@ __device__ __forceinline__ f4v transpose_rows(const f4v& v) {
     return f4v{__uint_as_float(e.a), __uint_as_float(o.a), __uint_as_float(e.b), __uint_as_float(o.b)};
 }
 
-// Row n of x in every row: lane (row g, column c) receives lane 16 n + c.
-// Two swaps; the first is shared by every n (the compiler merges it).
-__device__ __forceinline__ uint32_t row_bcast(uint32_t x, int n) {
-    const U2 h = swap16(x, x);                   // (x0, x0, x2, x2), (x1, x1, x3, x3)
-    const uint32_t y = (n & 1) ? h.b : h.a;
-    const U2 q = swap32(y, y);                   // (y0, y0, y0, y0), (y2, y2, y2, y2)
-    return (n & 2) ? q.b : q.a;
-}
-__device__ __forceinline__ float row_bcast(float x, int n) {
-    return __uint_as_float(row_bcast(__float_as_uint(x), n));
-}
-
 // Sum over the four rows, in every row: (x0 + x1) + (x2 + x3) per column.
 __device__ __forceinline__ float rows_sum(float x) {
     const U2 h = swap16(__float_as_uint(x), __float_as_uint(x));
@@ -247,14 +235,21 @@ struct MfmaWeights {
     }
 };
 
-// max(x, 0), +0 for NaN, as the forward's ReLU (one instruction).
-__device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, __builtin_huge_valf()); }
+// max(x, 0), +0 for NaN, as the forward's ReLU: the median of x, 0 and inf, one
+// instruction. inf comes from opaque_inf: as a constant the compiler turns the
+// median into a canonicalisation and a maximum.
+__device__ __forceinline__ float opaque_inf() {
+    float v = __builtin_huge_valf();
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ float relu(float x, float inf) { return __builtin_amdgcn_fmed3f(x, 0.0f, inf); }
 
 // One 16-fragment block: out[ob] = relu(bias + W in), IB input blocks holding
 // KIN inputs, OB output blocks.
 template <int OB, int IB, int KIN>
 __device__ __forceinline__ void mfma_layer(const f4v (*w)[IB][64], const f4v (*bias)[64], const f4v (&in)[IB],
-                                           f4v (&out)[OB], int lane) {
+                                           f4v (&out)[OB], int lane, float inf) {
 #pragma unroll
     for (int ob = 0; ob < OB; ++ob) {
         f4v acc = bias[ob][lane];
@@ -266,58 +261,37 @@ __device__ __forceinline__ void mfma_layer(const f4v (*w)[IB][64], const f4v (*b
                 if (16 * ib + 4 * s < KIN) acc = mfma4(wv[s], in[ib][s], acc);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = relu(acc[i]);
+        for (int i = 0; i < 4; ++i) acc[i] = relu(acc[i], inf);
         out[ob] = acc;
     }
 }
 
-// One 16-fragment block: d_in[ob] = (W^T d_out), masked by act > 0 when MASK.
-template <int OB, int IB, bool MASK>
-__device__ __forceinline__ void mfma_back(const f4v (*wT)[IB][64], const f4v (&d_out)[IB], const f4v* mask,
-                                          f4v (&d_in)[OB], int lane) {
+// One block: d_in[ob] = W^T d_out, masked by act > 0 when MASK. With SPLIT two data
+// backwards run side by side, d_out2 to d_in2, and a weight operand is read once.
+template <int OB, int IB, bool MASK, bool SPLIT>
+__device__ __forceinline__ void mfma_back(const f4v (*wT)[IB][64], const f4v (&d_out)[IB], const f4v (&d_out2)[IB],
+                                          const f4v* mask, f4v (&d_in)[OB], f4v (&d_in2)[OB], int lane) {
 #pragma unroll
     for (int ob = 0; ob < OB; ++ob) {
-        f4v acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib) {
-            const f4v wv = wT[ob][ib][lane];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc = mfma4(wv[s], d_out[ib][s], acc);
-        }
-        if (MASK) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = mask[ob][i] > 0.0f ? acc[i] : 0.0f;
-        }
-        d_in[ob] = acc;
-    }
-}
-
-// Two data backwards through the same layer at once (each weight operand read
-// once, two independent product chains): d_in1 = W^T d_out1, d_in2 = W^T d_out2,
-// both masked by act > 0 when MASK.
-template <int OB, int IB, bool MASK>
-__device__ __forceinline__ void mfma_back2(const f4v (*wT)[IB][64], const f4v (&d_out1)[IB], const f4v (&d_out2)[IB],
-                                           const f4v* mask, f4v (&d_in1)[OB], f4v (&d_in2)[OB], int lane) {
-#pragma unroll
-    for (int ob = 0; ob < OB; ++ob) {
-        f4v acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+        f4v acc = f4v{0.f, 0.f, 0.f, 0.f}, acc2 = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ib = 0; ib < IB; ++ib) {
             const f4v wv = wT[ob][ib][lane];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                acc1 = mfma4(wv[s], d_out1[ib][s], acc1);
-                acc2 = mfma4(wv[s], d_out2[ib][s], acc2);
+                acc = mfma4(wv[s], d_out[ib][s], acc);
+                if (SPLIT) acc2 = mfma4(wv[s], d_out2[ib][s], acc2);
             }
         }
+        if (!SPLIT) acc2 = acc;
         if (MASK) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                acc1[i] = mask[ob][i] > 0.0f ? acc1[i] : 0.0f;
+                acc[i] = mask[ob][i] > 0.0f ? acc[i] : 0.0f;
                 acc2[i] = mask[ob][i] > 0.0f ? acc2[i] : 0.0f;
             }
         }
-        d_in1[ob] = acc1;
+        d_in[ob] = acc;
         d_in2[ob] = acc2;
     }
 }

@@ -107,9 +107,9 @@ __device__ __forceinline__ f16v bias16(const f4v* __restrict__ b) {
     return d;
 }
 
-__device__ __forceinline__ void relu16(f16v& d) {
+__device__ __forceinline__ void relu16(f16v& d, float inf) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) d[r] = relu(d[r]);
+    for (int r = 0; r < 16; ++r) d[r] = relu(d[r], inf);
 }
 
 // Logits of the wave's 64 fragments (lane = fragment; every lane takes part).
@@ -123,6 +123,7 @@ __device__ __forceinline__ void mfma_logits(const FwdRegs<S>& wr, const f4v* __r
                                             int lane) {
     using FW = FwdWeights<S>;
     constexpr int NB = FW::NB;
+    const float inf = opaque_inf();
     const f4v* __restrict__ w = wg + lane;
     const f4v* __restrict__ bh = wl - FW::kWo + 4 * (lane >> 5);
     float xs[2][S::C / 2];   // per column block: inputs 2m (lanes 0..31) and 2m + 1 (lanes 32..63)
@@ -144,8 +145,8 @@ __device__ __forceinline__ void mfma_logits(const FwdRegs<S>& wr, const f4v* __r
                 d1 = mfma32(a[e], xs[1][4 * j + e], d1);
             }
         }
-        relu16(d0);
-        relu16(d1);
+        relu16(d0, inf);
+        relu16(d1, inf);
         f16v e0 = bias16(bh + FW::kB1), e1 = e0;
 #pragma unroll
         for (int j = 0; j < FW::J1; ++j) {
@@ -172,8 +173,8 @@ __device__ __forceinline__ void mfma_logits(const FwdRegs<S>& wr, const f4v* __r
                     d[1] = mfma32(a1[e], xs[cb][4 * j + e], d[1]);
                 }
             }
-            relu16(d[0]);
-            relu16(d[1]);
+            relu16(d[0], inf);
+            relu16(d[1], inf);
             f16v e0 = bias16(bh + FW::kB1), e1 = bias16(bh + FW::kB1 + 8);
 #pragma unroll
             for (int j = 0; j < FW::J1; ++j) {
@@ -192,8 +193,8 @@ __device__ __forceinline__ void mfma_logits(const FwdRegs<S>& wr, const f4v* __r
     f4v out = wl[FW::kBo - FW::kWo];
 #pragma unroll
     for (int rb = 0; rb < NB; ++rb) {
-        relu16(h2[0][rb]);
-        relu16(h2[1][rb]);
+        relu16(h2[0][rb], inf);
+        relu16(h2[1][rb], inf);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {   // units 32 rb + 4 t .. + 3
             const f4v a = wl[4 * (8 * rb + t) + (lane & 3)];
