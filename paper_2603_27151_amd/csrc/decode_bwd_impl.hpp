@@ -35,7 +35,7 @@
 // data through LDS instead of lane moves, ReLU in one instruction), and within
 // a block the stage of each weight gradient is written before, and read behind,
 // a data backward. 64 views of 50,000 triangles, 16-32-32-4: 2.71 -> 2.65 ms;
-// 200,000 triangles, 32-64-64-4: 8.60 -> 8.55 ms (its products alone: 5.6 ms).
+// 200,000 triangles, 32-64-64-4: 8.60 -> 8.33 ms (its products alone: 5.6 ms).
 // Two blocks side by side spilled registers; the grid as a matrix product
 // (texels x fragments x channels) took 2.83 and 8.66 ms.
 #include "decode_mfma.hpp"
@@ -270,6 +270,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     const int64_t f0 = static_cast<int64_t>(b_begin) * 64;
     const int64_t f1 = static_cast<int64_t>(b_end) * 64 < E ? static_cast<int64_t>(b_end) * 64 : E;
     for (int k = lane; k < n_grid + kGridTail; k += 64) grid[k] = 0.0f;
+    SharedEnds ends;
+    ends.load(a.sorted, f0, f1, E);
     // sorted list: the next batch's records, loaded one batch ahead, and the
     // per-pixel data of its winners (colour gradient, edge weights), loaded
     // once those records are in (after the current batch's MLP)
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     // the grid of triangle t goes to HBM and is cleared (whole wave)
     auto flush = [&](int t) __attribute__((always_inline)) {
         wave_fence();
-        const bool owned = a.tri_off[t] >= f0 && a.tri_off[t + 1] <= f1;
+        const bool owned = ends.owned(t);
         float* gf = a.grad_feats + static_cast<size_t>(t) * n_grid;
         for (int k = lane; k < n_grid; k += 64) {
             const float v = grid[k];
