@@ -1203,21 +1203,23 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     const int T = scene->T;
     const int64_t n_tex = static_cast<int64_t>(T) * mc_count(scene->R) * kPCh;
     // the triangle-sorted path keeps one triangle's texture gradient per wave in LDS
-    // (18 KB at R = 5); a texture too large for that takes the per-pixel path with
-    // global atomics
-    const bool sorted_path = ptri_bwd_lds(scene->R) <= 65536;
-    // levels: folded into the sorted path's flush where level R - 1 fits its stage;
-    // otherwise the texture gradient goes to a workspace and through the assembly's
-    // backward
-    const bool fused = lv && sorted_path && ptri_levels_fit(scene->R);
+    // (36 KB at R = 5, with the levels' restriction 10); a texture too large for that
+    // takes the per-pixel path with global atomics
+    const bool sorted_path = ptri_sorted(scene->R);
+    // levels: folded into the sorted path's flush; otherwise the texture gradient goes
+    // to a workspace and through the assembly's backward
+    const bool fused = lv && sorted_path;
     if (lv && !fused) {
         if ((st = ensure(c, c->gtex, static_cast<size_t>(n_tex) * sizeof(float)))) return st;
         grad_tex = static_cast<float*>(c->gtex.p);
     }
-    const int nb = sorted_path ? ptri_blocks(c->num_cus, scene->R) : pwinner_blocks(c->num_cus);
+    const int nb = sorted_path ? ptri_blocks(c->num_cus, fused, scene->R, lv ? lv->Rmin : 0, lv ? lv->Rtop : 0)
+                               : pwinner_blocks(c->num_cus);
     const int rows = sorted_path ? nb : nb * 4;
+    // the partial sums' rows do not depend on the levels (eight waves per CU at most)
+    const int most = sorted_path ? std::max(nb, 8 * c->num_cus) : rows;
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
-        (st = ensure(c, c->partial, static_cast<size_t>(rows) * kPParams * 4)) ||
+        (st = ensure(c, c->partial, static_cast<size_t>(most) * kPParams * 4)) ||
         (st = ensure(c, c->gvert, static_cast<size_t>(T) * 9 * sizeof(double))))
         return st;
     RasterArgs a = raster_args(c, p, o, p.kind);

@@ -312,8 +312,7 @@ struct PTriArgs {
     int Rmin, Rtop;
     float* graw[kPMaxLevels];
 };
-size_t ptri_bwd_lds(int R);
-bool ptri_levels_fit(int R);   // level R - 1 fits the kernel's stage buffer
+bool ptri_sorted(int R);
 
 // measured ceilings (probe.hip)
 void launch_probe_copy(const float4* src, float4* dst, int64_t n, int num_cus, hipStream_t s);
@@ -321,7 +320,7 @@ void launch_probe_read(const float4* src, int64_t n, float* partial, int64_t n_p
 void launch_probe_atomic(float* slots, int64_t n_slots, int64_t n_ops, int num_cus, hipStream_t s);
 void launch_probe_fma(float* out, int64_t n_threads, int iters, hipStream_t s);
 void launch_probe_mfma(float* out, int64_t n_threads, int iters, hipStream_t s);
-int ptri_blocks(int num_cus, int R);
+int ptri_blocks(int num_cus, bool levels, int R, int Rmin, int Rtop);
 void launch_ptri_bwd(const PTriArgs& a, hipStream_t s);
 int pwinner_blocks(int num_cus);
 void launch_pwinner_bwd(const PWinArgs& a, hipStream_t s);

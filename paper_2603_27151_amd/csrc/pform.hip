@@ -556,16 +556,10 @@ __device__ __forceinline__ void vertex_grad(const ViewDesc& vd, const TriRec& tr
 // One weight-gradient block of the wave's 64 pixels on the matrix cores:
 // D[j][c] += sum over pixels of delta[p][j] act[p][c] (v_mfma_f32_16x16x4f32,
 // K = pixels: step s of lane group grp takes pixel 16 grp + s, so that lane
-// (grp, col) reads 16 consecutive pixels of unit col from the stage), and
-// bsum += the lane's 16 values of delta unit col (the bias gradient).
-__device__ __forceinline__ void wgrad_block(float (*st)[kPIn][kPStage], const float (&act)[kPIn], const float* delta,
-                                            int nd, int lane, f4v& acc, float& bsum) {
+// (grp, col) reads 16 consecutive pixels of unit col from the stage: act in
+// st[0], delta in st[1]), and bsum += the lane's 16 values of delta unit col (the bias gradient).
+__device__ __forceinline__ void wgrad_staged(const float (*st)[kPIn][kPStage], int lane, f4v& acc, float& bsum) {
     const int col = lane & 15, grp = lane >> 4;
-#pragma unroll
-    for (int u = 0; u < kPIn; ++u) {
-        st[0][u][lane] = act[u];
-        st[1][u][lane] = u < nd ? delta[u] : 0.0f;
-    }
     wave_fence();
     float4 A4[4], B4[4];
 #pragma unroll
@@ -582,6 +576,16 @@ __device__ __forceinline__ void wgrad_block(float (*st)[kPIn][kPStage], const fl
         acc = mfma4(A4[q].w, B4[q].w, acc);
         bsum += (A4[q].x + A4[q].y) + (A4[q].z + A4[q].w);
     }
+}
+
+__device__ __forceinline__ void wgrad_block(float (*st)[kPIn][kPStage], const float (&act)[kPIn], const float* delta,
+                                            int nd, int lane, f4v& acc, float& bsum) {
+#pragma unroll
+    for (int u = 0; u < kPIn; ++u) {
+        st[0][u][lane] = act[u];
+        st[1][u][lane] = u < nd ? delta[u] : 0.0f;
+    }
+    wgrad_staged(st, lane, acc, bsum);
 }
 
 __global__ __launch_bounds__(256) void pwinner_bwd_kernel(PWinArgs a) {
@@ -787,46 +791,149 @@ void launch_pwinner_bwd(const PWinArgs& a, hipStream_t s) {
 // backward over the triangle-sorted fragment list
 // ---------------------------------------------------------------------------
 
+// The 16-16-16-3 MLP on the matrix cores, in a wave's registers: every operand
+// is one value per lane and step. Layout of the activations as in the grid
+// form's backward (element i of an f4v: unit 4 i + grp of the fragment 16 nb +
+// col), the contractions in ascending unit order, so that the hidden layers,
+// the logits and the data gradients are bit for bit those of the scalar
+// chains (dense, and sums over j ascending from 0).
+struct PMlp {
+    f4v l0, l1, lo, l1T, l0T, b0, b1;
+    float loT, bo;
+    __device__ __forceinline__ void load(const float* __restrict__ m, int lane) {
+        const int col = lane & 15, grp = lane >> 4, u = unit_of(col);
+        const bool out = (col & 3) == 0 && (col >> 2) < kPOut;   // output g is element 0 of lane group g
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = 4 * s + grp;
+            l0[s] = m[kPW0 + u * kPIn + k];
+            l1[s] = m[kPW1 + u * kPHid + k];
+            lo[s] = out ? m[kPW2 + (col >> 2) * kPHid + k] : 0.0f;
+            l1T[s] = m[kPW1 + k * kPHid + u];
+            l0T[s] = u < kPFeat ? m[kPW0 + k * kPIn + u] : 0.0f;   // the harmonics take no gradient
+            b0[s] = m[kPB0 + k];
+            b1[s] = m[kPB1 + k];
+        }
+        loT = grp < kPOut ? m[kPW2 + grp * kPHid + u] : 0.0f;
+        bo = grp < kPOut ? m[kPB2 + grp] : 0.0f;
+    }
+};
+__device__ __forceinline__ f4v pmlp_dot(const f4v& w, const f4v& x, f4v acc) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = mfma4(w[s], x[s], acc);
+    return acc;
+}
+// Element i of block nb to row 4 i + grp of a stage, the fragment's column.
+__device__ __forceinline__ void stage_units(float (*st)[kPStage], const f4v (&v)[4], int lane) {
+    const int col = lane & 15, grp = lane >> 4;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st[4 * i + grp][16 * nb + col] = v[nb][i];
+}
+
 // One wave per workgroup walks a contiguous range of the fragment list sorted
 // by triangle (every winner, and the fragments in front of it where the pixel
 // carries a score weight), 64 fragments per batch, and keeps the gradient of
-// the current triangle's texture (V x 8 floats) and its nine float64 vertex
-// sums in its LDS. Per fragment: its opacity lookup and the score term;
-// per winner also the colour path of pwinner_bwd_kernel (recompute, blend,
-// MLP data backward on the VALU, features onto the three grid vertices, the
-// float64 vertex chain with the edge term) and the MLP weight gradient on the
-// matrix cores. Adds into the row are LDS float atomics (two fragments of a
-// run may share a grid vertex). When the triangle changes, the row's nonzero
-// entries go to HBM: plain stores when the wave holds all of the triangle's
+// the current triangle's texture (V x 8) and its nine vertex sums in its LDS,
+// in float64. Per fragment: its opacity lookup and the score term; per winner
+// also the colour path of pwinner_bwd_kernel (recompute, blend, the MLP and its
+// data and weight gradients on the matrix cores, features onto the three grid
+// vertices, the float64 vertex chain with the edge term). Adds into the row
+// are LDS atomics (two fragments of a run may share a grid vertex): of
+// float64 where that fits, because an LDS add of 64 float32 takes 194 cycles
+// here, one lane after the other, and one of 64 float64 takes 10 (ptri_row64). When the triangle changes,
+// the row goes to HBM: plain stores when the wave holds all of the triangle's
 // fragments, float atomics when the triangle straddles two waves' ranges.
 //
 // LEVELS: the gradient of the learnable levels instead of the assembled
-// texture's (the assembly's backward folded in). Every add into the row is
-// multiplied by tex (1 - tex) at its grid vertex (the sigmoid's derivative;
-// the texels are the ones the fragment's lookups already read), so the row
-// holds the gradient of the level-R sum; when the triangle changes, the
-// restriction chain (the transpose of the lookups at the level-R vertices:
-// the coincident vertex with weight 1, the six lattice neighbours with 1/2)
-// runs in LDS, level R - 1 in the stage buffer (free between batches), level
-// R - 2 back in the row, and so on, and each learnable level goes out. The
+// texture's (the assembly's backward folded in). Every add is multiplied by
+// tex (1 - tex) at its grid vertex (the sigmoid's derivative; the texels are
+// the ones the fragment's lookups already read), which gives the gradient of
+// the level-R sum. The rest is the restriction chain, the transpose of the
+// lookups at the level-R vertices: the coincident coarse vertex takes weight
+// 1, the two ends of the coarse edge that a vertex halves 1/2 each. Where level R
+// itself is not learnable (it is not in the training's levels) its step is
+// taken before the add: a fragment's three vertices lie in one coarse
+// triangle, so its three corners take three sums each (corner_code), and the
+// row is level R - 1 (153 vertices instead of 561 at R = 5: 9.9 KB of LDS, two
+// waves per SIMD). When the triangle changes, the remaining steps run
+// in LDS, gathering: level L - 1 in the stage buffer (free between batches),
+// level L - 2 behind it, and so on, and each learnable level goes out. The
 // restriction is linear, so a triangle split between two waves restricts
 // each part and adds them. The seven fine-grid indices of every coarse
 // vertex are tabulated once per workgroup (a neighbour outside the grid
 // points at a zero vertex one past the level's last), so a restriction step
-// is one table read and seven 16-byte reads per (vertex, four channels).
-constexpr int kPTabMax = 153 + 45 + 15 + 6 + 1;   // coarse vertices of levels 4..0 (the sorted path has R <= 5)
-template <bool LEVELS>
-__global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
+// is one table read and seven reads per (vertex, four channels).
+//
+// What bounds it: latency at two waves per SIMD, and the waves' uneven shares (a
+// triangle costs a flush besides its fragments; with counters in the kernel the
+// longest wave took 515 us, the average one 311). Runs from four places of
+// the list per wave left the spread and cost the flushes of the triangles that
+// they cut (432 us). Four 800 x 800 views of 50,000 triangles, levels 2..4 onto
+// 5: 606 us with float32 rows of level 5 and the MLP on the vector ALUs, 381
+// now.
+constexpr int kPCoarse = 153 + 45 + 15 + 6 + 3 + 5;   // vertices of levels 4..0, each with its zero vertex
+static_assert(kPCoarse * kPCh <= 2 * kPIn * kPStage, "the coarse levels fit the stage buffer");
+
+// The level of ptri_bwd_kernel's row, and its LDS: the row (planes of one channel,
+// each with the zero vertex), then the tables of the coarser learnable levels.
+__host__ __device__ constexpr int ptri_row_level(bool levels, int R, int Rtop) { return levels && Rtop < R ? R - 1 : R; }
+// Rows of level 5 are float32: 36 KB of float64 leave three waves per CU, 18 KB
+// six (a step with the separate backward, four 800 x 800 views of 50,000 triangles:
+// 2,369 us in float64, 2,036 in float32); smaller ones do not bound the waves.
+constexpr bool ptri_row64(int Rr) { return Rr < 5; }
+static size_t ptri_lds(bool levels, int R, int Rmin, int Rtop) {
+    const int Rr = ptri_row_level(levels, R, Rtop);
+    size_t n = static_cast<size_t>(mc_count(Rr) + 1) * kPCh * (ptri_row64(Rr) ? sizeof(double) : sizeof(float));
+    if (levels)
+        for (int L = Rr - 1; L >= Rmin; --L) n += static_cast<size_t>(mc_count(L)) * sizeof(uint4);
+    return n;
+}
+
+// Weights of a micro-triangle's vertices at the corners of the level below's
+// triangle that holds it, in halves: bits 2 (3 q + k) for vertex q and corner
+// k. Corners: 0 = (I, J), or (I + 1, J + 1) in an inverted triangle, 1 =
+// (I + 1, J), 2 = (I, J + 1) with I = i / 2, J = j / 2; (pi, pj) = (i, j) & 1.
+constexpr uint32_t corner_code_of(int inv, int pi, int pj) {
+    const int vx[2][3] = {{0, 1, 0}, {1, 1, 0}}, vy[2][3] = {{0, 0, 1}, {1, 0, 1}};
+    uint32_t code = 0;
+    for (int q = 0; q < 3; ++q) {
+        const int x = pi + vx[inv][q], y = pj + vy[inv][q];   // from (2 I, 2 J)
+        const int dx = x & 1, dd = dx && (y & 1) ? 1 : 0, dy = (y & 1) && !dx ? 1 : 0;
+        for (int e = 0; e < 2; ++e) {   // the two ends (twice the same one where coincident)
+            const int I = (e ? x + dx : x - dx) / 2, J = (e ? y + dy - dd : y - dy + dd) / 2;
+            const int k = I == 1 && J == 0 ? 1 : I == 0 && J == 1 ? 2 : 0;
+            code += 1u << (2 * (3 * q + k));
+        }
+    }
+    return code;
+}
+__device__ __forceinline__ uint32_t corner_code(bool inv, int pi, int pj) {
+    const uint32_t u0 = pi ? corner_code_of(0, 1, 0) : corner_code_of(0, 0, 0);
+    const uint32_t u1 = pi ? corner_code_of(0, 1, 1) : corner_code_of(0, 0, 1);
+    const uint32_t v0 = pi ? corner_code_of(1, 1, 0) : corner_code_of(1, 0, 0);
+    const uint32_t v1 = pi ? corner_code_of(1, 1, 1) : corner_code_of(1, 0, 1);
+    return inv ? (pj ? v1 : v0) : (pj ? u1 : u0);
+}
+// the inverted coarse triangles: those of upright micro-triangles with both indices odd and of
+// inverted ones with one or both odd
+__device__ __forceinline__ bool corner_inverted(bool inv, int pi, int pj) { return inv ? (pi | pj) != 0 : (pi & pj) != 0; }
+
+template <bool LEVELS, typename Row>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ptri_bwd_kernel(PTriArgs a) {
     __shared__ __align__(16) float stage[2][kPIn][kPStage];
     __shared__ double vsum[9];
-    __shared__ uint4 s_tab[LEVELS ? kPTabMax : 1];   // per coarse vertex: centre, six neighbours (16-bit)
-    extern __shared__ __align__(16) float row[];   // [V + 1][8]: the current triangle's texture gradient, a zero vertex
+    extern __shared__ __align__(16) char s_row[];   // [8][Vr + 1] of Row, then the tables
+    Row* const row = reinterpret_cast<Row*>(s_row);
     const int lane = threadIdx.x, col = lane & 15, grp = lane >> 4;
     float (*st)[kPIn][kPStage] = stage;
-    const int R = a.R, n = 1 << R, V = mc_count(R), NR = V * kPCh;
-    if constexpr (LEVELS) {   // the restriction tables of levels R - 1 down to Rmin, in that order
+    const int R = a.R, n = 1 << R, NR = mc_count(R) * kPCh;
+    const int Rr = ptri_row_level(LEVELS, R, a.Rtop), Vr = mc_count(Rr), Vp = Vr + 1;
+    uint4* const s_tab = reinterpret_cast<uint4*>(row + kPCh * Vp);   // per coarse vertex: centre, six neighbours (16-bit)
+    if constexpr (LEVELS) {   // the restriction tables of levels Rr - 1 down to Rmin, in that order
         int off = 0;
-        for (int L = R; L > a.Rmin; --L) {
+        for (int L = Rr; L > a.Rmin; --L) {
             const int nc = 1 << (L - 1), nfl = 1 << L, Vc = mc_count(L - 1), Vfl = mc_count(L);
             for (int q = lane; q < Vc; q += 64) {
                 int I, J;
@@ -845,7 +952,9 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
             off += Vc;
         }
     }
-    cfloat* mp = as_const(a.mlp);
+    PMlp mlp;
+    mlp.load(a.mlp, lane);
+    const float inf = opaque_inf();
     gfloat* tex = as_global(a.tex);
     const int64_t E = a.tri_off[a.T];
     const int64_t nb = (E + 63) / 64;
@@ -853,114 +962,96 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
     const int64_t wid = xcd_block();
     const int64_t bbeg = nb * wid / nw, bend = nb * (wid + 1) / nw;
     const int64_t f0 = bbeg * 64, f1 = bend * 64 < E ? bend * 64 : E;
-    for (int k = lane; k < NR + kPCh; k += 64) row[k] = 0.0f;
+    for (int k = lane; k < kPCh * Vp; k += 64) row[k] = Row(0);
     if (lane < 9) vsum[lane] = 0.0;
     f4v acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
     float ab0 = 0.f, ab1 = 0.f, ab2 = 0.f;
     int cur = -1;   // triangle held in the row (wave-uniform)
-    // whether the wave holds all of the current triangle's fragments, loaded
-    // when the triangle becomes current (its flush needs it)
-    bool cur_owned = false;
-    // level L's gradient (n floats at src) out to its grid rows: plain stores
-    // when the wave owns the triangle, else atomics of the nonzero entries;
-    // two rows per lane and step, their LDS reads issued together
-    auto put = [&](float* __restrict__ g, const float* src, int nf4, bool owned) __attribute__((always_inline)) {
-        const float4* s4 = reinterpret_cast<const float4*>(src);
-        float4* g4 = reinterpret_cast<float4*>(g);
-        auto out1 = [&](int k, float4 v) __attribute__((always_inline)) {
-            if (owned) {
-                if (a.accumulate) {   // the outputs were zero-filled unless accumulating
-                    const float4 o = g4[k];
-                    v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-                }
-                g4[k] = v;
-            } else {
-                if (v.x != 0.0f) atomicAdd(&g[4 * k], v.x);
-                if (v.y != 0.0f) atomicAdd(&g[4 * k + 1], v.y);
-                if (v.z != 0.0f) atomicAdd(&g[4 * k + 2], v.z);
-                if (v.w != 0.0f) atomicAdd(&g[4 * k + 3], v.w);
+    SharedEnds ends;
+    ends.load(a.sorted, f0, f1, E);
+    // four channels of a vertex's gradient out to its grid row: a plain store when
+    // the wave owns the triangle, else atomics of the nonzero entries
+    auto put = [&](float* __restrict__ g, float4 v, bool owned) __attribute__((always_inline)) {
+        if (owned) {
+            if (a.accumulate) {   // the outputs were zero-filled unless accumulating
+                const float4 o = *reinterpret_cast<const float4*>(g);
+                v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
             }
-        };
-        int k = lane;
-        for (; k + 64 < nf4; k += 128) {
-            const float4 v0 = s4[k], v1 = s4[k + 64];
-            out1(k, v0);
-            out1(k + 64, v1);
+            *reinterpret_cast<float4*>(g) = v;
+        } else {
+            if (v.x != 0.0f) atomicAdd(g, v.x);
+            if (v.y != 0.0f) atomicAdd(g + 1, v.y);
+            if (v.z != 0.0f) atomicAdd(g + 2, v.z);
+            if (v.w != 0.0f) atomicAdd(g + 3, v.w);
         }
-        if (k < nf4) out1(k, s4[k]);
     };
-    // the row's nonzero entries go out and are cleared
+    // the row goes out and is cleared
     auto flush = [&](int t) __attribute__((always_inline)) {
         wave_fence();
-        const bool owned = cur_owned;
-        if constexpr (LEVELS) {
-            float* cur_l = row;
-            float* nxt_l = &st[0][0][0];
-            int off = 0;
-            for (int L = R;; --L) {
-                const int VL = mc_count(L);
-                if (L <= a.Rtop) put(a.graw[L - a.Rmin] + static_cast<size_t>(t) * VL * kPCh, cur_l, VL * 2, owned);
-                if (L == a.Rmin) break;
-                // level L onto level L - 1: lane per (coarse vertex, four channels); the
-                // neighbours in a fixed order, an absent one read as the zero vertex
-                const int Vc = mc_count(L - 1);
-                const float4* c4 = reinterpret_cast<const float4*>(cur_l);
-                float4* n4 = reinterpret_cast<float4*>(nxt_l);
-                auto one = [&](int e, uint4 ix) __attribute__((always_inline)) {
-                    const int h = e & 1;
-                    const float4 c = c4[(ix.x & 0xFFFFu) * 2 + h];
-                    const float4 v1 = c4[(ix.x >> 16) * 2 + h], v2 = c4[(ix.y & 0xFFFFu) * 2 + h];
-                    const float4 v3 = c4[(ix.y >> 16) * 2 + h], v4 = c4[(ix.z & 0xFFFFu) * 2 + h];
-                    const float4 v5 = c4[(ix.z >> 16) * 2 + h], v6 = c4[ix.w * 2 + h];
-                    const float4 sd = make_float4(((((v1.x + v2.x) + v3.x) + v4.x) + v5.x) + v6.x,
-                                                  ((((v1.y + v2.y) + v3.y) + v4.y) + v5.y) + v6.y,
-                                                  ((((v1.z + v2.z) + v3.z) + v4.z) + v5.z) + v6.z,
-                                                  ((((v1.w + v2.w) + v3.w) + v4.w) + v5.w) + v6.w);
-                    n4[e] = make_float4(c.x + 0.5f * sd.x, c.y + 0.5f * sd.y, c.z + 0.5f * sd.z, c.w + 0.5f * sd.w);
-                };
-                int e = lane;
-                for (; e + 64 < Vc * 2; e += 128) {   // two items per step: both table reads first
-                    const uint4 i0 = s_tab[off + (e >> 1)], i1 = s_tab[off + ((e + 64) >> 1)];
-                    one(e, i0);
-                    one(e + 64, i1);
-                }
-                if (e < Vc * 2) one(e, s_tab[off + (e >> 1)]);
-                if (lane < 2) n4[Vc * 2 + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // level L - 1's zero vertex
-                off += Vc;
-                wave_fence();
-                float* tmp = cur_l;
-                cur_l = nxt_l;
-                nxt_l = tmp;
-            }
-            float4* r4 = reinterpret_cast<float4*>(row);   // the row and its zero vertex
-            for (int k = lane; k < (NR + kPCh) / 4; k += 64) r4[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        } else {
-            float4* r4 = reinterpret_cast<float4*>(row);
-            float4* g4 = reinterpret_cast<float4*>(a.grad_tex + static_cast<size_t>(t) * NR);
-            float* g = a.grad_tex + static_cast<size_t>(t) * NR;
-            for (int k = lane; k < NR / 4; k += 64) {
-                float4 v = r4[k];
-                if (v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f) {
-                    r4[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (owned) {   // the texture gradient was zero-filled unless accumulating
-                        if (a.accumulate) {
-                            const float4 o = g4[k];
-                            v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-                        }
-                        g4[k] = v;
-                    } else {
-                        if (v.x != 0.0f) atomicAdd(&g[4 * k], v.x);
-                        if (v.y != 0.0f) atomicAdd(&g[4 * k + 1], v.y);
-                        if (v.z != 0.0f) atomicAdd(&g[4 * k + 2], v.z);
-                        if (v.w != 0.0f) atomicAdd(&g[4 * k + 3], v.w);
-                    }
-                }
+        int l = lane;   // opaque: no address of the flush is held in a register across batches
+        asm volatile("" : "+v"(l));
+        const bool owned = ends.owned(t);
+        if (!LEVELS || Rr <= a.Rtop) {
+            float* g = (LEVELS ? a.graw[Rr - a.Rmin] : a.grad_tex) + static_cast<size_t>(t) * Vr * kPCh;
+#pragma unroll 1
+            for (int e = l; e < 2 * Vr; e += 64) {
+                const Row* s = row + (e & 1) * 4 * Vp + (e >> 1);
+                const float4 v = make_float4(static_cast<float>(s[0]), static_cast<float>(s[Vp]),
+                                             static_cast<float>(s[2 * Vp]), static_cast<float>(s[3 * Vp]));
+                if (v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f) put(g + 4 * e, v, owned);
             }
         }
-        if (lane < 9) {
-            const double v = vsum[lane];
-            vsum[lane] = 0.0;
-            if (v != 0.0) atomicAdd(&a.gvert[static_cast<size_t>(t) * 9 + lane], v);
+        if constexpr (LEVELS) {
+            // a level onto the next: l per (coarse vertex, four channels), the neighbours
+            // in a fixed order, an absent one read as the zero vertex
+            const float4* src = nullptr;   // level L (null: the row)
+            float4* dst = reinterpret_cast<float4*>(&st[0][0][0]);
+            int off = 0;
+            for (int L = Rr; L > a.Rmin; --L) {
+                const int Vc = mc_count(L - 1);
+                float* const g = L - 1 <= a.Rtop ? a.graw[L - 1 - a.Rmin] + static_cast<size_t>(t) * Vc * kPCh : nullptr;
+#pragma unroll 1
+                for (int e = l; e < 2 * Vc; e += 64) {
+                    const uint4 ix = s_tab[off + (e >> 1)];
+                    const int h = e & 1;
+                    const uint32_t id[7] = {ix.x & 0xFFFFu, ix.x >> 16, ix.y & 0xFFFFu, ix.y >> 16,
+                                            ix.z & 0xFFFFu, ix.z >> 16, ix.w};
+                    float4 v;
+                    if (src == nullptr) {
+                        float o[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const Row* s = row + (4 * h + c) * Vp;
+                            const Row sd = ((((s[id[1]] + s[id[2]]) + s[id[3]]) + s[id[4]]) + s[id[5]]) + s[id[6]];
+                            o[c] = static_cast<float>(s[id[0]] + Row(0.5) * sd);
+                        }
+                        v = make_float4(o[0], o[1], o[2], o[3]);
+                    } else {
+                        float4 s[7];
+#pragma unroll
+                        for (int k = 0; k < 7; ++k) s[k] = src[2 * id[k] + h];
+                        v.x = s[0].x + 0.5f * (((((s[1].x + s[2].x) + s[3].x) + s[4].x) + s[5].x) + s[6].x);
+                        v.y = s[0].y + 0.5f * (((((s[1].y + s[2].y) + s[3].y) + s[4].y) + s[5].y) + s[6].y);
+                        v.z = s[0].z + 0.5f * (((((s[1].z + s[2].z) + s[3].z) + s[4].z) + s[5].z) + s[6].z);
+                        v.w = s[0].w + 0.5f * (((((s[1].w + s[2].w) + s[3].w) + s[4].w) + s[5].w) + s[6].w);
+                    }
+                    dst[e] = v;
+                    if (g && (v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f)) put(g + 4 * e, v, owned);
+                }
+                if (l < 2) dst[Vc * 2 + l] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // the level's zero vertex
+                off += Vc;
+                wave_fence();
+                src = dst;
+                dst += (Vc + 1) * 2;
+            }
+        }
+#pragma unroll 1
+        for (int k = l; k < kPCh * Vp * static_cast<int>(sizeof(Row)) / 16; k += 64)
+            reinterpret_cast<float4*>(s_row)[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (l < 9) {
+            const double v = vsum[l];
+            vsum[l] = 0.0;
+            if (v != 0.0) atomicAdd(&a.gvert[static_cast<size_t>(t) * 9 + l], v);
         }
         wave_fence();
     };
@@ -1053,34 +1144,32 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
         }
         const bool cpath = win && (gc[0] != 0.f || gc[1] != 0.f || gc[2] != 0.f);
         const bool vpath = cpath || (win && (ex != 0.f || ey != 0.f));
-        // the winner's setup record and vertices, for its vertex chain after the MLP
+        // the winner's setup record and vertices, for its vertex chain after the MLP:
+        // loaded before the MLP's last layer, whose products cover their latency
         TriRec tr{};
         float vx[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) vx[k] = 0.f;
-        if (vpath) {
-            tr = a.recs[a.views[v].rec_base + tri];
+        auto load_tri = [&]() __attribute__((always_inline)) {
+            if (vpath) {
+                tr = a.recs[a.views[v].rec_base + tri];
 #pragma unroll
-            for (int k = 0; k < 9; ++k) vx[k] = a.verts[static_cast<size_t>(tri) * 9 + k];
-        }
+                for (int k = 0; k < 9; ++k) vx[k] = a.verts[static_cast<size_t>(tri) * 9 + k];
+            }
+        };
         const float4(&tv)[3][2] = P.tv;
-        float in[kPIn], h1[kPHid], h2[kPHid], d1[kPHid], d2[kPHid], d3[kPOut];
         float dfeat[kPFeat];
 #pragma unroll
-        for (int u = 0; u < kPHid; ++u) {
-            in[u] = 0.f;
-            h1[u] = 0.f;
-            h2[u] = 0.f;
-            d1[u] = 0.f;
-            d2[u] = 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < kPOut; ++c) d3[c] = 0.f;
-#pragma unroll
         for (int c = 0; c < kPFeat; ++c) dfeat[c] = 0.f;
-        if (cpath) {
-            const ViewDesc& vd = a.views[v];
-            float feat[kPCh];
+        const uint64_t cp_mask = __ballot(cpath);
+        if (cp_mask) {
+            // The batch's MLP on the matrix cores, 16 fragments per block, the four
+            // blocks' chains side by side (fragments without a colour path: zeros).
+            // Between a fragment's own lane and its block's lanes the values go
+            // through the stage.
+            float feat[kPCh], in[kPIn];
+#pragma unroll
+            for (int u = 0; u < kPIn; ++u) in[u] = 0.f;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {   // the texels' interpolation, as fetch_texel
                 feat[4 * h + 0] = mc_mix(m, tv[0][h].x, tv[1][h].x, tv[2][h].x);
@@ -1088,66 +1177,165 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
                 feat[4 * h + 2] = mc_mix(m, tv[0][h].z, tv[1][h].z, tv[2][h].z);
                 feat[4 * h + 3] = mc_mix(m, tv[0][h].w, tv[1][h].w, tv[2][h].w);
             }
+            if (cpath) {
+                const ViewDesc& vd = a.views[v];
 #pragma unroll
-            for (int c = 0; c < kPFeat; ++c) in[c] = feat[c];
-            float d[3];
-            view_dir(vd.Mi, vd.W, vd.H, x, y, d);
-            sh2(d, in + kPFeat);
-            float o[kPOut];
-            dense<kPIn, kPHid, true>(mp + kPW0, mp + kPB0, in, h1);
-            dense<kPHid, kPHid, true>(mp + kPW1, mp + kPB1, h1, h2);
-            dense<kPHid, kPOut, false>(mp + kPW2, mp + kPB2, h2, o);
-            const float A = feat[3];
-            float dA = 0.f;
-#pragma unroll
-            for (int c = 0; c < kPOut; ++c) {
-                const float mm = sigmoid_c(o[c]);
-                dfeat[c] = A * gc[c];
-                dA = __builtin_fmaf(gc[c], feat[c] - mm, dA);
-                d3[c] = (1.0f - A) * gc[c] * (mm * (1.0f - mm));
-            }
-            dfeat[3] = dA;
-#pragma unroll
-            for (int u = 0; u < kPHid; ++u) {
-                float sacc = 0.f;
-#pragma unroll
-                for (int c = 0; c < kPOut; ++c) sacc = __builtin_fmaf(mp[kPW2 + c * kPHid + u], d3[c], sacc);
-                d2[u] = h2[u] > 0.f ? sacc : 0.f;
+                for (int c = 0; c < kPFeat; ++c) in[c] = feat[c];
+                float d[3];
+                view_dir(vd.Mi, vd.W, vd.H, x, y, d);
+                sh2(d, in + kPFeat);
             }
 #pragma unroll
-            for (int u = 0; u < kPHid; ++u) {
-                float sacc = 0.f;
+            for (int u = 0; u < kPIn; ++u) st[0][u][lane] = in[u];
+            wave_fence();
+            f4v xin[4], h1[4], h2[4];
 #pragma unroll
-                for (int j = 0; j < kPHid; ++j) sacc = __builtin_fmaf(mp[kPW1 + j * kPHid + u], d2[j], sacc);
-                d1[u] = h1[u] > 0.f ? sacc : 0.f;
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) xin[nb][s] = st[0][4 * s + grp][16 * nb + col];
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                h1[nb] = pmlp_dot(mlp.l0, xin[nb], mlp.b0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h1[nb][i] = relu(h1[nb][i], inf);
             }
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                h2[nb] = pmlp_dot(mlp.l1, h1[nb], mlp.b1);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h2[nb][i] = relu(h2[nb][i], inf);
+            }
+            // the sigmoid of output g in lane group g, to the fragment's lane
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const f4v o = pmlp_dot(mlp.lo, h2[nb], f4v{mlp.bo, 0.f, 0.f, 0.f});
+                st[1][grp][16 * nb + col] = sigmoid_c(o[0]);
+                // zeros where the fragment has no colour path: they take no part below
+                const bool cp = (cp_mask >> (16 * nb + col)) & 1u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    h1[nb][i] = cp ? h1[nb][i] : 0.0f;
+                    h2[nb][i] = cp ? h2[nb][i] : 0.0f;
+                }
+            }
+            wave_fence();
+            float d3[kPOut];
+            {
+                const float A = feat[3];
+                float dA = 0.f;
+#pragma unroll
+                for (int c = 0; c < kPOut; ++c) {
+                    const float mm = st[1][c][lane];
+                    dfeat[c] = cpath ? A * gc[c] : 0.0f;
+                    dA = __builtin_fmaf(gc[c], feat[c] - mm, dA);
+                    d3[c] = cpath ? (1.0f - A) * gc[c] * (mm * (1.0f - mm)) : 0.0f;
+                }
+                dfeat[3] = cpath ? dA : 0.0f;
+            }
+            wave_fence();
+            // layer 2: the deltas' rows past kPOut hold what was there, and so do rows
+            // of the product that nothing reads
+#pragma unroll
+            for (int c = 0; c < kPOut; ++c) st[1][c][lane] = d3[c];
+            stage_units(st[0], h2, lane);
+            wave_fence();
+            f4v dl[4];
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const float dO = grp < kPOut ? st[1][grp][16 * nb + col] : 0.0f;
+                dl[nb] = mfma4(mlp.loT, dO, f4v{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dl[nb][i] = h2[nb][i] > 0.0f ? dl[nb][i] : 0.0f;
+            }
+            wgrad_staged(st, lane, acc2, ab2);
+            // layer 1
+            stage_units(st[0], h1, lane);
+            stage_units(st[1], dl, lane);
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                f4v d = pmlp_dot(mlp.l1T, dl[nb], f4v{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[i] = h1[nb][i] > 0.0f ? d[i] : 0.0f;
+                dl[nb] = d;
+            }
+            wgrad_staged(st, lane, acc1, ab1);
+            // layer 0
+            stage_units(st[0], xin, lane);
+            stage_units(st[1], dl, lane);
+            f4v dx[4];
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) dx[nb] = pmlp_dot(mlp.l0T, dl[nb], f4v{0.f, 0.f, 0.f, 0.f});
+            wgrad_staged(st, lane, acc0, ab0);
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                st[0][grp][16 * nb + col] = dx[nb][0];
+                st[0][4 + grp][16 * nb + col] = dx[nb][1];
+            }
+            wave_fence();
+#pragma unroll
+            for (int c = 0; c < kPFeat; ++c) dfeat[c] += cpath ? st[0][c][lane] : 0.0f;
+            wave_fence();
+        }
+        load_tri();
+        // along (b1, b2)
+        float dfu = 0.f, dfv = 0.f;
+        if (cpath) {
 #pragma unroll
             for (int c = 0; c < kPFeat; ++c) {
-                float sacc = 0.f;
-#pragma unroll
-                for (int j = 0; j < kPHid; ++j) sacc = __builtin_fmaf(mp[kPW0 + j * kPIn + c], d1[j], sacc);
-                dfeat[c] += sacc;
+                const float t0 = c < 4 ? (&tv[0][0].x)[c] : (&tv[0][1].x)[c - 4];
+                const float t1 = c < 4 ? (&tv[1][0].x)[c] : (&tv[1][1].x)[c - 4];
+                const float t2 = c < 4 ? (&tv[2][0].x)[c] : (&tv[2][1].x)[c - 4];
+                dfu = __builtin_fmaf(dfeat[c], m.inv ? t0 - t2 : t1 - t0, dfu);
+                dfv = __builtin_fmaf(dfeat[c], m.inv ? t0 - t1 : t2 - t0, dfv);
             }
         }
-        if (__ballot(cpath)) {
-            wgrad_block(st, in, d1, kPHid, lane, acc0, ab0);
-            wgrad_block(st, h1, d2, kPHid, lane, acc1, ab1);
-            wgrad_block(st, h2, d3, kPOut, lane, acc2, ab2);
+        // What the fragment adds to its three grid vertices, zero where it has no
+        // weight or no gradient (LEVELS: times the sigmoid's derivative at the
+        // grid vertex). Branches, products and float32 adds in the runs' loop took
+        // 3,900 cycles per run of 23 fragments, the float64 adds alone 1,850.
+        float add[3][kPCh];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bool wq = m.w[q] != 0.0f;
+#pragma unroll
+            for (int c = 0; c < kPCh; ++c) {
+                const float tq = c == kPCh - 1 ? s7[q] : c < 4 ? (&tv[q][0].x)[c] : (&tv[q][1].x)[c - 4];
+                const float wc = LEVELS ? m.w[q] * (tq * (1.0f - tq)) : m.w[q];
+                const float g = c == kPCh - 1 ? da : dfeat[c];
+                add[q][c] = wq && g != 0.0f ? wc * g : 0.0f;
+            }
+        }
+        int vtx[3];
+        if (LEVELS && Rr < R) {   // onto the corners of the coarse triangle
+            const int pi = m.i & 1, pj = m.j & 1, I = m.i >> 1, J = m.j >> 1;
+            const uint32_t code = corner_code(m.inv, pi, pj);
+            const int r0 = mc_index(n >> 1, I, J), r1 = mc_index(n >> 1, I, J + 1);
+            vtx[0] = corner_inverted(m.inv, pi, pj) ? r1 + 1 : r0;
+            vtx[1] = r0 + 1;
+            vtx[2] = r1;
+            // 0, 1/2 or 1 (zero also times an infinity)
+            float f[3][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) f[q][k] = 0.5f * static_cast<float>((code >> (2 * (3 * q + k))) & 3u);
+#pragma unroll
+            for (int c = 0; c < kPCh; ++c) {
+                float o[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    o[k] = ((f[0][k] != 0.0f ? f[0][k] * add[0][c] : 0.0f) + (f[1][k] != 0.0f ? f[1][k] * add[1][c] : 0.0f)) +
+                           (f[2][k] != 0.0f ? f[2][k] * add[2][c] : 0.0f);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) add[k][c] = o[k];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) vtx[q] = m.idx[q];
         }
         // --- the winner's vertex gradient (colour path and edge term), float64 ---
         double gw[9] = {0., 0., 0., 0., 0., 0., 0., 0., 0.};
         if (vpath) {
-            float dfu = 0.f, dfv = 0.f;
-            if (cpath) {
-#pragma unroll
-                for (int c = 0; c < kPFeat; ++c) {
-                    const float t0 = c < 4 ? (&tv[0][0].x)[c] : (&tv[0][1].x)[c - 4];
-                    const float t1 = c < 4 ? (&tv[1][0].x)[c] : (&tv[1][1].x)[c - 4];
-                    const float t2 = c < 4 ? (&tv[2][0].x)[c] : (&tv[2][1].x)[c - 4];
-                    dfu = __builtin_fmaf(dfeat[c], m.inv ? t0 - t2 : t1 - t0, dfu);
-                    dfv = __builtin_fmaf(dfeat[c], m.inv ? t0 - t1 : t2 - t0, dfv);
-                }
-            }
             const ViewDesc& vd = a.views[v];
             float pb1, pb2;
             double E3[3];
@@ -1168,27 +1356,18 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
             if (t != cur) {
                 if (cur >= 0) flush(cur);
                 cur = t;
-                cur_owned = a.tri_off[t] >= f0 && a.tri_off[t + 1] <= f1;
             }
             const int end = heads ? __builtin_ctzll(heads) : 64;
             const bool in_run = lane >= h && lane < end;
-            if (in_run) {
+            if (in_run && da != 0.0f) {
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    if (m.w[q] == 0.0f) continue;
-                    float* rv = row + m.idx[q] * kPCh;
-                    // LEVELS: times the sigmoid's derivative at the grid vertex
-                    const float w7 = LEVELS ? m.w[q] * (s7[q] * (1.0f - s7[q])) : m.w[q];
-                    if (da != 0.0f) atomicAdd(rv + (kPCh - 1), w7 * da);
-                    if (cpath) {
+                for (int q = 0; q < 3; ++q) atomicAdd(row + (kPCh - 1) * Vp + vtx[q], static_cast<Row>(add[q][kPCh - 1]));
+            }
+            if (in_run && cpath) {
 #pragma unroll
-                        for (int c = 0; c < kPFeat; ++c) {
-                            const float tq = c < 4 ? (&tv[q][0].x)[c] : (&tv[q][1].x)[c - 4];
-                            const float wc = LEVELS ? m.w[q] * (tq * (1.0f - tq)) : m.w[q];
-                            if (dfeat[c] != 0.0f) atomicAdd(rv + c, wc * dfeat[c]);
-                        }
-                    }
-                }
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int c = 0; c < kPFeat; ++c) atomicAdd(row + c * Vp + vtx[q], static_cast<Row>(add[q][c]));
             }
             if (__ballot(in_run && vpath)) {   // the run's winners: vertex sums over the wave
                 double vv[9], q[3];
@@ -1227,14 +1406,25 @@ __global__ __launch_bounds__(64) void ptri_bwd_kernel(PTriArgs a) {
     }
 }
 
-size_t ptri_bwd_lds(int R) { return static_cast<size_t>(mc_count(R) + 1) * kPCh * sizeof(float); }
+// The sorted path's grids (a finer one's texture gradient takes the per-pixel path).
+bool ptri_sorted(int R) { return R <= 5; }
+
+static size_t ptri_lds(const PTriArgs& a) { return ptri_lds(a.levels, a.R, a.Rmin, a.Rtop); }
 
 // As many single-wave workgroups as are resident at once (the LDS row bounds them), a
 // multiple of eight: the wave ranges are static, so a second round of workgroups
 // would double the time.
-int ptri_blocks(int num_cus, int R) {
+using PTriKernel = void (*)(PTriArgs);
+static PTriKernel ptri_kernel(bool levels, int R, int Rtop) {
+    const bool wide = ptri_row64(ptri_row_level(levels, R, Rtop));
+    if (levels) return wide ? ptri_bwd_kernel<true, double> : ptri_bwd_kernel<true, float>;
+    return wide ? ptri_bwd_kernel<false, double> : ptri_bwd_kernel<false, float>;
+}
+
+int ptri_blocks(int num_cus, bool levels, int R, int Rmin, int Rtop) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ptri_bwd_kernel<true>, 64, ptri_bwd_lds(R)) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ptri_kernel(levels, R, Rtop), 64,
+                                                     ptri_lds(levels, R, Rmin, Rtop)) != hipSuccess ||
         per_cu < 1) {
         (void)hipGetLastError();
         per_cu = 1;
@@ -1242,19 +1432,10 @@ int ptri_blocks(int num_cus, int R) {
     return (num_cus * per_cu / kXcds) * kXcds > 0 ? (num_cus * per_cu / kXcds) * kXcds : kXcds;
 }
 
-bool ptri_levels_fit(int R) {
-    // level R - 1 and its zero vertex in the stage buffer; the tables of levels R - 1.. (R <= 5)
-    return R < 1 || (R <= 5 && static_cast<size_t>(mc_count(R - 1) + 1) * kPCh <= 2 * kPIn * kPStage);
-}
-
 void launch_ptri_bwd(const PTriArgs& a, hipStream_t s) {
     if (a.n_blocks <= 0) return;
-    if (a.levels)
-        hipLaunchKernelGGL(ptri_bwd_kernel<true>, dim3(static_cast<unsigned>(a.n_blocks)), dim3(64), ptri_bwd_lds(a.R),
-                           s, a);
-    else
-        hipLaunchKernelGGL(ptri_bwd_kernel<false>, dim3(static_cast<unsigned>(a.n_blocks)), dim3(64), ptri_bwd_lds(a.R),
-                           s, a);
+    hipLaunchKernelGGL(ptri_kernel(a.levels, a.R, a.Rtop), dim3(static_cast<unsigned>(a.n_blocks)), dim3(64), ptri_lds(a),
+                       s, a);
 }
 
 __global__ __launch_bounds__(256) void pvert_finish_kernel(const double* __restrict__ g, float* __restrict__ out,

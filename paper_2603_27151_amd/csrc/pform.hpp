@@ -50,6 +50,7 @@ struct Micro {
     float w[3];      // their weights
     float fu, fv;    // position inside the cell (i, j)
     bool inv;        // the inverted micro-triangle of the cell
+    int i, j;        // the cell
 };
 
 // The micro-triangle containing (b1, b2) on the level with n segments per
@@ -65,6 +66,8 @@ __device__ __forceinline__ Micro micro_of(int n, float b1, float b2) {
     int j = static_cast<int>(__builtin_floorf(v));
     j = j < 0 ? 0 : (j > n - 1 - i ? n - 1 - i : j);
     Micro m;
+    m.i = i;
+    m.j = j;
     m.fu = u - static_cast<float>(i);
     m.fv = v - static_cast<float>(j);
     const float s = m.fu + m.fv;
