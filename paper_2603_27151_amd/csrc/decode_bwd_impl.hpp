@@ -341,7 +341,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         const uint64_t on_mask = __ballot(on);
         if (a.counter && lane == 0) atomicAdd(a.counter, static_cast<unsigned long long>(__popcll(on_mask)));
         float* st = s_stage[w];
-        const uint32_t cellw = static_cast<uint32_t>(c.ix) | (static_cast<uint32_t>(c.iy) << 16);
         // Each fragment's data for the MLP goes to its row of s_dx, which its
         // feature gradient takes later: the lanes of its block read it back from
         // there (moving it between lanes took five instructions per value).
@@ -674,19 +673,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         // channel), so that no two lanes of an LDS add share an address;
         // the winners' vertex gradients are summed over the run by a wave
         // reduction.
+        // One fragment per step also where it has 32 pairs only: two fragments may
+        // share a texel, and an LDS float32 add of 64 lanes takes 194 cycles, one
+        // lane after the other, where a read and a write take 26 (8-16-4, one 800 x 800
+        // view of 20,000 triangles: step 2,304 -> 2,187 us; 500 triangles: 465 -> 384).
         constexpr int LPF = 4 * S::C;                  // (corner, channel) pairs of one fragment
-        constexpr int FPS = LPF >= 64 ? 1 : 64 / LPF;  // fragments per step
         constexpr int PPF = LPF >= 64 ? LPF / 64 : 1;  // steps per fragment
-        // One fragment per step: each lane's fragment leaves its four corner
+        // Each lane's fragment leaves its four corner
         // weights (corner q = 2 dy + dx) in the stage, free once the MLP is
         // done, and keeps its cell's first texel; the steps then need no
         // per-fragment weight or address arithmetic beyond one add.
-        int cbase = 0;
-        if constexpr (FPS == 1) {
-            const float x1 = c.fx, y1 = c.fy, x0 = 1.0f - c.fx, y0 = 1.0f - c.fy;
-            *reinterpret_cast<float4*>(st + 4 * lane) = make_float4(x0 * y0, x1 * y0, x0 * y1, x1 * y1);
-            cbase = (c.iy * G + c.ix) * S::C;
-        }
+        const float x1 = c.fx, y1 = c.fy, x0 = 1.0f - c.fx, y0 = 1.0f - c.fy;
+        *reinterpret_cast<float4*>(st + 4 * lane) = make_float4(x0 * y0, x1 * y0, x0 * y1, x1 * y1);
+        const int cbase = (c.iy * G + c.ix) * S::C;
         wave_fence();
         const uint32_t tkey = on ? tri : 0xFFFFFFFFu;
         const uint32_t tprev = __shfl_up(tkey, 1, 64);
@@ -715,75 +714,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                 }
             }
             constexpr int UF = 4;                          // steps in flight: their staged reads go first
-            if constexpr (FPS == 1) {
-                // lane (corner q, channel k) of step pp: weight st[4 f + q],
-                // gradient s_dx[f][k], texel q of the fragment's cell
-                float* gl[PPF];
-                const float* wl[PPF];
-                const float* dl[PPF];
+            // lane (corner q, channel k) of step pp: weight st[4 f + q],
+            // gradient s_dx[f][k], texel q of the fragment's cell
+            float* gl[PPF];
+            const float* wl[PPF];
+            const float* dl[PPF];
+#pragma unroll
+            for (int pp = 0; pp < PPF; ++pp) {
+                const int idx = pp * 64 + lane;
+                const int q = idx / S::C, k = idx % S::C;
+                gl[pp] = grid + ((q >> 1) * G + (q & 1)) * S::C + k;
+                wl[pp] = st + q;
+                dl[pp] = s_dx[w] + k;
+            }
+            auto add = [&](int f, const float (&wv)[PPF], const float (&dv)[PPF]) __attribute__((always_inline)) {
+                const int cb = __builtin_amdgcn_readlane(cbase, LPF >= 64 ? f : __builtin_amdgcn_readfirstlane(f));
 #pragma unroll
                 for (int pp = 0; pp < PPF; ++pp) {
-                    const int idx = pp * 64 + lane;
-                    const int q = idx / S::C, k = idx % S::C;
-                    gl[pp] = grid + ((q >> 1) * G + (q & 1)) * S::C + k;
-                    wl[pp] = st + q;
-                    dl[pp] = s_dx[w] + k;
+                    float* gp = gl[pp] + cb;   // one fragment: 64 distinct addresses
+                    *gp = __builtin_fmaf(wv[pp], dv[pp], *gp);
                 }
-                auto add = [&](int f, const float (&wv)[PPF], const float (&dv)[PPF]) __attribute__((always_inline)) {
-                    const int cb = __builtin_amdgcn_readlane(cbase, f);
+            };
+            int f = LPF >= 64 || lane < LPF ? h : end;   // lanes past the pairs have none
+            for (; f + UF <= end; f += UF) {
+                float wv[UF][PPF], dv[UF][PPF];
+#pragma unroll
+                for (int u = 0; u < UF; ++u)
 #pragma unroll
                     for (int pp = 0; pp < PPF; ++pp) {
-                        float* gp = gl[pp] + cb;   // one fragment: 64 distinct addresses
-                        *gp = __builtin_fmaf(wv[pp], dv[pp], *gp);
+                        wv[u][pp] = wl[pp][4 * (f + u)];
+                        dv[u][pp] = dl[pp][(f + u) * DXS];
                     }
-                };
-                int f = h;
-                for (; f + UF <= end; f += UF) {
-                    float wv[UF][PPF], dv[UF][PPF];
 #pragma unroll
-                    for (int u = 0; u < UF; ++u)
+                for (int u = 0; u < UF; ++u) add(f + u, wv[u], dv[u]);
+            }
+            for (; f < end; ++f) {
+                float wv[PPF], dv[PPF];
 #pragma unroll
-                        for (int pp = 0; pp < PPF; ++pp) {
-                            wv[u][pp] = wl[pp][4 * (f + u)];
-                            dv[u][pp] = dl[pp][(f + u) * DXS];
-                        }
-#pragma unroll
-                    for (int u = 0; u < UF; ++u) add(f + u, wv[u], dv[u]);
+                for (int pp = 0; pp < PPF; ++pp) {
+                    wv[pp] = wl[pp][4 * f];
+                    dv[pp] = dl[pp][f * DXS];
                 }
-                for (; f < end; ++f) {
-                    float wv[PPF], dv[PPF];
-#pragma unroll
-                    for (int pp = 0; pp < PPF; ++pp) {
-                        wv[pp] = wl[pp][4 * f];
-                        dv[pp] = dl[pp][f * DXS];
-                    }
-                    add(f, wv, dv);
-                }
-            } else {
-                for (int f0 = h; f0 < end; f0 += FPS * UF) {
-                    int fs[UF];
-                    bool ok[UF];
-                    float dv[UF];
-#pragma unroll
-                    for (int u = 0; u < UF; ++u) {
-                        const int f = f0 + u * FPS + lane / LPF;
-                        ok[u] = f < end;
-                        fs[u] = ok[u] ? f : h;                     // lanes past the run repeat h with weight 0
-                        dv[u] = s_dx[w][fs[u] * DXS + lane % LPF % S::C];
-                    }
-#pragma unroll
-                    for (int u = 0; u < UF; ++u) {
-                        const uint32_t cw = static_cast<uint32_t>(__shfl(static_cast<int>(cellw), fs[u], 64));
-                        const float fx = __shfl(c.fx, fs[u], 64);
-                        const float fy = __shfl(c.fy, fs[u], 64);
-                        const int ix = static_cast<int>(cw & 0xFFFFu), iy = static_cast<int>(cw >> 16);
-                        const int q = lane % LPF / S::C, k = lane % LPF % S::C;   // corner, channel
-                        const int dxq = q & 1, dyq = q >> 1;
-                        const float wq = (dxq ? fx : 1.0f - fx) * (dyq ? fy : 1.0f - fy);
-                        // two fragments per step may share a texel
-                        atomicAdd(&grid[((iy + dyq) * G + ix + dxq) * S::C + k], ok[u] ? wq * dv[u] : 0.0f);
-                    }
-                }
+                add(f, wv, dv);
             }
             wave_fence();
         }

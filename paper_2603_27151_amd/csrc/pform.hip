@@ -835,16 +835,17 @@ __device__ __forceinline__ void stage_units(float (*st)[kPStage], const f4v (&v)
 // One wave per workgroup walks a contiguous range of the fragment list sorted
 // by triangle (every winner, and the fragments in front of it where the pixel
 // carries a score weight), 64 fragments per batch, and keeps the gradient of
-// the current triangle's texture (V x 8) and its nine vertex sums in its LDS,
-// in float64. Per fragment: its opacity lookup and the score term; per winner
-// also the colour path of pwinner_bwd_kernel (recompute, blend, the MLP and its
-// data and weight gradients on the matrix cores, features onto the three grid
-// vertices, the float64 vertex chain with the edge term). Adds into the row
-// are LDS atomics (two fragments of a run may share a grid vertex): of
-// float64 where that fits, because an LDS add of 64 float32 takes 194 cycles
-// here, one lane after the other, and one of 64 float64 takes 10 (ptri_row64). When the triangle changes,
-// the row goes to HBM: plain stores when the wave holds all of the triangle's
-// fragments, float atomics when the triangle straddles two waves' ranges.
+// the current triangle's texture (V x 8) and its nine vertex sums in its LDS.
+// Per fragment: its opacity lookup and the score term; per winner also the
+// colour path of pwinner_bwd_kernel (recompute, blend, the MLP and its data and
+// weight gradients on the matrix cores, features onto the three grid vertices,
+// the float64 vertex chain with the edge term). Adds into the row are LDS
+// atomics (two fragments of a run may share a grid vertex): of float64 where
+// that fits (ptri_row64), because an LDS add of 64 float32 takes 194 cycles
+// here, one lane after the other, and one of 64 float64 takes 10. When the
+// triangle changes, the row goes to HBM: plain stores when the wave holds all
+// of the triangle's fragments, float atomics when the triangle straddles two
+// waves' ranges.
 //
 // LEVELS: the gradient of the learnable levels instead of the assembled
 // texture's (the assembly's backward folded in). Every add is multiplied by
