@@ -140,8 +140,13 @@ __device__ __forceinline__ float exp_c(float x) {
 
 __device__ __forceinline__ float sigmoid_c(float x) { return 1.0f / (1.0f + exp_c(-x)); }
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return static_cast<uint32_t>(__builtin_amdgcn_bitop3_b32(static_cast<int>(a), static_cast<int>(b), static_cast<int>(c), 0x96));
+}
+
 // Philox4x32-10 (Salmon et al., SC'11). Counter (pixel, tri, view, step),
-// key (seed lo, seed hi); returns the first output word.
+// key (seed lo, seed hi); returns the first output word. Both halves of a
+// product in one instruction, and one for two exclusive ors.
 __device__ __forceinline__ uint32_t philox_x0(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -150,16 +155,14 @@ __device__ __forceinline__ uint32_t philox_x0(uint32_t c0, uint32_t c1, uint32_t
             k0 += 0x9E3779B9u;
             k1 += 0xBB67AE85u;
         }
-        const uint32_t lo0 = 0xD2511F53u * c0;
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2);
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
+        const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
+        const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
+        const uint32_t n0 = xor3(static_cast<uint32_t>(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3(static_cast<uint32_t>(p0 >> 32), c3, k1);
         c0 = n0;
-        c1 = lo1;
+        c1 = static_cast<uint32_t>(p1);
         c2 = n2;
-        c3 = lo0;
+        c3 = static_cast<uint32_t>(p0);
     }
     return c0;
 }

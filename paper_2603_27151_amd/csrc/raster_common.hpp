@@ -44,26 +44,39 @@ __device__ __forceinline__ int wave_scan_dpp(int v, int identity, Op op) {
     v = dpp_step<0x142, 0xA>(v, identity, op);
     return dpp_step<0x143, 0xC>(v, identity, op);
 }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t dpp_max_step_u64(uint64_t v) {
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
-    const uint32_t hi =
-        static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), CTRL, ROWS, 0xF, false));
-    const uint64_t u = (static_cast<uint64_t>(hi) << 32) | lo;
-    return u > v ? u : v;
+// The largest values over the wave of NB values per lane (wave-uniform): the
+// high words first, then the low words of the lanes that hold the largest
+// one. Six 32-bit steps each, of one instruction, with the values' steps side
+// by side, where 64-bit steps took seven and waited for each other.
+__device__ __forceinline__ uint32_t max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+template <int CTRL, int ROWS, int NB>
+__device__ __forceinline__ void dpp_max_step(uint32_t (&v)[NB]) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        v[b] = max_u32(v[b], static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v[b]), CTRL, ROWS, 0xF, false)));
 }
-
-// The largest value over the wave (wave-uniform).
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-    v = dpp_max_step_u64<0x111, 0xF>(v);
-    v = dpp_max_step_u64<0x112, 0xF>(v);
-    v = dpp_max_step_u64<0x114, 0xF>(v);
-    v = dpp_max_step_u64<0x118, 0xF>(v);
-    v = dpp_max_step_u64<0x142, 0xA>(v);
-    v = dpp_max_step_u64<0x143, 0xC>(v);
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
-    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), 63));
-    return (static_cast<uint64_t>(hi) << 32) | lo;
+template <int NB>
+__device__ __forceinline__ void wave_max_u32(uint32_t (&v)[NB]) {
+    dpp_max_step<0x111, 0xF>(v);
+    dpp_max_step<0x112, 0xF>(v);
+    dpp_max_step<0x114, 0xF>(v);
+    dpp_max_step<0x118, 0xF>(v);
+    dpp_max_step<0x142, 0xA>(v);
+    dpp_max_step<0x143, 0xC>(v);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) v[b] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v[b]), 63));
+}
+template <int NB>
+__device__ __forceinline__ void wave_max_u64(const uint64_t (&v)[NB], uint64_t (&out)[NB]) {
+    uint32_t hi[NB], lo[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) hi[b] = static_cast<uint32_t>(v[b] >> 32);
+    wave_max_u32(hi);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) lo[b] = static_cast<uint32_t>(v[b] >> 32) == hi[b] ? static_cast<uint32_t>(v[b]) : 0u;
+    wave_max_u32(lo);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) out[b] = (static_cast<uint64_t>(hi[b]) << 32) | lo[b];
 }
 
 // Smallest key any not-yet-processed entry of the tile list can produce.

@@ -87,7 +87,7 @@ struct FwdWaveLds {
     float qt[3][kQueue];    // beta_i / w_i (the decode forms the perspective-correct barycentrics)
     uint16_t qpl[kQueue];   // pixel of the region: block * 64 + pixel of the block
     // the region's pixels: current best key (their colours go straight to the output)
-    uint64_t key[64 * NB];
+    alignas(16) uint64_t key[64 * NB];   // (the coverage reads two at a time)
     // per round of the fragment step: the slice pair whose run of combinations starts here
     int8_t head[64];
     // counting only: the region's pixels that some fragment covers, per block (bits 0..31, 32..63)
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
         as_global_w(uniform_ptr(vd.vis_out ? vd.vis_out : (a.vis ? a.vis + vd.pix_base : nullptr)));
 
     // the pixels' best keys live in L.key; per block, the largest of them (wave-uniform)
-    uint64_t wmaxb[NB];
+    uint64_t wmaxb[NB], k_first[NB];
     uint64_t wmax = 0;   // ... over the region
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -237,9 +237,11 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
             }
         }
         L.key[b * 64 + lane] = k0;
-        wmaxb[b] = wave_max_u64(k0);
-        wmax = wmaxb[b] > wmax ? wmaxb[b] : wmax;
+        k_first[b] = k0;
     }
+    wave_max_u64(k_first, wmaxb);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) wmax = wmaxb[b] > wmax ? wmaxb[b] : wmax;
     if (a.counter && lane < 2 * NB) L.cov[lane] = 0u;
 
     // decode a batch of n queued candidates, one per lane
@@ -356,12 +358,13 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
         if (a.counter && lane == 0) atomicAdd(a.counter, static_cast<unsigned long long>(n));
         wave_fence();
         __builtin_amdgcn_s_setprio(1);
+        uint64_t k[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) k[b] = L.key[b * 64 + lane];
+        wave_max_u64(k, wmaxb);
         wmax = 0;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            wmaxb[b] = wave_max_u64(L.key[b * 64 + lane]);
-            wmax = wmaxb[b] > wmax ? wmaxb[b] : wmax;
-        }
+        for (int b = 0; b < NB; ++b) wmax = wmaxb[b] > wmax ? wmaxb[b] : wmax;
     };
 
     const int64_t beg = a.tile_start[tile], end = a.tile_start[tile + 1];
@@ -494,50 +497,66 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
                 const int32_t X[3] = {static_cast<int32_t>(q0.x), static_cast<int32_t>(q0.y), static_cast<int32_t>(q0.z)};
                 const int32_t Y[3] = {static_cast<int32_t>(q0.w), static_cast<int32_t>(q1.x), static_cast<int32_t>(q1.y)};
                 const float rA = __uint_as_float(q3.x);
-                const int sgn = rA < 0.0f ? -1 : 1;
+                const bool neg = rA < 0.0f;
                 // snapped position of the block's first pixel centre
-                const int64_t PX0 = static_cast<int64_t>(kSnap) * (rx + (cblk % BR) * 8) + kSnap / 2;
-                const int64_t PY0 = static_cast<int64_t>(kSnap) * (ry + (cblk / BR) * 8) + kSnap / 2;
-                double e0[3], ea[3], eb[3], thr[3];
-                int32_t nx[3], ny[3];
+                const int32_t PX0 = kSnap * (rx + (cblk % BR) * 8) + kSnap / 2;
+                const int32_t PY0 = kSnap * (ry + (cblk / BR) * 8) + kSnap / 2;
+                // The edge functions at the block's pixels are E = E0 + kSnap t with the
+                // integer t = pv nx - pu ny. An edge owns the centres exactly on it when
+                // it is a top or left edge: E >= 0, else E >= 1. With b = 0 or 1 that is
+                // t + floor((E0 - b) / kSnap) >= 0, whose terms fit 32 bits: |t| is below
+                // 14 2^25 (differences of coordinates below 2^24), and a floor beyond 2^29
+                // decides for the whole block. So each pixel takes three integer
+                // additions and the signs' disjunction, instead of three float64
+                // fused multiply-adds and comparisons at half the rate or less (64 views
+                // of 50,000 triangles: forward 1.72 -> 1.60 ms).
+                double e0[3];
+                int32_t nx[3], ny[3], f[3];
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {   // edge e joins vertices e+1 and e+2
                     const int va = e == 2 ? 0 : e + 1;
                     const int vb = e == 0 ? 2 : (e == 1 ? 0 : 1);
                     const int32_t dx = X[vb] - X[va], dy = Y[vb] - Y[va];
-                    const int64_t E0 =
-                        static_cast<int64_t>(dx) * (PY0 - Y[va]) - static_cast<int64_t>(dy) * (PX0 - X[va]);
-                    e0[e] = static_cast<double>(sgn * E0);
-                    nx[e] = sgn * dx;
-                    ny[e] = sgn * dy;
-                    ea[e] = -static_cast<double>(kSnap) * static_cast<double>(ny[e]);
-                    eb[e] = static_cast<double>(kSnap) * static_cast<double>(nx[e]);
-                    // an edge owns the centres exactly on it when it is a top or left edge:
-                    // E > 0, or E == 0 on an owning edge, is E > -1/2 for integer E
-                    thr[e] = (ny[e] < 0 || (ny[e] == 0 && nx[e] > 0)) ? -0.5 : 0.0;
+                    nx[e] = neg ? -dx : dx;
+                    ny[e] = neg ? -dy : dy;
+                    const int64_t E0 = static_cast<int64_t>(nx[e]) * (PY0 - Y[va]) - static_cast<int64_t>(ny[e]) * (PX0 - X[va]);
+                    e0[e] = static_cast<double>(E0);
+                    const bool own = ny[e] < 0 || (ny[e] == 0 && nx[e] > 0);
+                    const int64_t F = (E0 - (own ? 0 : 1)) >> 8;
+                    constexpr int64_t kFar = int64_t(1) << 29;
+                    f[e] = static_cast<int32_t>(F > kFar ? kFar : F < -kFar ? -kFar : F);
                 }
-                // a covered pixel whose best key is already at or below the
-                // triangle's depth bound can take no fragment of it (keys only
-                // fall), so it is left out of the mask here rather than
-                // rejected one combination at a time later
-                const uint64_t* __restrict__ kb = &L.key[cblk * 64];
+                static_assert(kSnap == 256, "the shift divides by kSnap");
+                // a covered pixel whose best key is already below the triangle's
+                // depth bound can take no fragment of it (keys only fall), so it is
+                // left out of the mask here rather than rejected one combination at
+                // a time later (the depths decide; equal ones stay in)
+                // (the keys' high words, two keys per read)
+                typedef uint32_t Keys2 __attribute__((ext_vector_type(4), may_alias));
+                const Keys2* __restrict__ kb = reinterpret_cast<const Keys2*>(&L.key[cblk * 64]);
+                const uint32_t depth = static_cast<uint32_t>(cent >> 32);
+                uint32_t out[2] = {0u, 0u}, beat[2] = {0u, 0u};   // bit 31 enters first
 #pragma unroll
-                for (int pv2 = 0; pv2 < 8; ++pv2) {
-                    double c[3];
+                for (int e = 0; e < 3; ++e) f[e] += 7 * (nx[e] - ny[e]);   // the last pixel
 #pragma unroll
-                    for (int e = 0; e < 3; ++e) c[e] = __builtin_fma(static_cast<double>(pv2), eb[e], e0[e]);
-                    uint32_t row = 0;
+                for (int pv2 = 7; pv2 >= 0; --pv2) {
+                    int32_t c[3] = {f[0], f[1], f[2]};
+                    Keys2 k{};
 #pragma unroll
-                    for (int pu2 = 0; pu2 < 8; ++pu2) {
-                        bool in = cent < kb[pv2 * 8 + pu2];
+                    for (int pu2 = 7; pu2 >= 0; --pu2) {
+                        const int h = pv2 >> 2;
+                        if (pu2 & 1) k = kb[(pv2 * 8 + pu2) >> 1];
+                        const uint32_t s = static_cast<uint32_t>(c[0] | c[1] | c[2]);   // the sign: outside an edge
+                        out[h] = __builtin_amdgcn_alignbit(out[h], s, 31);
+                        beat[h] = beat[h] + beat[h] + (depth <= (pu2 & 1 ? k.w : k.y) ? 1u : 0u);
 #pragma unroll
-                        for (int e = 0; e < 3; ++e)
-                            in = in & (__builtin_fma(static_cast<double>(pu2), ea[e], c[e]) > thr[e]);
-                        row |= in ? (1u << pu2) : 0u;
+                        for (int e = 0; e < 3; ++e) c[e] += ny[e];
                     }
-                    if (pv2 < 4) mlo |= row << (8 * pv2);
-                    else mhi |= row << (8 * (pv2 - 4));
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) f[e] -= nx[e];
                 }
+                mlo = beat[0] & ~out[0];
+                mhi = beat[1] & ~out[1];
                 // A pixel left out of the mask already has a passing fragment; every
                 // fragment of a pixel without one is in some mask, since the walk
                 // then reaches the end of the list.
