@@ -13,7 +13,7 @@ __global__ __launch_bounds__(256) void logp_kernel(FragLogView L, FragSelect sel
     gfloat* feats = as_global(uniform_ptr(feats_p));
     __shared__ f4v s_w[4][FwdWeights<S>::kLds];
     FwdRegs<S> wregs;
-    const f4v* wops = reinterpret_cast<const f4v*>(weights);
+    gf4v* wops = as_gf4v(reinterpret_cast<const f4v*>(weights));
     if constexpr (FwdWeights<S>::kRegs) wregs.load(wops, s_w[w], lane);
     for_log_batches(L, [&](uint32_t r, uint32_t b, uint32_t n) {
         const uint64_t at = static_cast<uint64_t>(r) * L.region + b + lane;
@@ -34,8 +34,9 @@ __global__ __launch_bounds__(256) void logp_kernel(FragLogView L, FragSelect sel
         // opaque copies of the weight pointers per batch: the compiler may not hoist
         // the weights' loads out of the batch loop
         if constexpr (FwdWeights<S>::kMfma) {
-            const f4v* wg = opaque_ptr(wops);
-            mfma_logits<S>(wregs, wg, FwdWeights<S>::kRegs ? s_w[w] : wg + FwdWeights<S>::kWo, x, o, lane);
+            gf4v* wg = as_gf4v(opaque_ptr(reinterpret_cast<const f4v*>(weights)));
+            if constexpr (FwdWeights<S>::kRegs) mfma_logits<S>(wregs, wg, s_w[w], x, o, lane);
+            else mfma_logits<S>(wregs, wg, wg + FwdWeights<S>::kWo, x, o, lane);
         } else {
             mlp_logits<S>(as_const(opaque_ptr(mlp)), x, o);
         }
