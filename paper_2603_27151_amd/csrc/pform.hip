@@ -130,7 +130,8 @@ __global__ __launch_bounds__(256) void mc_assemble_lds_kernel(AssembleArgs a) {
         for (int tt = 0; tt < TPB; ++tt) {
             if (tt < nt) {
                 float4* o = reinterpret_cast<float4*>(a.tex_out) + static_cast<size_t>(t0 + tt) * Vf * 2 + e;
-                *o = make_float4(sigmoid_c(z[tt].x), sigmoid_c(z[tt].y), sigmoid_c(z[tt].z), sigmoid_c(z[tt].w));
+                const f4v r = {sigmoid_c(z[tt].x), sigmoid_c(z[tt].y), sigmoid_c(z[tt].z), sigmoid_c(z[tt].w)};
+                __builtin_nontemporal_store(r, reinterpret_cast<f4v*>(o));
             }
         }
     }

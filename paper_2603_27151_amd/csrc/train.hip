@@ -299,6 +299,16 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const 
     }
 }
 
+// Non-temporal: read or written once.
+typedef float nt4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float4 nt_load(const float4* p) {
+    const nt4 v = __builtin_nontemporal_load(reinterpret_cast<const nt4*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void nt_store(float4 v, float4* p) {
+    __builtin_nontemporal_store(nt4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt4*>(p));
+}
+
 // Adam on 16-byte groups of four parameters (vec = 1, n a multiple of 4,
 // every array 16-byte aligned): the same arithmetic per element, with
 // 16-byte loads and stores.
@@ -308,8 +318,8 @@ __global__ void __launch_bounds__(256) adam4_kernel(float4* __restrict__ p, cons
                                                     float bc1, float bc2) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n4;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const float4 gi = g[i];
-        float4 mi = m[i], vi = v[i], pi = p[i];
+        const float4 gi = nt_load(g + i);
+        float4 mi = nt_load(m + i), vi = nt_load(v + i), pi = p[i];
         float* pm = &mi.x;
         float* pv = &vi.x;
         float* pp = &pi.x;
@@ -319,8 +329,8 @@ __global__ void __launch_bounds__(256) adam4_kernel(float4* __restrict__ p, cons
             pm[k] = b1 * pm[k] + omb1 * pg[k];
             pp[k] -= lr * (pm[k] / bc1) / (sqrtf(pv[k] / bc2) + eps);
         }
-        m[i] = mi;
-        v[i] = vi;
+        nt_store(mi, m + i);
+        nt_store(vi, v + i);
         p[i] = pi;
     }
 }
