@@ -556,7 +556,7 @@ __global__ __launch_bounds__(256) void zero_kernel(ZeroList z) {
     for (int r = 0; r < z.k; ++r) {
         int32_t* p = z.p[r];
         const int64_t n = z.n[r], n4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n / 4 : 0;
-        for (int64_t i = tid; i < n4; i += step) reinterpret_cast<int4*>(p)[i] = make_int4(0, 0, 0, 0);
+        for (int64_t i = tid; i < n4; i += step) nt_store(make_float4(0.f, 0.f, 0.f, 0.f), reinterpret_cast<float4*>(p) + i);
         for (int64_t i = 4 * n4 + tid; i < n; i += step) p[i] = 0;
     }
 }

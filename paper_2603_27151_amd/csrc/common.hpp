@@ -322,6 +322,32 @@ __device__ __forceinline__ T* opaque_ptr(T* p) {
     return reinterpret_cast<T*>(v);
 }
 
+// Loads and stores of what a kernel uses once, past the caches.
+typedef float nt4 __attribute__((ext_vector_type(4)));
+typedef uint32_t ntu4 __attribute__((ext_vector_type(4)));
+typedef uint32_t ntu2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void nt_store(uint4 v, uint4* p) {
+    __builtin_nontemporal_store(ntu4{v.x, v.y, v.z, v.w}, reinterpret_cast<ntu4*>(p));
+}
+__device__ __forceinline__ void nt_store(uint2 v, uint2* p) {
+    __builtin_nontemporal_store(ntu2{v.x, v.y}, reinterpret_cast<ntu2*>(p));
+}
+__device__ __forceinline__ uint2 nt_load(const uint2* p) {
+    const ntu2 v = __builtin_nontemporal_load(reinterpret_cast<const ntu2*>(p));
+    return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ uint4 nt_load(const uint4* p) {
+    const ntu4 v = __builtin_nontemporal_load(reinterpret_cast<const ntu4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 nt_load(const float4* p) {
+    const nt4 v = __builtin_nontemporal_load(reinterpret_cast<const nt4*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void nt_store(float4 v, float4* p) {
+    __builtin_nontemporal_store(nt4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt4*>(p));
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const int l = __lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));

@@ -283,9 +283,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         const int64_t fi = static_cast<int64_t>(bi) * 64 + lane;
         nvalid = bi < b_end && fi < E;
         if (nvalid) {
-            const FragRec fr = a.sorted[fi];
-            na = make_uint4(fr.p0.x, fr.p0.y, fr.p1.x, fr.p1.y);
-            nx = fr.x;
+            const uint2* fr = reinterpret_cast<const uint2*>(a.sorted + fi);
+            const uint2 p0 = nt_load(fr), p1 = nt_load(fr + 1);
+            na = make_uint4(p0.x, p0.y, p1.x, p1.y);
+            nx = nt_load(fr + 2);
         }
     };
     auto pixfetch = [&]() __attribute__((always_inline)) {
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         for (int k = lane; k < n_grid; k += 64) {
             const float v = grid[k];
             grid[k] = 0.0f;
-            if (owned) gf[k] = a.accumulate ? gf[k] + v : v;
+            if (owned) __builtin_nontemporal_store(a.accumulate ? gf[k] + v : v, &gf[k]);
             else if (v != 0.0f) atomicAdd(&gf[k], v);
         }
         if (lane < 9) {

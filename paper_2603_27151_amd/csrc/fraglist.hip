@@ -110,9 +110,9 @@ __global__ __launch_bounds__(256) void place_kernel(FragLogView L, const float* 
         uint4 e = make_uint4(0u, 0xFFFFFFFFu, 0u, 0u);
         uint2 bc = make_uint2(0u, 0u);
         float gl = 0.0f;
-        if (b + lane < n) e = L.frag[at];
+        if (b + lane < n) e = nt_load(L.frag + at);
         if (keep) {
-            bc = L.bary[at];
+            bc = nt_load(L.bary + at);
             if (grad_logp) gl = grad_logp[e.x];
         }
         const uint32_t tri = e.y;

@@ -350,9 +350,9 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
                 const uint32_t at = log_cursor + static_cast<uint32_t>(lane);
                 if (at < a.log_region) {
                     const int64_t pg = pix_base + static_cast<int64_t>(gy) * W + gx;
-                    a.log_frag[log_base + at] = make_uint4(static_cast<uint32_t>(pg), tri, static_cast<uint32_t>(key >> 32),
-                                                           static_cast<uint32_t>(v));
-                    a.log_bary[log_base + at] = make_uint2(__float_as_uint(b1), __float_as_uint(b2));
+                    nt_store(make_uint4(static_cast<uint32_t>(pg), tri, static_cast<uint32_t>(key >> 32),
+                                        static_cast<uint32_t>(v)), a.log_frag + log_base + at);
+                    nt_store(make_uint2(__float_as_uint(b1), __float_as_uint(b2)), a.log_bary + log_base + at);
                 }
             }
         }

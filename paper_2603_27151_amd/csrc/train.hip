@@ -299,16 +299,6 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const 
     }
 }
 
-// Non-temporal: read or written once.
-typedef float nt4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 nt_load(const float4* p) {
-    const nt4 v = __builtin_nontemporal_load(reinterpret_cast<const nt4*>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void nt_store(float4 v, float4* p) {
-    __builtin_nontemporal_store(nt4{v.x, v.y, v.z, v.w}, reinterpret_cast<nt4*>(p));
-}
-
 // Adam on 16-byte groups of four parameters (vec = 1, n a multiple of 4,
 // every array 16-byte aligned): the same arithmetic per element, with
 // 16-byte loads and stores.
@@ -319,7 +309,7 @@ __global__ void __launch_bounds__(256) adam4_kernel(float4* __restrict__ p, cons
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n4;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const float4 gi = nt_load(g + i);
-        float4 mi = nt_load(m + i), vi = nt_load(v + i), pi = p[i];
+        float4 mi = nt_load(m + i), vi = nt_load(v + i), pi = nt_load(p + i);
         float* pm = &mi.x;
         float* pv = &vi.x;
         float* pp = &pi.x;
@@ -331,7 +321,7 @@ __global__ void __launch_bounds__(256) adam4_kernel(float4* __restrict__ p, cons
         }
         nt_store(mi, m + i);
         nt_store(vi, v + i);
-        p[i] = pi;
+        nt_store(pi, p + i);
     }
 }
 
