@@ -743,7 +743,9 @@ int decode_blocks(soup_ctx* c, int64_t fragments) {
 }
 
 // The view of a log that its readers take. A region's batches are shared by as many waves as
-// give each about eight (a wave per region where the regions are short).
+// give each about eight, and down to one each while the waves do not fill the GPU (a batch is a
+// chain of dependent loads and an atomic: 128 x 128 pixels, count 10.2 -> 5.4 us, place
+// 11.1 -> 5.1; a view of 10,000 triangles 7.7 -> 6.0 and 11.0 -> 8.7).
 FragLogView log_view(const soup_ctx::FragLog& g) {
     FragLogView v{};
     v.frag = static_cast<uint4*>(g.frag.p);
@@ -751,7 +753,8 @@ FragLogView log_view(const soup_ctx::FragLog& g) {
     v.counts = static_cast<uint32_t*>(g.counts.p);
     v.region = static_cast<uint32_t>(g.region);
     v.n_regions = g.regions;
-    v.split = static_cast<int>(std::max<uint64_t>(1, std::min<uint64_t>(16, g.hint / 512)));
+    const uint64_t fill = 8192 / static_cast<uint64_t>(std::max(1, g.regions));
+    v.split = static_cast<int>(std::max<uint64_t>(1, std::min<uint64_t>(16, std::max(g.hint / 512, std::min(g.hint / 64, fill)))));
     return v;
 }
 
