@@ -1030,6 +1030,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     {
         DecodeArgs d = decode_args(c, p, a);
         d.n_blocks = nb;
+        d.short_list = !c->fixed && static_cast<int64_t>((from_log ? c->flog : c->rlog).total) < static_cast<int64_t>(nb) * 4 * 8 * 64;
         d.sorted = static_cast<FragRec*>(c->sorted.p);
         d.tri_off = static_cast<int64_t*>(c->tri_off.p);
         d.grad_color = grad_color;

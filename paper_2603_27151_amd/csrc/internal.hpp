@@ -210,6 +210,7 @@ struct DecodeArgs {
     float* grad_verts;             // [T, 9]: zeroed by the caller unless accumulate
     int accumulate;
     float* mlp_partial;            // [n_blocks * 4, n_params]
+    int short_list;                  // 1: fewer than eight batches of 64 fragments per wave (known on the host)
     unsigned long long* counter;   // decode counter or null
     int n_blocks;
 };
