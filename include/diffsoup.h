@@ -131,8 +131,8 @@ enum {
     SOUP_T_LOGP = 9,     /* log p(f*) pass (includes its replay and decode) */
     SOUP_T_LOSS = 10,    /* L2 loss */
     SOUP_T_FILL = 11,    /* zero fills */
-    SOUP_T_REPLAY = 12,  /* backward front-set replay (coverage, fragment list) */
-    SOUP_T_GRAD = 13,    /* per-triangle feature and vertex gradient reduction */
+    SOUP_T_REPLAY = 12,  /* backward: the walk that logs the fragments where no forward did, and their counts */
+    SOUP_T_GRAD = 13,    /* backward: the fragment list's offsets and placement by triangle */
     SOUP_T_COVER = 14,   /* adaptive control: coverage counts */
     SOUP_T_EDGELEN = 15, /* adaptive control: screen-space edge lengths */
     SOUP_T_APPLY = 16,   /* adaptive control: applying a plan */
@@ -184,7 +184,7 @@ soup_status soup_last_stats(const soup_ctx* ctx, soup_stats* out);
  *   vis   [P] uint64   winner key, 0xFFFFFFFFFFFFFFFF where no fragment passes
  *   color [P,3] float  sigmoid of the winner's RGB logits, or background
  *   logp  [P] float    log p(f*) of Eq. (6) (mode 0), or NULL
- * The call synchronises `stream` once (after binning) to size the tile list
+ * The call waits once for the tile lists' total (after their counts) to size the tile list
  * workspace; everything else is asynchronous.
  */
 soup_status soup_rasterize_fwd(soup_ctx* ctx, const soup_scene* scene, const soup_views* views,

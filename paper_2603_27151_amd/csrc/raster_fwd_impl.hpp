@@ -15,9 +15,9 @@
 //    that block, appends one (triangle, block) pair per such block to a queue
 //    of waiting pairs, in list order;
 //  - coverage, lanes over 64 waiting pairs: each computes the exact 64-pixel
-//    coverage mask of its triangle over its block from float64 edge
-//    functions (every value an exact integer); covering pairs leave their
-//    edge and vertex data in the wave's LDS;
+//    coverage mask of its triangle over its block from integer edge
+//    functions; covering pairs leave their edge and vertex data in the wave's
+//    LDS;
 //  - fragments, lanes over covered (pair, pixel) combinations: the slice's
 //    combinations are taken 64 at a time in slice order (a lane finds its pair
 //    by a max-scan over the starts of the pairs' runs and its pixel as the
@@ -34,6 +34,11 @@
 // pixel: front-to-back early-out without sorting fragments. The result does
 // not depend on the visiting order (the draws are fixed by Philox), only the
 // amount of work does.
+//
+// What bounds it: the decode's products and the walk's vector instructions,
+// which take turns on a SIMD (64 views of 50,000 triangles, 1.49 ms: matrix
+// cores busy 27% of the time, vector instructions issued in 48%; three waves
+// per SIMD, as many as the LDS holds).
 #include "fwd_mfma.hpp"
 #include "pform.hpp"
 
