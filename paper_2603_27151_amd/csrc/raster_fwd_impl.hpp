@@ -670,7 +670,9 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const uint64_t won = __ballot(oin[b] && okey[b] != kBgKey);
-            n_cov += __popcll(won | (static_cast<uint64_t>(L.cov[2 * b + 1]) << 32) | L.cov[2 * b]);
+            // (a mask may hold pixels outside the view where the depth bound is zero, as their keys are)
+            const uint64_t masks = ((static_cast<uint64_t>(L.cov[2 * b + 1]) << 32) | L.cov[2 * b]) & __ballot(oin[b]);
+            n_cov += __popcll(won | masks);
         }
         if (lane == 0 && n_cov) atomicAdd(a.counter + 8, static_cast<unsigned long long>(n_cov));
     }

@@ -54,3 +54,18 @@ def test_masks(kind, flat):
     got = vis.cpu().numpy().view(np.uint64).reshape(rvis.shape)
     assert (rvis != np.uint64(0xFFFFFFFFFFFFFFFF)).any()
     assert np.array_equal(got, rvis)
+
+
+@pytest.mark.parametrize("size", [(13, 9), (1, 1), (31, 17)])
+def test_covered_pixels_at_the_near_plane(size):
+    """Triangles of depth 0 over views that end inside a block: the pixels counted as covered are the view's."""
+    from paper_2603_27151_amd import _lib, raster as R
+    rng = np.random.Generator(np.random.PCG64(4))
+    verts = np.array([[[-3.0, -1.0, -1.0], [3.0, -1.0, -1.0], [0.0, 5.0, -1.0]]] * 3)
+    s = W.random_scene(rng, verts, 4, 8, [8, 16, 4])
+    v = W.View(size[0], size[1], 3, np.eye(4, dtype=np.float32))
+    ctx = _lib.Ctx(torch.cuda.current_device())
+    ctx.set_counting(True)
+    vis, _, _ = R.rasterize_fwd(R.DeviceScene.from_host(s), R.Views.from_list([v]), R.Opts(seed=2), ctx=ctx)
+    assert np.array_equal(vis.cpu().numpy().view(np.uint64).reshape(size[1], size[0]), O.forward(s, v, O.Opts(seed=2))[0])
+    assert ctx.stats()["covered_pixels"] == size[0] * size[1]
