@@ -8,7 +8,7 @@
 // scatter: per (view, triangle): writes (zmin << 32 | tri) into the list of
 //          every tile its bounding box touches.
 // sort:    sorts each tile's list ascending (a wave sorts a short list
-//          bitonic in registers; a workgroup sorts a long one bitonic in LDS,
+//          bitonic in registers; a workgroup sorts a long one likewise,
 //          in blocks of kSortBlock entries), so that the raster can walk
 //          triangles front to back and stop early.
 #include "internal.hpp"
@@ -309,51 +309,99 @@ __global__ __launch_bounds__(256) void scatter_small_kernel(const ViewDesc* __re
     }
 }
 
-// Bitonic sort of a short list by one wave, held in registers: entry e =
-// 64 r + lane is register r of its lane (R = entries per lane, n <= 64 R; the
-// slots past n hold the largest key and stay at the end). A compare-exchange
-// at distance j pairs e with e ^ j: between lanes for j < 64, between two
-// registers of one lane for j >= 64. Entry e keeps the smaller key when it is
+// The value of lane (lane ^ J), J = 1, 2, 4 .. 32, by lane permutations within
+// the vector ALU (through the LDS a general shuffle waits for its round trip).
+template <int J>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
+    auto dpp = [](uint32_t x, auto ctrl) __attribute__((always_inline)) {
+        return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    if constexpr (J == 1) {
+        return dpp(v, std::integral_constant<int, 0xB1>{});        // quad_perm 1 0 3 2
+    } else if constexpr (J == 2) {
+        return dpp(v, std::integral_constant<int, 0x4E>{});        // quad_perm 2 3 0 1
+    } else if constexpr (J == 4) {                                 // ^7 (row_half_mirror), then ^3 (quad_perm 3 2 1 0)
+        return dpp(dpp(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+    } else if constexpr (J == 8) {
+        return dpp(v, std::integral_constant<int, 0x128>{});       // row_ror:8
+    } else if constexpr (J == 16) {   // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+        const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return lane_id() & 16 ? q[0] : q[1];
+    } else {                          // halves (lo, lo) and (hi, hi)
+        static_assert(J == 32);
+        const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return lane_id() & 32 ? q[0] : q[1];
+    }
+}
+template <int J>
+__device__ __forceinline__ uint64_t xor_lane(uint64_t v) {
+    const uint32_t lo = xor_lane<J>(static_cast<uint32_t>(v)), hi = xor_lane<J>(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
+// Bitonic sort of up to 64 R W entries by W waves, held in registers: entry e =
+// 64 R w + 64 r + lane is register r of its lane in wave w (the slots past n
+// hold the largest key and stay at the end). A compare-exchange at distance j
+// pairs e with e ^ j: between lanes for j < 64, between two registers of one
+// lane for 64 <= j < 64 R, between two waves, through the LDS, for the three
+// steps at j >= 64 R of four waves. Entry e keeps the smaller key when it is
 // the lower of its pair in an ascending run (e & k == 0) or the upper of its
 // pair in a descending one.
-template <int R>
-__device__ __forceinline__ void wave_bitonic_sort(uint64_t* __restrict__ list, int n) {
-    const int lane = lane_id();
-    constexpr int N = 64 * R;
+template <int R, int J>
+__device__ __forceinline__ void exchange_lanes(uint64_t (&v)[R], int e0, int k) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = e0 + 64 * r;
+        const uint64_t a = v[r], b = xor_lane<J>(a);
+        const bool keep_min = ((e & J) == 0) == ((e & k) == 0);
+        v[r] = (a < b) == keep_min ? a : b;
+    }
+}
+template <int R, int W>
+__device__ __forceinline__ void bitonic_sort(uint64_t* __restrict__ list, int n, int w, uint64_t* __restrict__ s) {
+    const int lane = lane_id(), e0 = 64 * R * w + lane;
+    constexpr int N = 64 * R * W;
     uint64_t v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = 64 * r + lane < n ? list[64 * r + lane] : kBgKey;
+    for (int r = 0; r < R; ++r) v[r] = e0 + 64 * r < n ? list[e0 + 64 * r] : kBgKey;
 #pragma unroll
     for (int k = 2; k <= N; k <<= 1) {
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            if (j >= 64) {
+        for (int j = k >> 1; j >= 64; j >>= 1) {
+            if (j >= 64 * R) {
+                __syncthreads();   // the last exchange's reads are done
+#pragma unroll
+                for (int r = 0; r < R; ++r) s[e0 + 64 * r] = v[r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int e = e0 + 64 * r;
+                    const uint64_t a = v[r], b = s[e ^ j];
+                    const bool keep_min = ((e & j) == 0) == ((e & k) == 0);
+                    v[r] = (a < b) == keep_min ? a : b;
+                }
+            } else {
                 const int jr = j >> 6;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     if (r & jr) continue;   // the pair (r, r + jr), seen from its lower register
-                    const int e = 64 * r + lane;
                     const uint64_t a = v[r], b = v[r | jr];
-                    const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-                    const bool up = (e & k) == 0;
-                    v[r] = up ? lo : hi;
-                    v[r | jr] = up ? hi : lo;
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int e = 64 * r + lane;
-                    const uint64_t b = static_cast<uint64_t>(__shfl_xor(static_cast<long long>(v[r]), j, 64));
-                    const bool keep_min = ((e & j) == 0) == ((e & k) == 0);
-                    const uint64_t a = v[r];
-                    v[r] = keep_min ? (a < b ? a : b) : (a < b ? b : a);
+                    const bool up = ((e0 + 64 * r) & k) == 0, swap = (a < b) != up;
+                    v[r] = swap ? b : a;
+                    v[r | jr] = swap ? a : b;
                 }
             }
         }
+        if (k > 32) exchange_lanes<R, 32>(v, e0, k);
+        if (k > 16) exchange_lanes<R, 16>(v, e0, k);
+        if (k > 8) exchange_lanes<R, 8>(v, e0, k);
+        if (k > 4) exchange_lanes<R, 4>(v, e0, k);
+        if (k > 2) exchange_lanes<R, 2>(v, e0, k);
+        exchange_lanes<R, 1>(v, e0, k);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
-        if (64 * r + lane < n) list[64 * r + lane] = v[r];
+        if (e0 + 64 * r < n) list[e0 + 64 * r] = v[r];
 }
 
 constexpr int kWaveSortMax = 256;   // longest list sorted by one wave
@@ -361,9 +409,14 @@ constexpr int kWaveSortMax = 256;   // longest list sorted by one wave
 // Workgroup b owns tiles b + i * gridDim.x, i = 0..3 (strided, so that the
 // long lists of a crowded screen region spread over many workgroups). A list
 // of at most kWaveSortMax entries is sorted by the wave of its tile;
-// longer lists are then sorted by the whole workgroup, bitonic in LDS, in
-// blocks of kSortBlock.
-__global__ __launch_bounds__(256) void sort_kernel(const int64_t* __restrict__ tile_start, int64_t n_tiles,
+// longer lists are then sorted by the whole workgroup, in blocks of kSortBlock.
+// Both hold the entries in registers and exchange them by lane permutations; a
+// workgroup's waves meet in the LDS three times, where a bitonic sort in it met
+// after each of 66 steps. 64 views of 50,000 triangles: 191 -> 122 us, 200,000
+// triangles 346 -> 192, four training views 51 -> 25. Six waves per SIMD: left
+// to itself the compiler takes 136 registers, and the short lists, which wait
+// on their loads, then take longer than the long ones save (201 us).
+__global__ __launch_bounds__(256, 6) void sort_kernel(const int64_t* __restrict__ tile_start, int64_t n_tiles,
                                                    uint64_t* __restrict__ entries, int64_t cap) {
     __shared__ uint64_t s[kSortBlock];
     const int w = threadIdx.x >> 6;
@@ -374,9 +427,9 @@ __global__ __launch_bounds__(256) void sort_kernel(const int64_t* __restrict__ t
         if (tile < n_tiles) {
             const int64_t beg = tile_start[tile];
             const int n = static_cast<int>(min<int64_t>(tile_start[tile + 1] - beg, kWaveSortMax + 1));
-            if (n > 1 && n <= 64) wave_bitonic_sort<1>(entries + beg, n);
-            else if (n > 64 && n <= 128) wave_bitonic_sort<2>(entries + beg, n);
-            else if (n > 128 && n <= kWaveSortMax) wave_bitonic_sort<4>(entries + beg, n);
+            if (n > 1 && n <= 64) bitonic_sort<1, 1>(entries + beg, n, 0, nullptr);
+            else if (n > 64 && n <= 128) bitonic_sort<2, 1>(entries + beg, n, 0, nullptr);
+            else if (n > 128 && n <= kWaveSortMax) bitonic_sort<4, 1>(entries + beg, n, 0, nullptr);
         }
     }
     for (int i = 0; i < 4; ++i) {
@@ -386,28 +439,18 @@ __global__ __launch_bounds__(256) void sort_kernel(const int64_t* __restrict__ t
         if (end - beg <= kWaveSortMax) continue;
         for (int64_t b0 = beg; b0 < end; b0 += kSortBlock) {
             const int n = static_cast<int>(min<int64_t>(kSortBlock, end - b0));
-            int N = 1;
-            while (N < n) N <<= 1;
-            __syncthreads();
-            for (int j = threadIdx.x; j < N; j += blockDim.x) s[j] = j < n ? entries[b0 + j] : kBgKey;
-            __syncthreads();
-            for (int k = 2; k <= N; k <<= 1) {
-                for (int j = k >> 1; j > 0; j >>= 1) {
-                    // one compare-exchange per thread and step: pair t has its lower
-                    // element at t with a zero bit inserted at j's position
-                    for (int t = threadIdx.x; t < (N >> 1); t += blockDim.x) {
-                        const int x = 2 * t - (t & (j - 1)), xj = x + j;
-                        const uint64_t a = s[x], c = s[xj];
-                        const bool up = (x & k) == 0;
-                        if ((a > c) == up) {
-                            s[x] = c;
-                            s[xj] = a;
-                        }
-                    }
-                    __syncthreads();
-                }
+            uint64_t* const list = entries + b0;
+            if (n <= 64) {   // the last block of a longer list
+                if (w == 0) bitonic_sort<1, 1>(list, n, 0, nullptr);
+            } else if (n <= kWaveSortMax) {
+                if (w == 0) bitonic_sort<4, 1>(list, n, 0, nullptr);
+            } else if (n <= 512) {
+                bitonic_sort<2, 4>(list, n, w, s);
+            } else if (n <= 1024) {
+                bitonic_sort<4, 4>(list, n, w, s);
+            } else {
+                bitonic_sort<8, 4>(list, n, w, s);
             }
-            for (int j = threadIdx.x; j < n; j += blockDim.x) entries[b0 + j] = s[j];
         }
     }
 }
