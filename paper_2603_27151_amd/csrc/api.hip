@@ -1240,7 +1240,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     ZeroList z;
     z.add(c->gvert.p, static_cast<int64_t>(T) * 18);
     if (fused) {
-        if (!o.accumulate)
+        if (!o.accumulate && T > 0)   // (an empty soup's array of levels may be NULL)
             for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l)
                 z.add(lv->graw[l], static_cast<int64_t>(T) * mc_count(lv->Rmin + l) * kPCh);
     } else if (!o.accumulate || lv) {   // the workspace starts from zero
@@ -1271,7 +1271,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
             ta.levels = 1;
             ta.Rmin = lv->Rmin;
             ta.Rtop = lv->Rtop;
-            for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l) ta.graw[l] = lv->graw[l];
+            for (int l = 0; T > 0 && l <= lv->Rtop - lv->Rmin; ++l) ta.graw[l] = lv->graw[l];
         }
         ta.gvert = static_cast<double*>(c->gvert.p);
         ta.mlp_partial = static_cast<float*>(c->partial.p);
@@ -1316,7 +1316,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         launch_pwinner_bwd(wa, s);
     }
     HIP_TRY(c, hipGetLastError());
-    if (lv && !fused) {   // the workspace's texture gradient through the assembly's backward
+    if (lv && !fused && T > 0) {   // the workspace's texture gradient through the assembly's backward
         Timed t(c, SOUP_T_ASSEMBLE_BWD, s);
         AssembleArgs aa{};
         for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l) aa.graw[l] = lv->graw[l];
@@ -1327,7 +1327,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         aa.tex = scene->tex;
         aa.grad_tex = grad_tex;
         aa.accumulate = o.accumulate;
-        if (mc_assemble_bwd_lds(aa.Rmin, aa.Rmax) > mc_assemble_bwd_lds_cap(c->lds_limit) && !o.accumulate && T > 0)
+        if (mc_assemble_bwd_lds(aa.Rmin, aa.Rmax) > mc_assemble_bwd_lds_cap(c->lds_limit) && !o.accumulate)
             for (int l = 0; l <= aa.Rtop - aa.Rmin; ++l)
                 launch_fill_f32(aa.graw[l], static_cast<int64_t>(T) * mc_count(aa.Rmin + l) * kPCh, 0.0f, s);
         launch_mc_assemble_bwd(aa, c->lds_limit, s);
@@ -1367,9 +1367,10 @@ soup_status soup_mc_assemble(soup_ctx* c, int32_t T, int32_t Rmin, int32_t Rtop,
     soup_status st;
     if ((st = check_levels(c, T, Rmin, Rtop, Rmax))) return st;
     if (T > 0 && (!raw || !tex)) return fail(c, SOUP_ERR_INVALID, "mc_assemble: NULL buffers");
+    if (T == 0) return SOUP_OK;
     AssembleArgs aa{};
     for (int l = 0; l <= Rtop - Rmin; ++l) {
-        if (T > 0 && !raw[l]) return fail(c, SOUP_ERR_INVALID, "mc_assemble: level %d is NULL", Rmin + l);
+        if (!raw[l]) return fail(c, SOUP_ERR_INVALID, "mc_assemble: level %d is NULL", Rmin + l);
         aa.raw[l] = raw[l];
     }
     aa.Rmin = Rmin;
@@ -1395,9 +1396,10 @@ soup_status soup_mc_assemble_bwd(soup_ctx* c, int32_t T, int32_t Rmin, int32_t R
     if ((st = check_levels(c, T, Rmin, Rtop, Rmax))) return st;
     if (accumulate != 0 && accumulate != 1) return fail(c, SOUP_ERR_INVALID, "accumulate = %d (0 or 1)", accumulate);
     if (T > 0 && (!tex || !grad_tex || !grad_raw)) return fail(c, SOUP_ERR_INVALID, "mc_assemble_bwd: NULL buffers");
+    if (T == 0) return SOUP_OK;
     AssembleArgs aa{};
     for (int l = 0; l <= Rtop - Rmin; ++l) {
-        if (T > 0 && !grad_raw[l]) return fail(c, SOUP_ERR_INVALID, "mc_assemble_bwd: level %d is NULL", Rmin + l);
+        if (!grad_raw[l]) return fail(c, SOUP_ERR_INVALID, "mc_assemble_bwd: level %d is NULL", Rmin + l);
         aa.graw[l] = grad_raw[l];
     }
     aa.Rmin = Rmin;
@@ -1411,7 +1413,7 @@ soup_status soup_mc_assemble_bwd(soup_ctx* c, int32_t T, int32_t Rmin, int32_t R
     hipStream_t s = static_cast<hipStream_t>(stream);
     {
         Timed t(c, SOUP_T_ASSEMBLE_BWD, s);
-        if (mc_assemble_bwd_lds(Rmin, Rmax) > mc_assemble_bwd_lds_cap(c->lds_limit) && !accumulate && T > 0)
+        if (mc_assemble_bwd_lds(Rmin, Rmax) > mc_assemble_bwd_lds_cap(c->lds_limit) && !accumulate)
             for (int l = 0; l <= Rtop - Rmin; ++l)
                 launch_fill_f32(grad_raw[l], static_cast<int64_t>(T) * mc_count(Rmin + l) * kPCh, 0.0f, s);
         launch_mc_assemble_bwd(aa, c->lds_limit, s);

@@ -61,3 +61,26 @@ def test_paper_form(R, levels, accumulate):
             ctx, scene, views, minv, opts, vis, col, gc, gl, levels[0], None, [None] * (levels[1] - levels[0] + 1), gm)
     _call(accumulate, _lib.PMLP_PARAMS, fwd, bwd)
     ctx.close()
+
+
+@pytest.mark.parametrize("R,Rmin,Rtop", [(5, 2, 4), (6, 2, 4)])
+def test_no_level_arrays(R, Rmin, Rtop):
+    """... and the host arrays of its levels may be NULL."""
+    from paper_2603_27151_amd import _lib, raster
+    ctx, h = _lib.Ctx(torch.cuda.current_device()), _lib._Holder()
+    vs = raster.Views.from_list(VIEWS)
+    views, minv = vs.c_struct(h), h.arr(raster.inv_view_proj(vs), C.c_float)
+    opts = _lib.make_opts(background=(0.1, 0.2, 0.3))
+    scene = _lib.soup_pscene(0, R, None, None, None)
+    s, L, p = _lib._stream(None), _lib.lib(), _lib._ptr
+    minv = C.cast(minv, C.c_void_p)
+
+    def bwd(vis, col, gc, gl, gm):
+        ctx.check(L.soup_pbackward_levels(ctx.p, C.byref(scene), C.byref(views), minv, C.byref(opts), p(vis), p(col),
+                                          p(gc), p(gl), Rmin, Rtop, None, None, p(gm), s))
+
+    _call(0, _lib.PMLP_PARAMS, lambda vis, col, logp: ctx.check(L.soup_pforward(
+        ctx.p, C.byref(scene), C.byref(views), minv, C.byref(opts), p(vis), p(col), p(logp), s)), bwd)
+    ctx.check(L.soup_mc_assemble(ctx.p, 0, Rmin, Rtop, R, None, None, s))
+    ctx.check(L.soup_mc_assemble_bwd(ctx.p, 0, Rmin, Rtop, R, None, None, None, 0, s))
+    ctx.close()
