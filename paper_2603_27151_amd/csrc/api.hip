@@ -256,6 +256,14 @@ soup_status check_opts(soup_ctx* c, const soup_opts* o) {
     return SOUP_OK;
 }
 
+// A fragment log holds a pixel's index in 32 bits.
+constexpr int64_t kMaxLogPixels = int64_t(1) << 32;
+
+soup_status check_log_pixels(soup_ctx* c, const char* what, int64_t n_pix) {
+    if (n_pix >= kMaxLogPixels) return fail(c, SOUP_ERR_CAPACITY, "%s needs fewer than 2^32 pixels per call", what);
+    return SOUP_OK;
+}
+
 Opts to_opts(const soup_opts* o) {
     Opts r{};
     r.seed = o->seed;
@@ -857,7 +865,7 @@ soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const ui
                              const float* grad_logp, const float2* edge_w, int T, bool from_log, ZeroList& z,
                              hipStream_t s) {
     soup_status st;
-    if (p.n_pix >= (int64_t(1) << 32)) return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
+    if ((st = check_log_pixels(c, "backward", p.n_pix))) return st;
     if (!from_log && (st = replay(c, p, o, vis, grad_color, grad_logp, edge_w, false, s))) return st;
     const soup_ctx::FragLog& g = from_log ? c->flog : c->rlog;
     const FragLogView L = log_view(g);
@@ -946,6 +954,7 @@ soup_status soup_rasterize_fwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = plan_single(c, p, scene, views))) return st;
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color) return fail(c, SOUP_ERR_INVALID, "vis and color outputs are required");
+    if (logp && opts->mode == 0 && (st = check_log_pixels(c, "log p", p.n_pix))) return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     if ((st = bin(c, p, o, true, s))) return st;
@@ -1112,6 +1121,7 @@ soup_status soup_pforward(soup_ctx* c, const soup_pscene* scene, const soup_view
     if ((st = plan_paper(c, p, scene, views, inv_view_proj))) return st;
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color) return fail(c, SOUP_ERR_INVALID, "vis and color outputs are required");
+    if (logp && opts->mode == 0 && (st = check_log_pixels(c, "log p", p.n_pix))) return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     if ((st = bin(c, p, o, true, s))) return st;
@@ -1284,8 +1294,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         }
         if (gl) {
             // the score term (Eq. (9)): every fragment in front of a winner, and the winner
-            if (p.n_pix >= (int64_t(1) << 32))
-                return fail(c, SOUP_ERR_CAPACITY, "backward needs fewer than 2^32 pixels per call");
+            if ((st = check_log_pixels(c, "backward", p.n_pix))) return st;
             if (!from_log && (st = replay(c, p, o, vis, grad_color, gl, nullptr, false, s))) return st;
             Timed t(c, SOUP_T_GRAD, s);
             PFragArgs fa{};
