@@ -334,8 +334,10 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, bool forward, hipStream_t s
     const int chunk = bin_chunk_size(static_cast<int>(p.views.size()), p.maxT, c->num_cus);
     const int stride = bin_stride(chunk, p.n_tiles);
     soup_status st;
-    // the forward counts its regions in 32 bits
-    if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >= (int64_t(1) << 32))
+    // the forward counts its regions in 32 bits, a wave adds its grid to an index, and every wave fetches
+    // one index past the last
+    if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >=
+        (int64_t(1) << 32) - kMaxRegions - 2 * static_cast<int64_t>(kWorkCounters))
         return fail(c, SOUP_ERR_CAPACITY, "too many pixels in one call (2^32 forward regions)");
     if ((st = ensure(c, c->views, vbytes + sbytes)) ||
         (st = ensure(c, c->recs, static_cast<size_t>(p.n_recs) * sizeof(TriRec))) ||

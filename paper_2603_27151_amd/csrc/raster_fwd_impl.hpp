@@ -178,7 +178,7 @@ __global__ __launch_bounds__(64, S::H >= 64 ? 2 : 3) void raster_fwd_kernel(Rast
     for (;;) {
     const uint64_t item = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(next)));
     if (item >= n_items) break;
-    // (the sums stay below 2^32: checked on the host)
+    // (the sums stay below 2^32, also of the indices past the last: checked on the host)
     if (static_cast<uint32_t>(item) + gridDim.x < a.fixed) next = static_cast<uint32_t>(item) + gridDim.x;
     else if (lane == 0) next = a.fixed + atomicAdd(a.work + kWorkStride * wc, 1u) * kWorkCounters + wc;   // fetched while this one runs
     const uint32_t tile = static_cast<uint32_t>(item / RPT);

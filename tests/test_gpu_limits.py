@@ -1,5 +1,5 @@
 """Calls of more pixels than a kernel's 32-bit indices hold are refused before any work: the pixels of a
-fragment log (log p). Only the refusal is exercised: nothing is launched, and the output buffers are stand-ins."""
+fragment log (log p), and the regions that the forward's waves take, with what the waves add to them. Only the refusal is exercised: nothing is launched, and the output buffers are stand-ins."""
 import ctypes as C
 
 import numpy as np
@@ -33,5 +33,23 @@ def test_log_p_of_too_many_pixels(paper):
                                out, out, out)
         else:
             _lib.soup_rasterize_fwd(ctx, _empty_scene(_lib, h), views, opts, out, out, out)
+    assert e.value.status == 3 and ctx.workspace_bytes() == before
+    ctx.close()
+
+
+@pytest.mark.parametrize("last", [(16384, 16384), (16384, 16376), (16384, 16361)])
+def test_too_many_regions(last):
+    """8-pixel tiles: 2^32 regions and up to some thousand fewer."""
+    from paper_2603_27151_amd import _lib
+    ctx, h = _lib.Ctx(torch.cuda.current_device()), _lib._Holder()
+    ctx.set_tile(8)
+    sizes = [(16384, 16384)] * 1023 + [last]
+    n = sum(((w + 7) // 8) * ((hh + 7) // 8) for w, hh in sizes)
+    assert (1 << 32) - 4112 <= n <= 1 << 32
+    out = torch.zeros(4, dtype=torch.int64, device="cuda")
+    before = ctx.workspace_bytes()
+    with pytest.raises(_lib.SoupError, match="regions") as e:
+        _lib.soup_render(ctx, [_empty_scene(_lib, h)] * len(sizes), _views(_lib, h, sizes), _lib.make_opts(mode=1),
+                         [out] * len(sizes))
     assert e.value.status == 3 and ctx.workspace_bytes() == before
     ctx.close()
