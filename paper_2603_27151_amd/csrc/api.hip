@@ -1442,7 +1442,7 @@ soup_status soup_loss_l2(soup_ctx* c, const float* color, const float* target, i
     HIP_TRY(c, hipSetDevice(c->device));
     {
         Timed t(c, SOUP_T_LOSS, static_cast<hipStream_t>(stream));
-        launch_loss_l2(color, target, P, grad_color, grad_logp, loss, static_cast<double*>(c->sum.p), static_cast<hipStream_t>(stream));
+        launch_loss_l2(color, target, P, grad_color, grad_logp, loss, static_cast<hipStream_t>(stream));
     }
     HIP_TRY(c, hipGetLastError());
     return SOUP_OK;

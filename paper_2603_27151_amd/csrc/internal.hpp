@@ -224,7 +224,7 @@ void launch_edge_weights(const ViewDesc* views, int V, int64_t P, const Opts& o,
                          const float* color, const float* grad_color, float2* ew, hipStream_t s);
 void launch_mlp_reduce(const float* partial, int n_rows, int n_params, float* out, bool accumulate, hipStream_t s);
 void launch_loss_l2(const float* color, const float* target, int64_t P, float* gc, float* gl, float* loss,
-                    double* parts, hipStream_t s);
+                    hipStream_t s);
 void launch_selftest_sigmoid(const float* x, float* y, int64_t n, hipStream_t s);
 void launch_selftest_uniform(uint64_t seed, const uint32_t* pixel, const uint32_t* tri, uint32_t view_id,
                              uint32_t step, float* u, int64_t n, hipStream_t s);

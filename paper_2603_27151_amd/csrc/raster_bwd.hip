@@ -156,20 +156,35 @@ void launch_mlp_reduce(const float* partial, int n_rows, int n_params, float* ou
 // ---------------------------------------------------------------------------
 
 // Per pixel: d = colour - target, g_C = 2 d / (3P), g_L = |d|^2 / (3P) (its
-// share of the mean), loss += g_L. Four pixels (48 bytes of each input) per
-// thread and step with 16-byte loads and stores when every array is 16-byte
-// aligned; the pixels past the last group of four (and unaligned arrays) one
-// at a time.
+// share of the mean); the loss is the sum of the shares, in double. The first
+// `head` pixels are left to the second launch, and each workgroup leaves its sum
+// in their share array (two words each): the call needs no memory but the
+// caller's, so that calls on several streams have nothing in common. Four pixels
+// (48 bytes of each input) per thread and step with 16-byte loads and stores when
+// every array is 16-byte aligned; the pixels past the last group of four (and
+// unaligned arrays) one at a time.
+__device__ __forceinline__ float loss_l2_pixel(const float* c, const float* t, float inv, float* g) {
+    float sq = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float d = c[k] - t[k];
+        g[k] = 2.0f * d * inv;
+        sq = __builtin_fmaf(d, d, sq);
+    }
+    return sq * inv;
+}
+__device__ __forceinline__ float loss_l2_inv(int64_t P) { return 1.0f / (3.0f * static_cast<float>(P)); }
+
 __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ color, const float* __restrict__ target,
-                                                      int64_t P, float* __restrict__ gc, float* __restrict__ gl,
-                                                      double* __restrict__ parts, int vec4) {
+                                                      int64_t P, int head, float* __restrict__ gc,
+                                                      float* __restrict__ gl, int vec4) {
     __shared__ double red[4];
-    const float inv = 1.0f / (3.0f * static_cast<float>(P));
+    const float inv = loss_l2_inv(P);
     double part = 0.0;   // (a float32 sum with one atomic per workgroup was up to 2e-6 off)
     const int64_t tid = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    const int64_t P4 = vec4 ? P / 4 : 0;
-    for (int64_t q = tid; q < P4; q += stride) {
+    const int64_t P4 = vec4 ? P / 4 : head / 4;   // groups of four before the single pixels (head: a multiple of four)
+    for (int64_t q = head / 4 + tid; q < P4; q += stride) {
         const float4* c4 = reinterpret_cast<const float4*>(color) + 3 * q;
         const float4* t4 = reinterpret_cast<const float4*>(target) + 3 * q;
         const float4 a0 = c4[0], a1 = c4[1], a2 = c4[2];
@@ -179,14 +194,7 @@ __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ 
         float g[12], l[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            float sq = 0.0f;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float d = cv[3 * k + c] - tv[3 * k + c];
-                g[3 * k + c] = 2.0f * d * inv;
-                sq = __builtin_fmaf(d, d, sq);
-            }
-            l[k] = sq * inv;
+            l[k] = loss_l2_pixel(cv + 3 * k, tv + 3 * k, inv, g + 3 * k);
             part += static_cast<double>(l[k]);
         }
         float4* g4 = reinterpret_cast<float4*>(gc) + 3 * q;
@@ -196,37 +204,93 @@ __global__ __launch_bounds__(256) void loss_l2_kernel(const float* __restrict__ 
         reinterpret_cast<float4*>(gl)[q] = make_float4(l[0], l[1], l[2], l[3]);
     }
     for (int64_t p = 4 * P4 + tid; p < P; p += stride) {
-        float sq = 0.0f;
+        float g[3];
+        const float l = loss_l2_pixel(color + 3 * p, target + 3 * p, inv, g);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const float d = color[3 * p + c] - target[3 * p + c];
-            gc[3 * p + c] = 2.0f * d * inv;
-            sq = __builtin_fmaf(d, d, sq);
-        }
-        gl[p] = sq * inv;
-        part += static_cast<double>(sq * inv);
+        for (int k = 0; k < 3; ++k) gc[3 * p + k] = g[k];
+        gl[p] = l;
+        part += static_cast<double>(l);
     }
-    if (parts) {   // the workgroup's sum in double
+    if (head > 0) {   // the workgroup's sum in double
         double sum = part;
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
         __syncthreads();
-        if (threadIdx.x == 0) parts[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+        if (threadIdx.x == 0) {
+            const uint64_t v = __double_as_longlong((red[0] + red[1]) + (red[2] + red[3]));
+            gl[2 * blockIdx.x] = __uint_as_float(static_cast<uint32_t>(v));
+            gl[2 * blockIdx.x + 1] = __uint_as_float(static_cast<uint32_t>(v >> 32));
+        }
+    }
+}
+
+// The first `head` pixels, and the loss: their shares and the n_parts sums of the first launch, added
+// in a fixed order. One workgroup.
+constexpr int kL2Head = 2 * kSumParts;
+__global__ __launch_bounds__(1024) void loss_l2_head_kernel(const float* __restrict__ color,
+                                                            const float* __restrict__ target, int64_t P, int head,
+                                                            int n_parts, float* __restrict__ gc,
+                                                            float* __restrict__ gl, float* __restrict__ loss) {
+    constexpr int N = kL2Head / 1024;
+    __shared__ double red[16];
+    const int tid = threadIdx.x;
+    const float inv = loss_l2_inv(P);
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSumParts / 1024; ++i) {
+        const int k = i * 1024 + tid;
+        if (k < n_parts) {
+            const uint64_t lo = __float_as_uint(gl[2 * k]), hi = __float_as_uint(gl[2 * k + 1]);
+            sum += __longlong_as_double(static_cast<long long>((hi << 32) | lo));
+        }
+    }
+    float g[N][3], l[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int p = i * 1024 + tid;
+        l[i] = 0.0f;
+        if (p < head) l[i] = loss_l2_pixel(color + 3 * p, target + 3 * p, inv, g[i]);
+        sum += static_cast<double>(l[i]);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = sum;
+    __syncthreads();   // every part has been read
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int p = i * 1024 + tid;
+        if (p < head) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) gc[3 * p + k] = g[i][k];
+            gl[p] = l[i];
+        }
+    }
+    if (tid == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += red[i];
+        *loss = static_cast<float>(s);
     }
 }
 
 void launch_loss_l2(const float* color, const float* target, int64_t P, float* gc, float* gl, float* loss,
-                    double* parts, hipStream_t s) {
+                    hipStream_t s) {
     if (P <= 0) return;
     const uintptr_t al = reinterpret_cast<uintptr_t>(color) | reinterpret_cast<uintptr_t>(target) |
                          reinterpret_cast<uintptr_t>(gc) | reinterpret_cast<uintptr_t>(gl);
     const int vec4 = (al & 15) == 0 ? 1 : 0;
     int64_t g = ((vec4 ? (P + 3) / 4 : P) + 255) / 256;
     if (g > kSumParts) g = kSumParts;
-    hipLaunchKernelGGL(loss_l2_kernel, dim3(static_cast<unsigned>(g)), dim3(256), 0, s, color, target, P, gc, gl,
-                       loss ? parts : nullptr, vec4);
-    if (loss) launch_sum_parts(parts, static_cast<int>(g), 0, loss, s);
+    // two words of the head's shares per workgroup; a call no larger than the largest head is its head
+    const bool all = P <= kL2Head;
+    const int head = !loss ? 0 : all ? static_cast<int>(P) : static_cast<int>((2 * g + 3) / 4 * 4);
+    if (!loss || !all)
+        hipLaunchKernelGGL(loss_l2_kernel, dim3(static_cast<unsigned>(g)), dim3(256), 0, s, color, target, P, head, gc,
+                           gl, vec4);
+    if (loss)
+        hipLaunchKernelGGL(loss_l2_head_kernel, dim3(1), dim3(1024), 0, s, color, target, P, head,
+                           all ? 0 : static_cast<int>(g), gc, gl, loss);
 }
 
 // out = (add: the value there +) the parts, added in a fixed order.
