@@ -860,6 +860,14 @@ soup_status replay(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vi
     return fail(c, SOUP_ERR_CAPACITY, "fragment log overflowed twice");
 }
 
+// Backward of an empty soup: no fragments, and a zero gradient of the MLP. (The kernels of the
+// fragment list read the parameters, which such a soup may not have, before their first fragment.)
+soup_status empty_backward(soup_ctx* c, float* grad_mlp, int n_params, const Opts& o, hipStream_t s) {
+    if (!o.accumulate) launch_fill_f32(grad_mlp, n_params, 0.0f, s);
+    HIP_TRY(c, hipGetLastError());
+    return finish_stats(c, s, false);
+}
+
 // Backward, part 1: the fragments the backward needs, from the forward's log or a walk, sorted by
 // triangle into c->sorted, with c->tri_off the triangles' ranges. z: what else the backward needs
 // cleared before its decode.
@@ -867,7 +875,6 @@ soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const ui
                              const float* grad_logp, const float2* edge_w, int T, bool from_log, ZeroList& z,
                              hipStream_t s) {
     soup_status st;
-    if ((st = check_log_pixels(c, "backward", p.n_pix))) return st;
     if (!from_log && (st = replay(c, p, o, vis, grad_color, grad_logp, edge_w, false, s))) return st;
     const soup_ctx::FragLog& g = from_log ? c->flog : c->rlog;
     const FragLogView L = log_view(g);
@@ -1001,7 +1008,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color || !grad_color) return fail(c, SOUP_ERR_INVALID, "vis, color and grad_color are required");
     if (!grad_verts || !grad_feats || !grad_mlp) return fail(c, SOUP_ERR_INVALID, "gradient outputs are required");
-    if ((st = check_decode_lds(c, p.kind, p.G))) return st;
+    if ((st = check_decode_lds(c, p.kind, p.G)) || (st = check_log_pixels(c, "backward", p.n_pix))) return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     bool reused = false;
@@ -1014,6 +1021,7 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
         return st;
     }
     const int T = scene->T;
+    if (T == 0) return empty_backward(c, grad_mlp, p.n_params, o, s);
     const int64_t n_grid = static_cast<int64_t>(scene->G) * scene->G * scene->C;
     if ((st = ensure(c, c->edge_w, static_cast<size_t>(p.n_pix) * sizeof(float2))) ||
         (st = ensure(c, c->partial, static_cast<size_t>(decode_blocks(c, -1)) * 4 * p.n_params * 4)))
@@ -1206,6 +1214,9 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
                 if (!lv->graw[l]) return fail(c, SOUP_ERR_INVALID, "grad_raw[%d] (level %d) is NULL", l, lv->Rmin + l);
         }
     }
+    // (the per-pixel path takes its score term alone from a log)
+    if ((ptri_sorted(scene->R) || (grad_logp && opts->mode == 0)) && (st = check_log_pixels(c, "backward", p.n_pix)))
+        return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     bool reused = false;
@@ -1217,6 +1228,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         return st;
     }
     const int T = scene->T;
+    if (T == 0) return empty_backward(c, grad_mlp, kPParams, o, s);
     const int64_t n_tex = static_cast<int64_t>(T) * mc_count(scene->R) * kPCh;
     // the triangle-sorted path keeps one triangle's texture gradient per wave in LDS
     // (36 KB at R = 5, with the levels' restriction 10); a texture too large for that
@@ -1252,7 +1264,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     ZeroList z;
     z.add(c->gvert.p, static_cast<int64_t>(T) * 18);
     if (fused) {
-        if (!o.accumulate && T > 0)   // (an empty soup's array of levels may be NULL)
+        if (!o.accumulate)
             for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l)
                 z.add(lv->graw[l], static_cast<int64_t>(T) * mc_count(lv->Rmin + l) * kPCh);
     } else if (!o.accumulate || lv) {   // the workspace starts from zero
@@ -1283,7 +1295,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
             ta.levels = 1;
             ta.Rmin = lv->Rmin;
             ta.Rtop = lv->Rtop;
-            for (int l = 0; T > 0 && l <= lv->Rtop - lv->Rmin; ++l) ta.graw[l] = lv->graw[l];
+            for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l) ta.graw[l] = lv->graw[l];
         }
         ta.gvert = static_cast<double*>(c->gvert.p);
         ta.mlp_partial = static_cast<float*>(c->partial.p);
@@ -1296,7 +1308,6 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         }
         if (gl) {
             // the score term (Eq. (9)): every fragment in front of a winner, and the winner
-            if ((st = check_log_pixels(c, "backward", p.n_pix))) return st;
             if (!from_log && (st = replay(c, p, o, vis, grad_color, gl, nullptr, false, s))) return st;
             Timed t(c, SOUP_T_GRAD, s);
             PFragArgs fa{};
@@ -1327,7 +1338,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         launch_pwinner_bwd(wa, s);
     }
     HIP_TRY(c, hipGetLastError());
-    if (lv && !fused && T > 0) {   // the workspace's texture gradient through the assembly's backward
+    if (lv && !fused) {   // the workspace's texture gradient through the assembly's backward
         Timed t(c, SOUP_T_ASSEMBLE_BWD, s);
         AssembleArgs aa{};
         for (int l = 0; l <= lv->Rtop - lv->Rmin; ++l) aa.graw[l] = lv->graw[l];

@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     acc.l0.zero();
     if constexpr (S::NH == 2) acc.mid[0].zero();
     acc.out.zero();
-    if (a.T > 0) s_w.load(a.mlp, tid, blockDim.x);   // an empty soup may have no parameters, and has no fragments
+    s_w.load(a.mlp, tid, blockDim.x);
     __syncthreads();
     const uint64_t n_waves = static_cast<uint64_t>(gridDim.x) * NW;
     const uint64_t wid = static_cast<uint64_t>(blockIdx.x) * NW + w;

@@ -955,7 +955,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void pt
         }
     }
     PMlp mlp;
-    if (a.T > 0) mlp.load(a.mlp, lane);   // an empty soup may have no parameters, and has no fragments
+    mlp.load(a.mlp, lane);
     const float inf = opaque_inf();
     gfloat* tex = as_global(a.tex);
     const int64_t E = a.tri_off[a.T];

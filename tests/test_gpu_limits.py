@@ -1,5 +1,5 @@
 """Calls of more pixels than a kernel's 32-bit indices hold are refused before any work: the pixels of a
-fragment log (log p), and the regions that the forward's waves take, with what the waves add to them. Only the refusal is exercised: nothing is launched, and the output buffers are stand-ins."""
+fragment log (log p, the backwards), and the regions that the forward's waves take, with what the waves add to them. Only the refusal is exercised: nothing is launched, and the output buffers are stand-ins."""
 import ctypes as C
 
 import numpy as np
@@ -33,6 +33,23 @@ def test_log_p_of_too_many_pixels(paper):
                                out, out, out)
         else:
             _lib.soup_rasterize_fwd(ctx, _empty_scene(_lib, h), views, opts, out, out, out)
+    assert e.value.status == 3 and ctx.workspace_bytes() == before
+    ctx.close()
+
+
+@pytest.mark.parametrize("R", [None, 5, 6])   # the grid form; the paper form sorted and per pixel
+def test_backward_of_too_many_pixels(R):
+    from paper_2603_27151_amd import _lib
+    ctx, h = _lib.Ctx(torch.cuda.current_device()), _lib._Holder()
+    views = _views(_lib, h, [(16384, 16384)] * 16)
+    out = torch.zeros(4, dtype=torch.int64, device="cuda")
+    before = ctx.workspace_bytes()
+    with pytest.raises(_lib.SoupError, match="2\\^32 pixels") as e:
+        if R is None:
+            _lib.soup_rasterize_bwd(ctx, _empty_scene(_lib, h), views, _lib.make_opts(), *[out] * 7)
+        else:
+            _lib.soup_pbackward(ctx, _lib.soup_pscene(0, R, None, None, None), views, np.tile(np.eye(4), (16, 1, 1)),
+                                _lib.make_opts(), *[out] * 7)
     assert e.value.status == 3 and ctx.workspace_bytes() == before
     ctx.close()
 
