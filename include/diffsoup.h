@@ -425,7 +425,8 @@ soup_status soup_mc_assemble_bwd(soup_ctx* ctx, int32_t T, int32_t Rmin, int32_t
  *                      sum to L (the score term's per-pixel loss);
  *   loss (device scalar, may be NULL) = L (summed in double, in a fixed order).
  * Uses a context workspace of 48 bytes per pixel of the largest view, or of as
- * many views as 4 Mpixel hold where that is more (they share launches). */
+ * many views as 4 Mpixel hold where that is more and to be had (they share
+ * launches). */
 soup_status soup_loss_l1_ssim(soup_ctx* ctx, const float* color, const float* target, const soup_views* views,
                               float lambda, float* grad_color, float* grad_logp, float* loss, void* stream);
 

@@ -1628,9 +1628,18 @@ soup_status soup_loss_l1_ssim(soup_ctx* c, const float* color, const float* targ
     soup_status st = check_loss_l1_ssim(c, color, target, v, lambda, grad_color, grad_logp, &P, &maxp);
     if (st != SOUP_OK) return st;
     HIP_TRY(c, hipSetDevice(c->device));
-    // records for the largest view, or for as many views as 4 Mpixel hold (192 MB) where that is more
-    const int64_t stat_pixels = std::max(maxp, std::min<int64_t>(P, int64_t(1) << 22));
-    if ((st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * 12 * sizeof(float)))) return st;
+    // records for the largest view, or for as many views as 4 Mpixel hold (192 MB) where that is more; where
+    // that is not to be had (static mode, memory) the views share fewer launches
+    constexpr size_t kRecord = 12 * sizeof(float);
+    int64_t stat_pixels = std::max(maxp, std::min<int64_t>(P, int64_t(1) << 22));
+    if (c->fixed) stat_pixels = std::max(maxp, std::min(stat_pixels, static_cast<int64_t>(c->ssim.bytes / kRecord)));
+    st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * kRecord);
+    if (st == SOUP_ERR_OOM && stat_pixels > maxp) {
+        stat_pixels = maxp;
+        c->err.clear();
+        st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * kRecord);
+    }
+    if (st) return st;
     loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P, static_cast<float*>(c->ssim.p),
                         stat_pixels, static_cast<double*>(c->sum.p), true, static_cast<hipStream_t>(stream));
     HIP_TRY(c, hipGetLastError());
