@@ -68,7 +68,7 @@ struct soup_ctx {
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
     DevBuf tri_count, tri_fill, tri_off, tri_bsum, sorted, flags;
     DevBuf ssim;                                      // SSIM statistics of the training loss
-    DevBuf sum;                                       // the losses' parts (one double per workgroup)
+    DevBuf sum;                                       // the training loss's parts (one double per workgroup) and running total
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
     DevBuf gtex;                                      // its texture gradient when levels are asked for and the sorted path cannot fold them in
     void* host_stage = nullptr;      // pinned: descriptors up, totals down
@@ -560,8 +560,8 @@ namespace {
 // device, kept in noalloc_scratch_ptr.
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 constexpr int kNoAllocMaxDevices = 64;
-// ... and behind it the loss's parts
-static __device__ __align__(256) float scratch[kNoAllocScratchBytes / sizeof(float) + 2 * kSumParts];
+// ... and behind it the loss's parts and running total
+static __device__ __align__(256) float scratch[kNoAllocScratchBytes / sizeof(float) + 2 * (kSumParts + 1)];
 
 std::mutex noalloc_scratch_mu;
 float* noalloc_scratch_ptr[kNoAllocMaxDevices] = {};
@@ -613,8 +613,7 @@ soup_status soup_ctx_create(soup_ctx** out, int device) {
     // error messages are formatted into a 512-byte buffer: with this capacity in
     // place, reporting one allocates no memory
     c->err.reserve(512);
-    // the losses' parts: allocated here, so that a loss allocates nothing
-    c->sum.bytes = kSumParts * sizeof(double);
+    c->sum.bytes = (kSumParts + 1) * sizeof(double);
     if (noalloc_scratch_setup(c) != SOUP_OK || hipMalloc(&c->sum.p, c->sum.bytes) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&c->host_res), 64, hipHostMallocCoherent) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_total, hipEventDisableTiming) != hipSuccess ||
@@ -1608,6 +1607,7 @@ void loss_l1_ssim_launch(soup_ctx* c, const float* color, const float* target, c
             off += np;
             in_batch += np;
         }
+        b.last = 1;
         launch_loss_l1_ssim(b, lambda, inv_n, win, loss, parts, s);
     };
     if (timed) {

@@ -349,9 +349,6 @@ constexpr int kSsimR = 5;  // 11 x 11 window
 struct SsimWindow {
     float g[2 * kSsimR + 1];   // normalised 1-D Gaussian, sigma 1.5; the window is its outer product
 };
-// out = (add: the value there +) parts[0..n), n <= kSumParts, added in a fixed order.
-void launch_sum_parts(const double* parts, int n, int add, float* out, hipStream_t s);
-
 // Views whose loss one pair of launches evaluates (consecutive views of a call).
 constexpr int kSsimViews = 32;
 struct SsimBatch {
@@ -365,8 +362,10 @@ struct SsimBatch {
     int tile[kSsimViews + 1];        // first tile of each view, and their number
     int n;
     int add;                         // 1: the loss of earlier batches is added to
+    int last;                        // 1: no batch follows, the loss goes out
 };
 int ssim_tiles(int W, int H);
+// parts: kSumParts sums and the running total
 void launch_loss_l1_ssim(const SsimBatch& b, float lam, float inv_n, const SsimWindow& win, float* loss,
                          double* parts, hipStream_t s);
 void launch_adam(float* p, const float* g, float* m, float* v, int64_t nvec, int vec, float lr, float b1, float omb1,

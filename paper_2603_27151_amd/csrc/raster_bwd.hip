@@ -293,28 +293,6 @@ void launch_loss_l2(const float* color, const float* target, int64_t P, float* g
                            all ? 0 : static_cast<int>(g), gc, gl, loss);
 }
 
-// out = (add: the value there +) the parts, added in a fixed order.
-__global__ __launch_bounds__(256) void sum_parts_kernel(const double* __restrict__ parts, int n, int add,
-                                                        float* __restrict__ out) {
-    __shared__ double s_sum[4];
-    double v = 0.0;
-#pragma unroll
-    for (int i = 0; i < kSumParts / 256; ++i) {
-        const int k = i * 256 + threadIdx.x;
-        v += k < n ? parts[k] : 0.0;
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        *out = static_cast<float>((add ? static_cast<double>(*out) : 0.0) + ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])));
-}
-
-void launch_sum_parts(const double* parts, int n, int add, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(256), 0, s, parts, n, add, out);
-}
-
 __global__ void selftest_sigmoid_kernel(const float* __restrict__ x, float* __restrict__ y, int64_t n) {
     for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x)

@@ -194,6 +194,28 @@ __global__ void __launch_bounds__(256) ssim_stats_kernel(SsimBatch b, float lam,
     if (threadIdx.x == 0) parts[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
+// The loss from a batch's n parts, added in a fixed order; the total of the batches so far is a double
+// behind them until the last one. One workgroup.
+__global__ void __launch_bounds__(256) loss_sum_kernel(double* __restrict__ parts, int n, int add, int last,
+                                                       float* __restrict__ out) {
+    __shared__ double s_sum[4];
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSumParts / 256; ++i) {
+        const int k = i * 256 + threadIdx.x;
+        v += k < n ? parts[k] : 0.0;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double total = (add ? parts[kSumParts] : 0.0) + ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]));
+        if (last) *out = static_cast<float>(total);
+        else parts[kSumParts] = total;
+    }
+}
+
 __global__ void __launch_bounds__(256) ssim_grad_kernel(SsimBatch b, float lam, float inv_n, SsimWindow win) {
     __shared__ float in[kHH][kHW][9];   // G1, G2, G3 per channel (zero outside the image)
     __shared__ float vs[kTH][9][kHW];   // their column sums
@@ -336,7 +358,8 @@ void launch_loss_l1_ssim(const SsimBatch& b, float lam, float inv_n, const SsimW
     const dim3 g(static_cast<unsigned>(tiles < kSumParts ? tiles : kSumParts));
     hipLaunchKernelGGL(ssim_stats_kernel, g, dim3(kTW * kTH), 0, s, b, lam, inv_n, win,
                        loss ? parts : nullptr);
-    if (loss) launch_sum_parts(parts, static_cast<int>(g.x), b.add, loss, s);
+    if (loss)
+        hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, parts, static_cast<int>(g.x), b.add, b.last, loss);
     hipLaunchKernelGGL(ssim_grad_kernel, g, dim3(kTW * kTH), 0, s, b, lam, inv_n, win);
 }
 
