@@ -738,36 +738,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                 wl[pp] = st + q;
                 dl[pp] = s_dx[w] + k;
             }
-            auto add = [&](int f, const float (&wv)[PPF], const float (&dv)[PPF]) __attribute__((always_inline)) {
-                const int cb = __builtin_amdgcn_readlane(cbase, LPF >= 64 ? f : __builtin_amdgcn_readfirstlane(f));
+            // N fragments from f. The cells are read from their lanes while the whole
+            // wave is active (a lane's register holds its value for certain only where
+            // that lane takes part); lanes past a narrow shape's pairs leave after that.
+            auto add = [&](auto n_steps, int f) __attribute__((always_inline)) {
+                constexpr int N = decltype(n_steps)::value;
+                int cb[N];
 #pragma unroll
-                for (int pp = 0; pp < PPF; ++pp) {
-                    float* gp = gl[pp] + cb;   // one fragment: 64 distinct addresses
-                    *gp = __builtin_fmaf(wv[pp], dv[pp], *gp);
-                }
-            };
-            int f = LPF >= 64 || lane < LPF ? h : end;   // lanes past the pairs have none
-            for (; f + UF <= end; f += UF) {
-                float wv[UF][PPF], dv[UF][PPF];
+                for (int u = 0; u < N; ++u) cb[u] = __builtin_amdgcn_readlane(cbase, f + u);
+                if (LPF < 64 && lane >= LPF) return;
+                float wv[N][PPF], dv[N][PPF];
 #pragma unroll
-                for (int u = 0; u < UF; ++u)
+                for (int u = 0; u < N; ++u)
 #pragma unroll
                     for (int pp = 0; pp < PPF; ++pp) {
                         wv[u][pp] = wl[pp][4 * (f + u)];
                         dv[u][pp] = dl[pp][(f + u) * DXS];
                     }
 #pragma unroll
-                for (int u = 0; u < UF; ++u) add(f + u, wv[u], dv[u]);
-            }
-            for (; f < end; ++f) {
-                float wv[PPF], dv[PPF];
+                for (int u = 0; u < N; ++u)
 #pragma unroll
-                for (int pp = 0; pp < PPF; ++pp) {
-                    wv[pp] = wl[pp][4 * f];
-                    dv[pp] = dl[pp][f * DXS];
-                }
-                add(f, wv, dv);
-            }
+                    for (int pp = 0; pp < PPF; ++pp) {
+                        float* gp = gl[pp] + cb[u];   // one fragment: distinct addresses
+                        *gp = __builtin_fmaf(wv[u][pp], dv[u][pp], *gp);
+                    }
+            };
+            int f = h;
+            for (; f + UF <= end; f += UF) add(std::integral_constant<int, UF>{}, f);
+            for (; f < end; ++f) add(std::integral_constant<int, 1>{}, f);
             wave_fence();
         }
     }
