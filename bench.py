@@ -736,7 +736,7 @@ def main():
                 break   # saturated
         # the same arrivals with a memory budget that fits two of the largest requests
         # (1920x1080 on the 100k-triangle soup), so that admission binds
-        big = max(SV.request_bytes(w, h, sc.T) for w, h in W.SERVING_RES for sc in soups)
+        big = max(SV.request_bytes(w, h, sc.T, sc.n_params()) for w, h in W.SERVING_RES for sc in soups)
         srv_b = SV.Server(soups, tile=None, n_streams=2, max_batch=16, budget_bytes=2 * big)
         srv_b.tile_by_res = dict(srv.tile_by_res)
         SV.run(srv_b, W.serving_requests(200.0, 1.0, seed=98))

@@ -67,8 +67,7 @@ struct soup_ctx {
     DevBuf fwd_weights;  // every scene's MLP weights as the forward's matrix operands
     DevBuf chunk_base;   // [binning chunks][tiles] first slot of a chunk in each tile list
     DevBuf tri_count, tri_fill, tri_off, tri_bsum, sorted, flags;
-    DevBuf ssim;                                      // SSIM statistics of the training loss
-    DevBuf sum;                                       // the training loss's parts (one double per workgroup) and running total
+    DevBuf ssim;                                      // the training loss's parts and running total, then its SSIM statistics
     DevBuf gvert;                                     // the paper form's float64 vertex gradient sums
     DevBuf gtex;                                      // its texture gradient when levels are asked for and the sorted path cannot fold them in
     void* host_stage = nullptr;      // pinned: descriptors up, totals down
@@ -613,8 +612,7 @@ soup_status soup_ctx_create(soup_ctx** out, int device) {
     // error messages are formatted into a 512-byte buffer: with this capacity in
     // place, reporting one allocates no memory
     c->err.reserve(512);
-    c->sum.bytes = (kSumParts + 1) * sizeof(double);
-    if (noalloc_scratch_setup(c) != SOUP_OK || hipMalloc(&c->sum.p, c->sum.bytes) != hipSuccess ||
+    if (noalloc_scratch_setup(c) != SOUP_OK ||
         hipHostMalloc(reinterpret_cast<void**>(&c->host_res), 64, hipHostMallocCoherent) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_total, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_log, hipEventDisableTiming) != hipSuccess) {
@@ -634,7 +632,7 @@ void soup_ctx_destroy(soup_ctx* c) {
                       &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
                       &c->tri_fill,   &c->tri_off,     &c->tri_bsum,     &c->sorted,      &c->flags,
                       &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
-                      &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
+                      &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
@@ -725,7 +723,7 @@ soup_status soup_ctx_workspace_bytes(const soup_ctx* c, int64_t* bytes) {
                             &c->bsum,       &c->entries,     &c->edge_w,    &c->partial,    &c->counters,    &c->tri_count,
                             &c->tri_fill,   &c->tri_off,     &c->tri_bsum,     &c->sorted,      &c->flags,
                             &c->flog.frag,  &c->flog.bary,   &c->flog.counts, &c->rlog.frag, &c->rlog.bary,  &c->rlog.counts,
-                            &c->masks,      &c->sum,       &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
+                            &c->masks,      &c->ssim,        &c->chunk_base, &c->fwd_weights, &c->gvert,     &c->gtex};
     int64_t n = 0;
     for (const DevBuf* b : bufs) n += static_cast<int64_t>(b->bytes);
     *bytes = n;
@@ -1630,18 +1628,20 @@ soup_status soup_loss_l1_ssim(soup_ctx* c, const float* color, const float* targ
     HIP_TRY(c, hipSetDevice(c->device));
     // records for the largest view, or for as many views as 4 Mpixel hold (192 MB) where that is more; where
     // that is not to be had (static mode, memory) the views share fewer launches
-    constexpr size_t kRecord = 12 * sizeof(float);
+    constexpr size_t kRecord = 12 * sizeof(float), kParts = (kSumParts + 2) * sizeof(double);   // (16-byte multiples)
     int64_t stat_pixels = std::max(maxp, std::min<int64_t>(P, int64_t(1) << 22));
-    if (c->fixed) stat_pixels = std::max(maxp, std::min(stat_pixels, static_cast<int64_t>(c->ssim.bytes / kRecord)));
-    st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * kRecord);
+    if (c->fixed && c->ssim.bytes > kParts)
+        stat_pixels = std::max(maxp, std::min(stat_pixels, static_cast<int64_t>((c->ssim.bytes - kParts) / kRecord)));
+    st = ensure(c, c->ssim, kParts + static_cast<size_t>(stat_pixels) * kRecord);
     if (st == SOUP_ERR_OOM && stat_pixels > maxp) {
         stat_pixels = maxp;
         c->err.clear();
-        st = ensure(c, c->ssim, static_cast<size_t>(stat_pixels) * kRecord);
+        st = ensure(c, c->ssim, kParts + static_cast<size_t>(stat_pixels) * kRecord);
     }
     if (st) return st;
-    loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P, static_cast<float*>(c->ssim.p),
-                        stat_pixels, static_cast<double*>(c->sum.p), true, static_cast<hipStream_t>(stream));
+    loss_l1_ssim_launch(c, color, target, v, lambda, grad_color, grad_logp, loss, P,
+                        reinterpret_cast<float*>(static_cast<char*>(c->ssim.p) + kParts), stat_pixels,
+                        static_cast<double*>(c->ssim.p), true, static_cast<hipStream_t>(stream));
     HIP_TRY(c, hipGetLastError());
     return SOUP_OK;
 }

@@ -44,16 +44,18 @@ class Batch:
     handle: object             # backend's completion handle
 
 
-def request_bytes(width: int, height: int, n_tris: int) -> int:
+def request_bytes(width: int, height: int, n_tris: int, n_params: int = 0) -> int:
     """Device bytes a request needs while in flight, an upper bound: its
     colour output (12 B/px) and an allowance of 8 B/px for the per-tile
     counters and offsets and, in large batches, the binning chunks' per-tile
     slots; 128 B per triangle for its 64-byte setup record and its tile-list
-    entries (the library's workspaces grow with 25% headroom). The GPU tests
+    entries; 5 B per parameter of its decoder for the parameters in the order
+    the matrix cores take them (the library's workspaces grow with 25%
+    headroom). The GPU tests
     check it against what a render actually allocates: its colour buffer
     plus the workspaces of a fresh context."""
     P = int(width) * int(height)
-    return P * (12 + 8) + int(n_tris) * 128
+    return P * (12 + 8) + int(n_tris) * 128 + int(n_params) * 5
 
 
 class Scheduler:
@@ -163,7 +165,7 @@ class Server:
         self.t0 = time.perf_counter()
 
     def need(self, soup: int, view) -> int:
-        return request_bytes(view.width, view.height, self.soups[soup].T)
+        return request_bytes(view.width, view.height, self.soups[soup].T, self.soups[soup].n_params())
 
     def tune_tiles(self, views: Sequence, reps: int = 5) -> Dict[tuple, dict]:
         """For each distinct resolution among ``views``, time one render of
