@@ -350,7 +350,8 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, bool forward, hipStream_t s
         (st = ensure(c, c->bsum, static_cast<size_t>((p.n_tiles + 1023) / 1024 + 1) * 8)) ||
         (st = ensure(c, c->counters, kCountersBytes + kWorkCounters * kWorkStride * 4)) ||
         (st = ensure(c, c->flags, 256)) || (st = ensure_host(c, vbytes + sbytes)) ||
-        (forward && (st = ensure(c, c->fwd_weights, fwd_weights_bytes(p.kind) * p.scenes.size()))))
+        // (a backward's binning sizes it too: a static-mode forward may follow)
+        (st = ensure(c, c->fwd_weights, fwd_weights_bytes(p.kind) * p.scenes.size())))
         return st;
     if (!c->flags_ready) {   // first allocation (never in static mode): clear the sticky flags
         launch_fill_i32(static_cast<int32_t*>(c->flags.p), 64, 0, s);
