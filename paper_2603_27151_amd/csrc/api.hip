@@ -868,17 +868,24 @@ soup_status empty_backward(soup_ctx* c, float* grad_mlp, int n_params, const Opt
 
 // Backward, part 1: the fragments the backward needs, from the forward's log or a walk, sorted by
 // triangle into c->sorted, with c->tri_off the triangles' ranges. z: what else the backward needs
-// cleared before its decode.
+// cleared before its decode. spare: a log that a static-mode repeat of the call would take instead
+// (the forward's where it overflowed: in static mode it is cut and flagged), or null.
 soup_status sorted_fragments(soup_ctx* c, const Plan& p, const Opts& o, const uint64_t* vis, const float* grad_color,
-                             const float* grad_logp, const float2* edge_w, int T, bool from_log, ZeroList& z,
-                             hipStream_t s) {
+                             const float* grad_logp, const float2* edge_w, int T, bool from_log,
+                             const soup_ctx::FragLog* spare, ZeroList& z, hipStream_t s) {
     soup_status st;
     if (!from_log && (st = replay(c, p, o, vis, grad_color, grad_logp, edge_w, false, s))) return st;
     const soup_ctx::FragLog& g = from_log ? c->flog : c->rlog;
     const FragLogView L = log_view(g);
     // the sorted list has at most as many entries as the log holds
-    if ((st = ensure(c, c->sorted, static_cast<size_t>(g.regions) * g.region * sizeof(FragRec))) ||
-        (st = ensure(c, c->masks, static_cast<size_t>(g.regions) * log_slots(L.region) * sizeof(ulonglong2))) ||
+    size_t entries = static_cast<size_t>(g.regions) * g.region;
+    size_t slots = static_cast<size_t>(g.regions) * log_slots(L.region);
+    if (spare && !c->fixed) {
+        entries = std::max(entries, static_cast<size_t>(spare->regions) * spare->region);
+        slots = std::max(slots, static_cast<size_t>(spare->regions) * log_slots(static_cast<uint32_t>(spare->region)));
+    }
+    if ((st = ensure(c, c->sorted, entries * sizeof(FragRec))) ||
+        (st = ensure(c, c->masks, slots * sizeof(ulonglong2))) ||
         (st = ensure(c, c->tri_count, static_cast<size_t>(T) * 4)) ||
         (st = ensure(c, c->tri_fill, static_cast<size_t>(T) * 8)) ||
         (st = ensure(c, c->tri_off, static_cast<size_t>(T + 1) * 8)) ||
@@ -1034,15 +1041,15 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     }
     // the last forward's fragment log, if it was made with these draws
     bool from_log = false;
-    if (reused && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode &&
-        (st = log_usable(c, &from_log)))
-        return st;
+    const bool log_here = reused && c->log_valid && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode;
+    if (log_here && (st = log_usable(c, &from_log))) return st;
+    const soup_ctx::FragLog* const spare = log_here && !from_log ? &c->flog : nullptr;
     ZeroList z;
     if (!o.accumulate) {
         z.add(grad_feats, static_cast<int64_t>(T) * n_grid);
         z.add(grad_verts, static_cast<int64_t>(T) * 9);
     }
-    if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, z, s))) return st;
+    if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, spare, z, s))) return st;
     const int nb = decode_blocks(c, c->fixed ? -1 : static_cast<int64_t>((from_log ? c->flog : c->rlog).total));
     {
         DecodeArgs d = decode_args(c, p, a);
@@ -1256,9 +1263,9 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         ew = static_cast<float2*>(c->edge_w.p);
     }
     bool from_log = false;
-    if (reused && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode &&
-        (st = log_usable(c, &from_log)))
-        return st;
+    const bool log_here = reused && c->log_valid && c->log_seed == o.seed && c->log_step == o.step && c->log_mode == o.mode;
+    if (log_here && (st = log_usable(c, &from_log))) return st;
+    const soup_ctx::FragLog* const spare = log_here && !from_log ? &c->flog : nullptr;
     ZeroList z;
     z.add(c->gvert.p, static_cast<int64_t>(T) * 18);
     if (fused) {
@@ -1272,7 +1279,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     if (sorted_path) {
         // every winner and, where the pixel carries a score weight, every fragment in
         // front of it (Eq. (9)), sorted by triangle
-        if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, z, s))) return st;
+        if ((st = sorted_fragments(c, p, o, vis, grad_color, gl, ew, T, from_log, spare, z, s))) return st;
         Timed t(c, SOUP_T_BWD, s);
         PTriArgs ta{};
         ta.views = a.views;
