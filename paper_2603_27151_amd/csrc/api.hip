@@ -491,12 +491,6 @@ soup_status finish_stats(soup_ctx* c, hipStream_t s, bool raster = true) {
     return SOUP_OK;
 }
 
-int persistent_blocks(soup_ctx* c, const Plan& p) {
-    const int64_t want = static_cast<int64_t>(c->num_cus) * 4;
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, p.n_tiles)));
-}
-
-
 soup_status plan_single(soup_ctx* c, Plan& p, const soup_scene* scene, const soup_views* views) {
     soup_status st = check_scene(c, scene, &p.kind);
     if (st) return st;

@@ -260,24 +260,7 @@ __device__ __forceinline__ void dense(cfloat* __restrict__ W, cfloat* __restrict
     }
 }
 
-// Forward of the shared MLP; keeps every hidden activation for a backward.
-template <class S>
-struct MlpAct {
-    float h[S::NH][S::H];
-    float o[4];
-};
-
-template <class S>
-__device__ __forceinline__ void mlp_forward(cfloat* __restrict__ p, const float (&x)[S::C],
-                                            MlpAct<S>& a) {
-    dense<S::C, S::H, true>(p + S::w_off(0), p + S::b_off(0), x, a.h[0]);
-#pragma unroll
-    for (int l = 1; l < S::NH; ++l)
-        dense<S::H, S::H, true>(p + S::w_off(l), p + S::b_off(l), a.h[l - 1], a.h[l]);
-    dense<S::H, 4, false>(p + S::w_off(S::NH), p + S::b_off(S::NH), a.h[S::NH - 1], a.o);
-}
-
-// Lightweight forward (no stored activations beyond one hidden layer).
+// The shared MLP's logits.
 template <class S>
 __device__ __forceinline__ void mlp_logits(cfloat* __restrict__ p, const float (&x)[S::C],
                                            float (&o)[4]) {
@@ -365,18 +348,5 @@ __device__ __forceinline__ void store_host(T* p, T v) {
 // the same launch needs a release per workgroup, which writes the L2 back each
 // time: the L2 loss of 64 views took 563 us instead of 206.)
 constexpr int kSumParts = 2048;   // workgroups of such a launch at most
-
-// Binary search: index v with base[v] <= x < base[v+1] over V entries.
-template <class T>
-__device__ __forceinline__ int find_segment(const ViewDesc* __restrict__ views, int V, int64_t x,
-                                            T ViewDesc::*field) {
-    int lo = 0, hi = V - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (views[mid].*field <= x) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
 
 }  // namespace soup
