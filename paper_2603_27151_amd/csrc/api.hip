@@ -735,17 +735,19 @@ soup_status soup_last_stats(const soup_ctx* c, soup_stats* out) {
 
 namespace {
 
-// Persistent grid of the decode kernel, workgroups of four waves: as many as are resident
-// with the 16->32->32->4 decoder, two per CU (64 views: 2.71 ms; four 2.75, and twice the rows
+// Persistent grid of the decode kernel, workgroups of four waves: two per CU, as many as are
+// resident with the 16->32->32->4 decoder (64 views: 2.71 ms; four 2.75, and twice the rows
 // of partial sums; three 3.35, the third waits for the first two), fewer where the
-// fragments (an upper bound; -1: unknown) give each wave less than a batch of 64.
+// fragments (an upper bound; -1: unknown) give each wave less than a batch of 64. Of the
+// 32->64->64->4 decoder, whose LDS leaves room for one, the second half starts behind the
+// first (200,000 triangles, 16 views 1080p: 8.29 ms; one per CU 8.20).
 int decode_blocks(soup_ctx* c, int64_t fragments) {
     const int64_t most = 2 * static_cast<int64_t>(std::max(1, c->num_cus));
     return static_cast<int>(fragments < 0 ? most : std::max<int64_t>(1, std::min(most, (fragments + 255) / 256)));
 }
 
 // The view of a log that its readers take. A region's batches are shared by as many waves as
-// give each about eight, and down to one each while the waves do not fill the GPU (a batch is a
+// give each about eight, and down to one each while there are fewer than 8,192 waves (a batch is a
 // chain of dependent loads and an atomic: 128 x 128 pixels, count 10.2 -> 5.4 us, place
 // 11.1 -> 5.1; a view of 10,000 triangles 7.7 -> 6.0 and 11.0 -> 8.7).
 FragLogView log_view(const soup_ctx::FragLog& g) {

@@ -342,7 +342,7 @@ __device__ __forceinline__ void store_host(T* p, T v) {
     if (p) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// A scalar sum over a launch: every workgroup leaves its part, in double, and a
+// A loss's sum over a launch: every workgroup leaves its part, in double, and a
 // one-workgroup launch adds them in order. (A float32 atomic per workgroup left
 // the losses up to 2e-6 off; the last workgroup to arrive adding the parts in
 // the same launch needs a release per workgroup, which writes the L2 back each

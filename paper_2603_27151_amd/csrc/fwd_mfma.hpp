@@ -21,9 +21,9 @@
 //
 // What bounds it: 64 fragments of 16->32->32->4 are 48 products of 64 cycles
 // and 32 of 8, 3.3 k cycles of a SIMD's matrix pipe, where the same chain on
-// the vector ALU was 1,664 instructions of 4 cycles (6.7 k) that nothing else
-// of the SIMD could use; the walk's vector work of the other waves now runs
-// beside the decode. The weights are laid out as A operands once per call and
+// the vector ALU was 1,664 instructions of 4 cycles (6.7 k). (The walk's vector
+// work of the SIMD's other waves does not run beside the products: float32
+// matrix and vector instructions take turns.) The weights are laid out as A operands once per call and
 // read by 16-byte loads, four steps each: a wave keeps those of 16->32->32->4
 // in registers while it stays with one scene and reads the 26 KB of
 // 32->64->64->4 from the caches. Forward kernels before and now: 64 views,

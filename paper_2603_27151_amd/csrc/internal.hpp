@@ -80,8 +80,8 @@ struct RasterArgs {
     uint2* log_bary;               // (b1, b2)
     uint32_t log_region;
     uint32_t* log_counts;
-    // the walk with the winners known: what it logs (sel.vis null: a forward), and the pixels'
-    // gradients, which decide whether a winner without a score weight is needed
+    // the walk with the winners known (MlpKind::kReplay, else unused): the saved winners, and the
+    // pixels' gradients, which decide whether a winner without a score weight is needed
     const uint64_t* replay_vis;
     const float* replay_color;     // [P,3] or null (every pixel is needed)
     const float* replay_logp;      // [P] score weights or null
@@ -126,8 +126,8 @@ struct FragLogView {
 // 64-entry batches of one region.
 __host__ __device__ constexpr uint32_t log_slots(uint32_t region) { return (region + 63) / 64; }
 // Workgroups of four waves for the kernels that read a log: one wave per share of a
-// region, at most eight workgroups per CU of this GPU (four views of 50,000 triangles: placing
-// 39 us with four, 32 with eight; 64 views the same).
+// region, at most 2,048 workgroups, eight for each of the MI355X's 256 CUs (four views of
+// 50,000 triangles: placing 39 us with four per CU, 32 with eight; 64 views the same).
 inline unsigned log_blocks(const FragLogView& L) {
     const int64_t waves = static_cast<int64_t>(L.n_regions) * L.split;
     return static_cast<unsigned>(waves < 4 ? 1 : waves > 8192 ? 2048 : (waves + 3) / 4);

@@ -1,11 +1,12 @@
 // Building blocks shared by the forward and backward kernels.
 //
-// Edge functions are evaluated in float64. Every operand is an integer below
-// 2^51 (snapped coordinates are bounded by 2^24, so products of differences
-// are below 2^50), so each value, including the incremental form
+// A fragment's edge functions are evaluated in float64. Every operand is an
+// integer below 2^51 (snapped coordinates are bounded by 2^24, so products of
+// differences are below 2^50), so each value, including the incremental form
 // E(x, y) = E(x0, y0) + dx * a + dy * b, is exact and equals the int64 edge
-// function of the contract; the tie rule and the conversion to float for the
-// barycentrics therefore match it bit for bit.
+// function of the contract; the conversion to float for the barycentrics
+// therefore matches it bit for bit. (Coverage takes its signs, with the tie
+// rule, from 32-bit integers: raster_fwd_impl.hpp.)
 #pragma once
 
 #include "internal.hpp"

@@ -7,8 +7,9 @@
 //        G1 = dS/dmu_x - 2 mu_x dS/dsigma_x^2 - mu_y dS/dsigma_xy,
 //        G2 = dS/dsigma_x^2,   G3 = dS/dsigma_xy,
 //    so that dS(q)/dx_p = w(p - q) (G1(q) + 2 x_p G2(q) + y_p G3(q)). It also
-//    writes each pixel's share of the loss (the score term's weight) and adds
-//    the loss into a scalar.
+//    writes each pixel's share of the loss (the score term's weight), and each
+//    workgroup the sum of its shares, in double.
+//  * loss_sum_kernel: the loss from the workgroups' sums.
 //  * ssim_grad_kernel: dL/dC = lambda sign(C - T) / (3P) minus
 //    (1 - lambda) / (3P) times the window sums of G1, G2, G3 around p.
 //    One thread per pixel of a 32 x 8 tile; the window is applied as two
@@ -73,8 +74,9 @@ __device__ __forceinline__ SsimView ssim_view(const SsimBatch& b, int tile, int&
     return v;
 }
 
-// All views of a batch in one launch, tiles dealt to a grid that is resident as
-// a whole: a launch per view left the GPU part empty for small views, and one
+// All views of a batch in one launch, tiles dealt by stride to at most kSumParts
+// workgroups, two rounds of the four per CU that the LDS (39 KB) admits: a launch
+// per view left the GPU part empty for small views, and one
 // float atomic per 32 x 8 tile on the loss queued behind each other. The two
 // passes' sums are fused multiply-adds: VALU work bounds both kernels, and a
 // separate multiply and add was twice the instructions (four views, 1.96 Mpixel:
