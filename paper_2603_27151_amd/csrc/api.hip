@@ -1232,7 +1232,7 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
     if (T == 0) return empty_backward(c, grad_mlp, kPParams, o, s);
     const int64_t n_tex = static_cast<int64_t>(T) * mc_count(scene->R) * kPCh;
     // the triangle-sorted path keeps one triangle's texture gradient per wave in LDS
-    // (36 KB at R = 5, with the levels' restriction 10); a texture too large for that
+    // (18 KB at R = 5, with the levels' restriction 11); a texture too large for that
     // takes the per-pixel path with global atomics
     const bool sorted_path = ptri_sorted(scene->R);
     // levels: folded into the sorted path's flush; otherwise the texture gradient goes
