@@ -263,6 +263,16 @@ soup_status check_log_pixels(soup_ctx* c, const char* what, int64_t n_pix) {
     return SOUP_OK;
 }
 
+// An eager call reads on the host what its kernels found, which a stream that captures does not run:
+// refused before anything is enqueued or kept.
+soup_status check_capture(soup_ctx* c, hipStream_t s) {
+    if (c->fixed || !s) return SOUP_OK;   // (the null stream cannot capture)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_TRY(c, hipStreamIsCapturing(s, &capture));
+    if (capture == hipStreamCaptureStatusNone) return SOUP_OK;
+    return fail(c, SOUP_ERR_HIP, "the stream is capturing: only static-mode calls can be captured");
+}
+
 Opts to_opts(const soup_opts* o) {
     Opts r{};
     r.seed = o->seed;
@@ -333,6 +343,7 @@ soup_status bin(soup_ctx* c, Plan& p, const Opts& o, bool forward, hipStream_t s
     const int chunk = bin_chunk_size(static_cast<int>(p.views.size()), p.maxT, c->num_cus);
     const int stride = bin_stride(chunk, p.n_tiles);
     soup_status st;
+    if ((st = check_capture(c, s))) return st;
     // the forward counts its regions in 32 bits, a wave adds its grid to an index, and every wave fetches
     // one index past the last
     if (p.n_tiles * fwd_regions_per_tile(c->tile, 8) >=
@@ -1009,7 +1020,9 @@ soup_status soup_rasterize_bwd(soup_ctx* c, const soup_scene* scene, const soup_
     if ((st = check_opts(c, opts))) return st;
     if (!vis || !color || !grad_color) return fail(c, SOUP_ERR_INVALID, "vis, color and grad_color are required");
     if (!grad_verts || !grad_feats || !grad_mlp) return fail(c, SOUP_ERR_INVALID, "gradient outputs are required");
-    if ((st = check_decode_lds(c, p.kind, p.G)) || (st = check_log_pixels(c, "backward", p.n_pix))) return st;
+    if ((st = check_decode_lds(c, p.kind, p.G)) || (st = check_log_pixels(c, "backward", p.n_pix)) ||
+        (st = check_capture(c, s)))
+        return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
     bool reused = false;
@@ -1216,7 +1229,8 @@ static soup_status pbackward_impl(soup_ctx* c, const soup_pscene* scene, const s
         }
     }
     // (the per-pixel path takes its score term alone from a log)
-    if ((ptri_sorted(scene->R) || (grad_logp && opts->mode == 0)) && (st = check_log_pixels(c, "backward", p.n_pix)))
+    if ((ptri_sorted(scene->R) || (grad_logp && opts->mode == 0)) &&
+        ((st = check_log_pixels(c, "backward", p.n_pix)) || (st = check_capture(c, s))))
         return st;
     HIP_TRY(c, hipSetDevice(c->device));
     const Opts o = to_opts(opts);
