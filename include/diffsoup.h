@@ -51,7 +51,7 @@ typedef enum {
  * the RGB logits and the opacity logit; colour = sigmoid(o0..o2),
  * alpha = sigmoid(o3)). */
 typedef struct {
-    int32_t T;                 /* triangles, >= 0 */
+    int32_t T;                 /* triangles, >= 0; an empty soup's device pointers may be NULL */
     int32_t G;                 /* feature grid side, >= 2; G * G * C <= 4096 (else SOUP_ERR_UNSUPPORTED) */
     int32_t C;                 /* feature channels = dims[0] */
     int32_t n_layers;          /* MLP layers (linear maps), >= 1 */
@@ -157,6 +157,8 @@ soup_status soup_read_timings(soup_ctx* ctx, double* ms, int64_t* count);
  * fragments) are bounded by the capacity in place. A call that would exceed
  * it produces no fragments for the overflowing part and sets a sticky flag
  * instead of failing. Counting and timing must be off.
+ * Outside static mode a call that reads its lists' sizes on the host is
+ * refused on a capturing stream (SOUP_ERR_HIP), before any work.
  * soup_ctx_check synchronises the device, returns SOUP_ERR_CAPACITY (and
  * clears the flag) if any static-mode call since the last check overflowed,
  * else SOUP_OK; the caller then reruns outside static mode, which grows the
